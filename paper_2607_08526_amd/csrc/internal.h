@@ -95,7 +95,7 @@ struct W8Args {
     int M, N, K;
     int tiles_m, tiles_n;
 };
-hipError_t launch_qgemm_w8a8(const W8Args &a, hipStream_t stream);
+hipError_t launch_qgemm_w8a8(const W8Args &a, int cus, hipStream_t stream);
 
 // Fused self-attention (attention.hip), head dimension 64: Q, K, V bf16
 // rows with strides (elements, multiples of 8), O fp32 or bf16.

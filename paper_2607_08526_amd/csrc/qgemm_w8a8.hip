@@ -12,16 +12,18 @@
 // Each 32 x 32 output tile of a 32-k block is one v_mfma_i32_32x32x32_i8
 // (exact), converted and folded into an fp32 accumulator with one FMA per
 // output (scale of the lane's column); s_x[m] and the layer epilogue are
-// applied at the store.  The per-block rescale is what bounds this kernel:
-// 16 outputs per lane per MFMA cost two VALU instructions each, several
-// times the MFMA's own issue time.
+// applied at the store.  The per-block rescale is what bounds this path:
+// 16 outputs per lane per MFMA cost two VALU instructions each (128 issue
+// cycles against the MFMA's 32), so a kernel can at best keep every SIMD's
+// VALU issuing: M N K / 32 * 2 lane operations.
 //
-// Tiling: 128 x 128 outputs per workgroup of 4 wavefronts (64 x 64 each,
-// 2 x 2 MFMA tiles), K in stages of 64 (two blocks) double-buffered in LDS
-// through registers; rows padded to 80 bytes so that the 32 rows an operand
-// read touches spread over the LDS banks.
+// Two kernels.  qgemm_w8a8_pipe_kernel takes K % 64 == 0 with 4-byte aligned
+// scales; qgemm_w8a8_kernel the rest (an odd number of blocks, scales at odd
+// 2-byte addresses).
+#include "dma.h"
 #include "epilogue.h"
 #include "internal.h"
+#include <type_traits>
 
 namespace qlk {
 namespace {
@@ -51,6 +53,10 @@ __device__ inline int xcd_tile(int p, int T)
     return xcd < r ? xcd * (q + 1) + idx : r * (q + 1) + (xcd - r) * q + idx;
 }
 
+// General kernel: 128 x 128 outputs per workgroup of 4 wavefronts (64 x 64
+// each, 2 x 2 MFMA tiles), K in stages of 64 (two blocks) double-buffered in
+// LDS through registers; rows padded to 80 bytes so that the 32 rows an
+// operand read touches spread over the LDS banks.
 __global__ __launch_bounds__(THREADS, 2) void qgemm_w8a8_kernel(const W8Args a)
 {
     __shared__ __align__(16) uint8_t lds[2 * STAGE];
@@ -179,11 +185,352 @@ __global__ __launch_bounds__(THREADS, 2) void qgemm_w8a8_kernel(const W8Args a)
         }
 }
 
+// Pipelined kernel (K % 64 == 0, K < 2^23, scales 4-byte aligned).
+//
+// A workgroup is KG groups of WM x WN wavefronts; every wavefront owns 64 x
+// (32 NJ) outputs (2 x NJ MFMA tiles), the groups the same (64 WM) x (32 NJ
+// WN) output tile over interleaved 64-k steps, and their fp32 sums are added
+// through LDS in group order at the end.  K groups are how a product with
+// few output tiles (a 1536-wide layer at 1290 tokens has 132 of 128 x 128)
+// still gives every SIMD four wavefronts without partial sums in memory.
+//
+// Four wavefronts per SIMD because one wavefront issues a VALU instruction
+// every ~5 cycles at best, while the SIMD takes an fp32 add or FMA from
+// another wavefront every 2 (v_fma_mix_f32 and the int-to-float conversion
+// take 4: hence the explicit fp32 scales and the seeded accumulators below).
+//
+// Activations, codes and scales go to LDS by direct-to-LDS loads through a
+// ring of NST stages of SB steps per group: at least 128 contiguous bytes of
+// every row (64-byte rows took 10-20% longer: the traffic from L2, 6-8 TB/s
+// here, is the second bound).  A stage's loads go out one behind each MFMA:
+// issued together they hold every wavefront up at the top of the step.
+// Within a step the MFMA of a tile is issued before the 32 rescale
+// instructions of the tile before it, so that the VALU always has work.
+template <int NJ_, int WM_, int WN_, int KG_, int SB_, int NST_, int OCC_>
+struct PipeGeo {
+    static constexpr int NJ = NJ_, WM = WM_, WN = WN_, KG = KG_, SB = SB_, NST = NST_, OCC = OCC_;
+    static constexpr int NT = 64 * WM * WN * KG;        // threads of a workgroup
+    static constexpr int TM = 64 * WM, TN = 32 * NJ * WN;  // output tile
+    static constexpr int NS = KG * SB;                  // 64-k steps per stage
+    static constexpr int RB = 64 * NS, CH = RB / 16;    // bytes and chunks per row and stage
+    static constexpr int XB = TM * RB, WB = TN * RB;    // operand bytes per stage
+    static constexpr int XL = XB / 16 / NT, WL = WB / 16 / NT;
+    static constexpr int SL = (TN * NS + NT - 1) / NT;  // scale loads (4 bytes each)
+    static constexpr int LOADS = XL + WL + SL;          // per thread and stage
+    static constexpr int STAGE = XB + WB + SL * NT * 4;
+    static constexpr int RED = KG > 1 ? KG * TM * TN * 4 : NT / 64 * 4096;  // output staging
+    static constexpr int LDS = NST * STAGE > RED ? NST * STAGE : RED;
+    static_assert(XB % (16 * NT) == 0 && WB % (16 * NT) == 0, "whole loads per thread");
+    static_assert(LDS <= 160 * 1024, "LDS of a CU");
+};
+
+// 16-byte chunk swizzle of a row of CH chunks: the fragment reads of 16
+// consecutive lanes (rows, one logical chunk) fall on distinct banks
+template <int CH>
+__device__ inline int row_swz(int row)
+{
+    return CH >= 16 ? row & 15
+         : CH == 8  ? (row & 7) ^ ((row >> 3) & 1)
+                    : ((row >> 1) ^ (row >> 3)) & 3;
+}
+
+template <class G>
+__global__ __launch_bounds__(G::NT, G::OCC) void qgemm_w8a8_pipe_kernel(const W8Args a)
+{
+    __shared__ __align__(16) uint8_t ring[G::LDS];
+    const int T = a.tiles_m * a.tiles_n;
+    const int tile = xcd_tile((int)blockIdx.x, T);
+    const int per_group = GROUP_M * a.tiles_n;
+    const int first_m = (tile / per_group) * GROUP_M;
+    const int gsz = min(a.tiles_m - first_m, GROUP_M);
+    const int within = tile % per_group;
+    const int m0 = (first_m + within % gsz) * G::TM, n0 = (within / gsz) * G::TN;
+
+    const int M = a.M, N = a.N, K = a.K, nb = K / 32;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kg = wave / (G::WM * G::WN), gw = wave % (G::WM * G::WN);
+    const int wm = (gw / G::WN) * 64, wn = (gw % G::WN) * 32 * G::NJ;
+
+    const uint8_t *const xb = reinterpret_cast<const uint8_t *>(a.qx) + (int64_t)m0 * K;
+    const uint8_t *const cb = reinterpret_cast<const uint8_t *>(a.codes) + (int64_t)n0 * K;
+    const uint8_t *const sb = reinterpret_cast<const uint8_t *>(a.scales) + (int64_t)n0 * nb * 2;
+    // loads: slot r * NT + tid holds chunk (slot % CH) ^ swizzle of row slot
+    // / CH; rows past the edge repeat the last one (their outputs are never
+    // stored), chunks past K the last one (their scales are taken as 0)
+    uint32_t xrow[G::XL], wrow[G::WL], srow[G::SL];
+    int xk[G::XL], wk[G::WL], sk[G::SL];
+#pragma unroll
+    for (int r = 0; r < G::XL; ++r) {
+        const int slot = r * G::NT + tid, row = slot / G::CH;
+        xrow[r] = (uint32_t)((min(m0 + row, M - 1) - m0) * K);
+        xk[r] = ((slot % G::CH) ^ row_swz<G::CH>(row)) * 16;
+    }
+#pragma unroll
+    for (int r = 0; r < G::WL; ++r) {
+        const int slot = r * G::NT + tid, row = slot / G::CH;
+        wrow[r] = (uint32_t)((min(n0 + row, N - 1) - n0) * K);
+        wk[r] = ((slot % G::CH) ^ row_swz<G::CH>(row)) * 16;
+    }
+#pragma unroll
+    for (int r = 0; r < G::SL; ++r) {
+        const int slot = (r * G::NT + tid) % (G::TN * G::NS);
+        srow[r] = (uint32_t)((min(n0 + slot / G::NS, N - 1) - n0) * nb * 2);
+        sk[r] = (slot % G::NS) * 4;
+    }
+
+    const int steps = K / 64, iters = (steps + G::NS - 1) / G::NS;
+    // the q-th load (of LOADS) of iteration it
+    auto issue = [&](int it, int q) {
+        const uint32_t base = dma_lds(ring + (it % G::NST) * G::STAGE);
+        if (q < G::XL)
+            dma_load16(xb, xrow[q] + (uint32_t)min(it * G::RB + xk[q], K - 16),
+                       base + (q * G::NT + wave * 64) * 16);
+        else if (q < G::XL + G::WL)
+            dma_load16(cb, wrow[q - G::XL] + (uint32_t)min(it * G::RB + wk[q - G::XL], K - 16),
+                       base + G::XB + ((q - G::XL) * G::NT + wave * 64) * 16);
+        else
+            dma_load4(sb,
+                      srow[q - G::XL - G::WL] +
+                          (uint32_t)min(it * G::NS * 4 + sk[q - G::XL - G::WL], (steps - 1) * 4),
+                      base + G::XB + G::WB + ((q - G::XL - G::WL) * G::NT + wave * 64) * 4);
+    };
+#pragma unroll
+    for (int it = 0; it < G::NST - 1; ++it)
+        if (it < iters)
+#pragma unroll
+            for (int q = 0; q < G::LOADS; ++q)
+                issue(it, q);
+
+    float acc[2][G::NJ][16];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < G::NJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                acc[i][j][r] = 0.0f;
+    constexpr int TT = 2 * G::NJ;  // MFMA tiles of a block
+    // Every MFMA accumulates onto the bit pattern of 1.5 * 2^23: the sum S
+    // (|S| <= 32 * 128 * 128 < 2^22) then reads as the float 1.5 * 2^23 + S,
+    // and one exact subtraction converts it (v_cvt_f32_i32 issues at a
+    // quarter of that rate).  The seed is opaque to the compiler so that it
+    // stays in registers instead of being rebuilt for each MFMA.
+    constexpr int SEED = 0x4B400000;
+    constexpr float SEEDF = 12582912.0f;
+    i32x16 seed = {SEED, SEED, SEED, SEED, SEED, SEED, SEED, SEED,
+                   SEED, SEED, SEED, SEED, SEED, SEED, SEED, SEED};
+    dma_pin(seed);
+    // the tile whose rescale runs behind the next tile's MFMA
+    i32x16 pend = seed;
+    float pend_s = 0.0f;
+
+    // One iteration; REFILL: a stage NST - 1 ahead is left to load (a
+    // compile-time condition, so that the step stays one basic block and the
+    // compiler keeps the order written here).
+    auto step = [&](int it, auto refill) {
+        constexpr bool REFILL = decltype(refill)::value;
+        // every LDS read of the previous stage has completed; this one landed
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if constexpr (REFILL)
+            __builtin_amdgcn_s_waitcnt(dma_vmcnt((G::NST - 2) * G::LOADS));
+        else
+            dma_wait<G::LOADS, G::NST - 2>(iters - 1 - it);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");  // no LDS read moves above the barrier
+        // the slot of the previous stage is free: its refill goes out one
+        // load behind each MFMA (together they would hold the wavefronts up
+        // at the top of the step, the address unit taking 16 to 64 cycles each)
+        const uint8_t *const st = ring + (it % G::NST) * G::STAGE;
+        // blocks 0 .. 2 SB - 1 of the group's steps of the stage
+        constexpr int NB = 2 * G::SB;
+        float sc[NB][G::NJ];
+#pragma unroll
+        for (int u = 0; u < G::SB; ++u) {
+            const int sub = kg * G::SB + u;
+            const bool live = it * G::NS + sub < steps;
+#pragma unroll
+            for (int j = 0; j < G::NJ; ++j) {
+                uint32_t w = *reinterpret_cast<const uint32_t *>(
+                    st + G::XB + G::WB + ((wn + 32 * j + l32) * G::NS + sub) * 4);
+                w = live ? w : 0u;
+                sc[2 * u][j] = f16_value((uint16_t)(w & 0xFFFFu));
+                sc[2 * u + 1][j] = f16_value((uint16_t)(w >> 16));
+                dma_pin(sc[2 * u][j]);
+                dma_pin(sc[2 * u + 1][j]);
+            }
+        }
+        // operands of block blk, two blocks alternating
+        i32x4 av[2][2], bv[2][G::NJ];
+        auto read = [&](int blk) {
+            const int lc = 4 * (kg * G::SB + blk / 2) + 2 * (blk & 1) + hi;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int xr = wm + 32 * i + l32;
+                av[blk & 1][i] = *reinterpret_cast<const i32x4 *>(
+                    st + xr * G::RB + (lc ^ row_swz<G::CH>(xr)) * 16);
+            }
+#pragma unroll
+            for (int j = 0; j < G::NJ; ++j) {
+                const int wr = wn + 32 * j + l32;
+                bv[blk & 1][j] = *reinterpret_cast<const i32x4 *>(
+                    st + G::XB + wr * G::RB + (lc ^ row_swz<G::CH>(wr)) * 16);
+            }
+        };
+        read(0);
+#pragma unroll
+        for (int blk = 0; blk < NB; ++blk)
+#pragma unroll
+            for (int t = 0; t < TT; ++t) {
+                const int i = t / G::NJ, j = t % G::NJ;
+                i32x16 d = __builtin_amdgcn_mfma_i32_32x32x32_i8(av[blk & 1][i], bv[blk & 1][j],
+                                                                 seed, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (blk + 1 < NB && t == 0)
+                    read(blk + 1);
+                if constexpr (REFILL)
+#pragma unroll
+                    for (int q = blk * TT + t; q < G::LOADS; q += NB * TT)
+                        issue(it + G::NST - 1, q);
+                // the tile before this one (the previous block's last for t = 0)
+                const int pt = (t + TT - 1) % TT, pi = pt / G::NJ, pj = pt % G::NJ;
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    acc[pi][pj][r] = __builtin_fmaf(pend_s, __int_as_float(pend[r]) - SEEDF,
+                                                    acc[pi][pj][r]);
+                pend = d;
+                pend_s = sc[blk][j];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+    };
+    int it = 0;
+#pragma unroll 1
+    for (; it + G::NST - 1 < iters; ++it)
+        step(it, std::true_type{});
+#pragma unroll 1
+    for (; it < iters; ++it)
+        step(it, std::false_type{});
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        acc[1][G::NJ - 1][r] = __builtin_fmaf(pend_s, __int_as_float(pend[r]) - SEEDF,
+                                              acc[1][G::NJ - 1][r]);
+
+    // Output: row 8 (r / 4) + 4 hi + r % 4, column l32 of each 32 x 32 tile.
+    // The K groups' tiles go to LDS as rows (the ring is free behind the
+    // barrier: every stage issued has been waited for and read), and every
+    // thread sums and stores groups of four columns.  One group: each
+    // wavefront turns one 32 x 32 tile at a time in a patch of its own.
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    const bool vec = epi_vec_ok(a.ep, a.Y, N);
+    auto store4 = [&](int m, int n, f32x4 v) {
+        if (m >= M || n >= N)
+            return;
+        const float sxm = f16_value(a.sx[m]);
+        const int64_t idx = (int64_t)m * N + n;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            v[e] = sxm * v[e];
+        if (vec) {
+            epi_store4(a.ep, a.Y, idx, n, v, false);
+        } else {
+#pragma unroll 1
+            for (int e = 0; e < 4 && n + e < N; ++e)
+                epi_store(a.ep, a.Y, idx + e, n + e, v[e]);
+        }
+    };
+    if constexpr (G::KG > 1) {
+        float *const red = reinterpret_cast<float *>(ring);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < G::NJ; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    red[kg * G::TM * G::TN +
+                        (wm + 32 * i + 8 * (r >> 2) + 4 * hi + (r & 3)) * G::TN + wn + 32 * j +
+                        l32] = acc[i][j][r];
+        __syncthreads();
+#pragma unroll 1
+        for (int q = tid; q < G::TM * G::TN / 4; q += G::NT) {
+            const f32x4 *const src = reinterpret_cast<const f32x4 *>(red) + q;
+            f32x4 v = src[0];
+#pragma unroll
+            for (int g = 1; g < G::KG; ++g)
+                v += src[g * (G::TM * G::TN / 4)];
+            store4(m0 + q / (G::TN / 4), n0 + 4 * (q % (G::TN / 4)), v);
+        }
+    } else {
+        float *const patch = reinterpret_cast<float *>(ring) + (tid >> 6) * 1024;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < G::NJ; ++j) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    patch[(8 * (r >> 2) + 4 * hi + (r & 3)) * 32 + l32] = acc[i][j][r];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int rl = 8 * t + (lane >> 3);
+                    const f32x4 v =
+                        *reinterpret_cast<const f32x4 *>(patch + rl * 32 + 4 * (lane & 7));
+                    store4(m0 + wm + 32 * i + rl, n0 + wn + 32 * j + 4 * (lane & 7), v);
+                }
+            }
+    }
+}
+
+template <class G>
+hipError_t launch_pipe(W8Args &b, hipStream_t stream)
+{
+    b.tiles_m = (b.M + G::TM - 1) / G::TM;
+    b.tiles_n = (b.N + G::TN - 1) / G::TN;
+    const int64_t T = (int64_t)b.tiles_m * b.tiles_n;
+    if (T <= 0 || T >= ((int64_t)1 << 31))
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(qgemm_w8a8_pipe_kernel<G>, dim3((unsigned)T), dim3(G::NT), 0, stream, b);
+    return hipGetLastError();
+}
+
+// The three shapes of the pipelined kernel (all four wavefronts per SIMD):
+//   LARGE  128 x 128 tiles, 8 wavefronts, no K groups, two workgroups per CU:
+//          the least operand traffic per output
+//   MID    64 x 128 tiles, 4 K groups, one workgroup of 16 wavefronts per CU
+//   SMALL  64 x 64 tiles, 8 K groups, likewise
+using PipeLarge = PipeGeo<1, 2, 4, 1, 2, 2, 4>;
+using PipeMid = PipeGeo<1, 1, 4, 4, 1, 3, 4>;
+using PipeSmall = PipeGeo<1, 1, 2, 8, 1, 2, 4>;
+
+// Estimated us of a shape: rounds of one workgroup per CU, each its 64-k
+// steps at the measured rate plus a fixed part (prologue, K-group sums,
+// store).  Fitted on 16 products (M 64 to 2048, N 512 to 8192, K 512 to 8192);
+// measured LARGE / MID / SMALL (before: the general kernel):
+//   1290 x 1536 x 1536   19.5 / 12.6 / 15.2 us  (41.0)
+//   1290 x 1536 x 6144   58.3 / 35.5 / 43.6     (132)
+//   2048 x 8192 x 2048   84.3 / 105  / 126      (116)
+//   64 x 4608 x 1536     17.8 / 10.5 / 7.5      (38.7)
+template <class G>
+double pipe_us(const W8Args &a, double per_step, double fixed, int cus)
+{
+    const int64_t T = (int64_t)((a.M + G::TM - 1) / G::TM) * ((a.N + G::TN - 1) / G::TN);
+    return (double)((T + cus - 1) / cus) * (a.K / 64 * per_step + fixed);
+}
+
 }  // namespace
 
-hipError_t launch_qgemm_w8a8(const W8Args &a, hipStream_t stream)
+hipError_t launch_qgemm_w8a8(const W8Args &a, int cus, hipStream_t stream)
 {
     W8Args b = a;
+    if (a.K % 64 == 0 && a.K < (1 << 23) && ((uintptr_t)a.scales & 3) == 0) {
+        const double large = pipe_us<PipeLarge>(a, 0.62, 0.0, cus) + 4.0;
+        const double mid = pipe_us<PipeMid>(a, 0.32, 2.8, cus) + 2.0;
+        const double small = pipe_us<PipeSmall>(a, 0.20, 1.9, cus) + 2.0;
+        if (large <= mid && large <= small)
+            return launch_pipe<PipeLarge>(b, stream);
+        return mid <= small ? launch_pipe<PipeMid>(b, stream) : launch_pipe<PipeSmall>(b, stream);
+    }
     b.tiles_m = (a.M + BM - 1) / BM;
     b.tiles_n = (a.N + BN - 1) / BN;
     const int64_t T = (int64_t)b.tiles_m * b.tiles_n;

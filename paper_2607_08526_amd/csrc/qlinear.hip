@@ -1254,7 +1254,7 @@ int qlinear_forward_w8a8(const int8_t *qx, const uint16_t *sx, int64_t M, int64_
     a.M = (int)M;
     a.N = (int)N;
     a.K = (int)K;
-    return launch_qgemm_w8a8(a, stream) == hipSuccess ? QL_OK : QL_ERR_HIP;
+    return launch_qgemm_w8a8(a, device_cus(), stream) == hipSuccess ? QL_OK : QL_ERR_HIP;
 }
 
 int qlinear_steer(float *h, int64_t M, int64_t N, const float *dir, float hnorm,

@@ -110,6 +110,36 @@ def test_forward_w8a8_ragged(gpu, orc, M, N, K):
     assert np.array_equal(Yg, forward_gpu(gpu, q, s, codes, scales, N))
 
 
+@pytest.mark.parametrize("M,N,K", [
+    (1, 1, 64), (63, 65, 192), (65, 129, 1152), (200, 130, 512),      # 64 x 64 tiles
+    (1000, 1030, 128), (1290, 1540, 320),                              # 64 x 128 tiles
+    (1153, 2049, 64), (2050, 4097, 192)])                              # 128 x 128 tiles
+def test_forward_w8a8_pipelined(gpu, orc, M, N, K):
+    """The pipelined kernel's tile shapes at their edges: fewer steps than a
+    stage, a part-filled last stage, one row or column past a tile, outputs
+    that cannot be stored four at a time.  Same inputs with scales at an odd
+    2-byte address take the general kernel: both within the bound (one fp32
+    rounding per block and one more per K group, of which there are at most
+    8, plus the row scale)."""
+    torch, ql = gpu
+    W, X = si.small_case(7150 + M + N + K, M, N, K)
+    codes, scales = orc.quantize(O.FMT_INT8, W)
+    q, s = orc.quantize_act(X, O.DT_BF16)
+    rows = np.unique(np.r_[0:min(M, 3), M // 2, max(0, M - 3):M])
+    Yr = orc.forward_w8a8(q[rows], s[rows], codes, scales, N)
+    B = bound(orc, q[rows], s[rows], codes, scales, N) * (K // 32 + 9) / (K // 32 + 1)
+    Yg = forward_gpu(gpu, q, s, codes, scales, N)
+    assert np.isfinite(Yg).all()
+    assert np.all(np.abs(Yg[rows] - Yr) <= B)
+    shifted = torch.empty(scales.size + 1, dtype=torch.int16, device="cuda")
+    odd = shifted[1:].view(scales.shape)
+    odd.copy_(dev(torch, scales, np.uint16))
+    Yo = ql.forward_w8a8(dev(torch, q, np.int8), dev(torch, s, np.uint16),
+                         dev(torch, codes, np.uint8), odd, N)
+    torch.cuda.synchronize()
+    assert np.all(np.abs(Yo.cpu().numpy().astype(np.float64)[rows] - Yr) <= B)
+
+
 def test_forward_w8a8_integer_exact(gpu, orc):
     """Integer activations with row absmax 127 and W = c * 2^-12: the
     product is an exact integer matmul times 2^-12."""
