@@ -24,10 +24,12 @@
  * Y [M][N], all row-major.
  *
  * Accuracy of the forward product against the exact sum above: fp32
- * activations, and bf16 activations at M <= 256 (or when K % 256 != 0 or
+ * activations, and bf16 activations at M <= 64 (or when K % 256 != 0 or
  * an operand is not 16-byte aligned), are contracted with the exact codes
- * and fp32 block partials (error a few fp32 roundings).  bf16 activations
- * at larger M take the fp16 path: X is copied
+ * and fp32 block partials (error a few fp32 roundings); so are bf16
+ * activations at larger M wherever an exact kernel is the faster one (most
+ * layers and blocks up to a few hundred rows).  The others take the fp16
+ * path: X is copied
  * exactly to fp16 with a power-of-two shift per row, each weight enters the
  * matrix cores as fp16(c * fp16(s * 2^f)) with one shift f per weight row
  * and K part (the library may cut a long reduction into parts; Q * max_b s

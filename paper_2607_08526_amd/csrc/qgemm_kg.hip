@@ -1,0 +1,380 @@
+// Quantized linear forward for few to a few hundred activation rows (bf16
+// X, int8 or q4 weights), in its exact per-block form, one launch and no
+// partial sums in memory:
+//
+//   Y[m][n] = sum_b s[n][b] * sum_{k in b} X[m][k] * c[n][k]
+//
+// Why.  At these sizes a layer is a few MB of codes and at most a few GFLOP,
+// so what decides is how many of the 256 CUs have work, how much of it is in
+// flight, and how many launches there are.  Cutting K into parts over
+// workgroups fills the GPU but stores fp32 partials and needs a second
+// launch to add them (4 to 6 us each).  Here the 16 wavefronts of a
+// workgroup cut K among themselves: KG groups of WN wavefronts own the same
+// TM x TN output tile, each its share of every stage's k, and their sums are
+// added through LDS in group order at the end.
+//
+// Shapes (per layer, chosen by kg_plan): TM = 32 MI rows (MI = 1 up to 32
+// rows, 2 above), and WN x KG = 4 x 4, 2 x 8 or 1 x 16, i.e. TN = 128, 64 or
+// 32 columns; each wavefront owns 32 MI x 32 outputs.  Sixteen wavefronts
+// because one wavefront issues a VALU instruction every ~5 cycles at best
+// while a SIMD takes one every 2 to 4 from several.
+//
+// Memory.  Activations, codes and scales of a stage (256 or 512 k) go to LDS
+// by direct-to-LDS loads of 16 bytes per lane, at least 128 contiguous bytes
+// per row, through a ring of NST stages; the loads of a stage go out spread
+// over the step before.  Up to 32 rows only the first XR = 8, 16 or 32 are
+// staged: the MFMA's other rows repeat them and are never stored.
+//
+// Contraction.  Per 32-k block and 32 x 32 tile two
+// v_mfma_f32_32x32x16_bf16 over k = 32 b + 16 g + 8 h + e (lane group g =
+// lane / 32, chunk h, element e), then acc += s * partial in fp32.  The codes
+// are converted as signed bytes (q4: nibbles in the high half of a byte, the
+// factor 16 taken out of the scale): exact in bf16 and without the offset
+// term, and its MFMAs, of the unsigned forms.
+//
+// Requirements (checked by the host): K % 256 == 0, K < 2^23, 16-byte
+// aligned X, codes and scales.
+#include <algorithm>
+#include <type_traits>
+
+#include "dma.h"
+#include "epilogue.h"
+#include "internal.h"
+
+namespace qlk {
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+constexpr int WAVES = 16, NT = 64 * WAVES;
+
+template <int FMT_, int MI_, int XR_, int WN_, int BPW_, int NST_>
+struct KgGeo {
+    static constexpr int FMT = FMT_, MI = MI_, XR = XR_, WN = WN_, BPW = BPW_, NST = NST_;
+    static constexpr int KG = WAVES / WN;
+    static constexpr int TM = 32 * MI, TN = 32 * WN;
+    static constexpr int EB = KG * BPW;                // 32-k blocks per stage
+    static constexpr int XRB = EB * 64, XCH = XRB / 16;  // activation bytes, chunks per row
+    static constexpr int CRB = FMT == QL_FMT_INT8 ? EB * 32 : EB * 16, CCH = CRB / 16;
+    static constexpr int SCH = EB / 8;                 // 16-byte scale chunks per column
+    static constexpr int XBYTES = XR * XRB, CBYTES = TN * CRB, SBYTES = TN * SCH * 16;
+    static constexpr int STAGE = XBYTES + CBYTES + SBYTES;
+    // loads in units of one wavefront (1 KB); wavefront w takes units w, w +
+    // 16, ..., the last ones repeated so that every wavefront counts the same
+    static constexpr int XU = XBYTES / 1024, CU = CBYTES / 1024, SU = (SBYTES + 1023) / 1024;
+    static constexpr int UNITS = XU + CU + SU, LOADS = (UNITS + WAVES - 1) / WAVES;
+    static constexpr int RROWS = XR < TM ? XR : TM;    // rows summed at the end
+    static constexpr int RED = KG * RROWS * TN * 4;
+    static constexpr int RING = NST * (XBYTES + CBYTES + SU * 1024);
+    static constexpr int SLOT = XBYTES + CBYTES + SU * 1024;
+    static constexpr int LDS = RING > RED ? RING : RED;
+    static_assert(EB % 8 == 0 && XBYTES % 1024 == 0 && CBYTES % 1024 == 0, "whole loads");
+    static_assert(LDS <= 160 * 1024, "LDS of a CU");
+};
+
+// chunk swizzles (physical = logical ^ swizzle): the fragment reads of 16
+// consecutive lanes (rows, one logical chunk) fall on distinct banks
+__device__ inline int xswz(int row) { return row & 15; }
+template <int CCH>
+__device__ inline int cswz(int row)
+{
+    return CCH >= 16 ? row & 15 : (row >> 1) & 7;  // 128-byte rows: two per bank row
+}
+
+__device__ inline f32x16 mfma(u32x4 a, u32x4 b, f32x16 c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// workgroup p of a layer of G: each XCD (p % 8) takes a contiguous range
+__device__ inline int logical_tile(int p, int G)
+{
+    const int q = G >> 3, r = G & 7;
+    const int xcd = p & 7, idx = p >> 3;
+    return xcd < r ? xcd * (q + 1) + idx : r * (q + 1) + (xcd - r) * q + idx;
+}
+
+__device__ inline float f16_value(uint32_t bits)
+{
+    return (float)__builtin_bit_cast(_Float16, (uint16_t)bits);
+}
+
+// bf16 pair of two fp32 values that bf16 holds exactly
+__device__ inline uint32_t bf16_pair(float lo, float hi)
+{
+    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+}
+__device__ inline float sbyte(uint32_t w, int i) { return (float)((int)(w << (24 - 8 * i)) >> 24); }
+
+// 8 codes (16-k chunk half of a lane) as bf16 pairs in k order
+__device__ inline u32x4 cvt_int8(uint32_t w0, uint32_t w1)
+{
+    return u32x4{bf16_pair(sbyte(w0, 0), sbyte(w0, 1)), bf16_pair(sbyte(w0, 2), sbyte(w0, 3)),
+                 bf16_pair(sbyte(w1, 0), sbyte(w1, 1)), bf16_pair(sbyte(w1, 2), sbyte(w1, 3))};
+}
+// q4: 16 times the codes (nibbles moved to the high half of their bytes,
+// read as signed bytes); the scale is divided by 16
+__device__ inline u32x4 cvt_q4(uint32_t w)
+{
+    const uint32_t e = (w << 4) & 0xF0F0F0F0u, o = w & 0xF0F0F0F0u;  // even, odd k
+    return u32x4{bf16_pair(sbyte(e, 0), sbyte(o, 0)), bf16_pair(sbyte(e, 1), sbyte(o, 1)),
+                 bf16_pair(sbyte(e, 2), sbyte(o, 2)), bf16_pair(sbyte(e, 3), sbyte(o, 3))};
+}
+
+// One output tile of layer d.
+template <class G>
+__device__ inline void kg_tile(const LinDesc &d, int tile, uint8_t *ring)
+{
+    constexpr int FMT = G::FMT, MI = G::MI;
+    constexpr bool Q4 = FMT == QL_FMT_Q4;
+    const int tm = tile % d.tiles_m, tn = tile / d.tiles_m;
+    const int M = d.M, N = d.N, K = d.K, nb = K >> 5;
+    const int m0 = tm * G::TM, n0 = tn * G::TN;
+    const int crow = Q4 ? K / 2 : K;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kg = wave / G::WN, wn = (wave % G::WN) * 32;
+
+    // this wavefront's loads: per unit a base, a per-lane offset within the
+    // stage's first columns, and the bytes a stage advances.  Rows past M and
+    // N repeat the last one; chunks past K the last chunk (K % 512 == 256 and
+    // a 512-k stage; their scales are taken as 0).
+    const uint8_t *ub[G::LOADS];
+    uint32_t urow[G::LOADS];
+    int ucol[G::LOADS], ustep[G::LOADS], ulim[G::LOADS];
+    uint32_t udst[G::LOADS];
+#pragma unroll
+    for (int q = 0; q < G::LOADS; ++q) {
+        const int u = min(q * WAVES + wave, G::UNITS - 1);  // wave-uniform
+        if (u < G::XU) {
+            const int slot = u * 64 + lane, row = slot / G::XCH;
+            ub[q] = reinterpret_cast<const uint8_t *>(d.X) + (int64_t)m0 * K * 2;
+            urow[q] = (uint32_t)((min(m0 + row, M - 1) - m0) * K * 2);
+            ucol[q] = ((slot % G::XCH) ^ xswz(row)) * 16;
+            ustep[q] = G::XRB;
+            ulim[q] = K * 2 - 16;
+            udst[q] = u * 1024;
+        } else if (u < G::XU + G::CU) {
+            const int slot = (u - G::XU) * 64 + lane, row = slot / G::CCH;
+            ub[q] = d.codes + (int64_t)n0 * crow;
+            urow[q] = (uint32_t)((min(n0 + row, N - 1) - n0) * crow);
+            ucol[q] = ((slot % G::CCH) ^ cswz<G::CCH>(row)) * 16;
+            ustep[q] = G::CRB;
+            ulim[q] = crow - 16;
+            udst[q] = u * 1024;
+        } else {
+            // scales: chunk-major, [SCH][TN] of 16 bytes
+            const int slot = ((u - G::XU - G::CU) * 64 + lane) % (G::TN * G::SCH);
+            const int row = slot % G::TN;
+            ub[q] = reinterpret_cast<const uint8_t *>(d.scales) + (int64_t)n0 * nb * 2;
+            urow[q] = (uint32_t)((min(n0 + row, N - 1) - n0) * nb * 2);
+            ucol[q] = (slot / G::TN) * 16;
+            ustep[q] = G::SCH * 16;
+            ulim[q] = nb * 2 - 16;
+            udst[q] = u * 1024;
+        }
+    }
+    const int iters = (nb + G::EB - 1) / G::EB;
+    auto issue = [&](int it, int q) {
+        dma_load16(ub[q], urow[q] + (uint32_t)min(it * ustep[q] + ucol[q], ulim[q]),
+                   dma_lds(ring + (it % G::NST) * G::SLOT) + udst[q]);
+    };
+#pragma unroll
+    for (int it = 0; it < G::NST - 1; ++it)
+        if (it < iters)
+#pragma unroll
+            for (int q = 0; q < G::LOADS; ++q)
+                issue(it, q);
+
+    // accumulator registers that hold staged rows: 8 (r / 4) + 4 g + r % 4
+    constexpr int AR = G::XR < 32 ? G::XR / 2 : 16;
+    float acc[MI][AR];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int r = 0; r < AR; ++r)
+            acc[i][r] = 0.0f;
+
+    auto step = [&](int it, auto refill) {
+        constexpr bool REFILL = decltype(refill)::value;
+        // every LDS read of the previous stage has completed; this one landed
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if constexpr (REFILL)
+            __builtin_amdgcn_s_waitcnt(dma_vmcnt((G::NST - 2) * G::LOADS));
+        else
+            dma_wait<G::LOADS, G::NST - 2>(iters - 1 - it);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");  // no LDS read moves above the barrier
+        const uint8_t *const st = ring + (it % G::NST) * G::SLOT;
+#pragma unroll
+        for (int u = 0; u < G::BPW; ++u) {
+            const int b = kg * G::BPW + u;  // block of the stage
+            uint32_t sw = *reinterpret_cast<const uint16_t *>(
+                st + G::XBYTES + G::CBYTES + ((b / 8) * G::TN + wn + l32) * 16 + (b % 8) * 2);
+            sw = it * G::EB + b < nb ? sw : 0u;
+            float s = f16_value(sw) * (Q4 ? 0.0625f : 1.0f);  // exact
+            dma_pin(s);
+            // the lane's codes of the block: 16 (int8) or 8 (q4) bytes
+            const int wr = wn + l32;
+            u32x4 wv[2];
+            if constexpr (Q4) {
+                const u32x2 c = *reinterpret_cast<const u32x2 *>(
+                    st + G::XBYTES + wr * G::CRB + (b ^ cswz<G::CCH>(wr)) * 16 + 8 * g);
+                wv[0] = cvt_q4(c[0]);
+                wv[1] = cvt_q4(c[1]);
+            } else {
+                const u32x4 c = *reinterpret_cast<const u32x4 *>(
+                    st + G::XBYTES + wr * G::CRB + ((2 * b + g) ^ cswz<G::CCH>(wr)) * 16);
+                wv[0] = cvt_int8(c[0], c[1]);
+                wv[1] = cvt_int8(c[2], c[3]);
+            }
+            if constexpr (REFILL)
+#pragma unroll
+                for (int q = u; q < G::LOADS; q += G::BPW)
+                    issue(it + G::NST - 1, q);
+            f32x16 p[MI];
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                const int xr = 32 * i + (l32 & (G::XR < 32 ? G::XR - 1 : 31));
+                u32x4 a[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    a[h] = *reinterpret_cast<const u32x4 *>(
+                        st + xr * G::XRB + ((4 * b + 2 * g + h) ^ xswz(xr)) * 16);
+                p[i] = mfma(a[0], wv[0], f32x16{});
+                p[i] = mfma(a[1], wv[1], p[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int r = 0; r < AR; ++r)
+                    acc[i][r] = __builtin_fmaf(s, p[i][r], acc[i][r]);
+        }
+    };
+    int it = 0;
+#pragma unroll 1
+    for (; it + G::NST - 1 < iters; ++it)
+        step(it, std::true_type{});
+#pragma unroll 1
+    for (; it < iters; ++it)
+        step(it, std::false_type{});
+
+    // The groups' sums as rows in LDS (every stage issued has been waited
+    // for and, behind the barrier, read), then every thread adds and stores
+    // groups of four columns.
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    float *const red = reinterpret_cast<float *>(ring);
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int r = 0; r < AR; ++r)
+            red[(kg * G::RROWS + 32 * i + 8 * (r >> 2) + 4 * g + (r & 3)) * G::TN + wn + l32] =
+                acc[i][r];
+    __syncthreads();
+    const bool vec = epi_vec_ok(d.ep, d.Y, N);
+#pragma unroll 1
+    for (int q = tid; q < G::RROWS * G::TN / 4; q += NT) {
+        const int m = m0 + q / (G::TN / 4), n = n0 + 4 * (q % (G::TN / 4));
+        if (m >= M || n >= N)
+            continue;
+        const f32x4 *const src = reinterpret_cast<const f32x4 *>(red) + q;
+        f32x4 v = src[0];
+#pragma unroll
+        for (int k = 1; k < G::KG; ++k)
+            v += src[k * (G::RROWS * G::TN / 4)];
+        const int64_t idx = (int64_t)m * N + n;
+        if (vec) {
+            epi_store4(d.ep, d.Y, idx, n, v, false);
+        } else {
+#pragma unroll 1
+            for (int e = 0; e < 4 && n + e < N; ++e)
+                epi_store(d.ep, d.Y, idx + e, n + e, v[e]);
+        }
+    }
+}
+
+// The shapes a launch may mix, XR = 8, 16 or 32 for launches of at most that
+// many rows and 64 above.
+template <int FMT, int XR>
+struct KgShapes {
+    static constexpr bool I8 = FMT == QL_FMT_INT8;
+    static constexpr int XR1 = XR < 32 ? XR : 32;
+    // up to 8 rows a stage is small: twice the k per stage, half the barriers
+    static constexpr bool FEW = XR <= 8;
+    using R1W4 = KgGeo<FMT, 1, XR1, 4, FEW ? 4 : 2, FEW && I8 ? 2 : 3>;
+    using R1W2 = KgGeo<FMT, 1, XR1, 2, FEW ? 2 : 1, 3>;
+    using R1W1 = KgGeo<FMT, 1, XR1, 1, FEW ? 2 : 1, 3>;
+    using R2W4 = KgGeo<FMT, 2, 64, 4, 2, I8 ? 2 : 3>;
+    using R2W2 = KgGeo<FMT, 2, 64, 2, 1, 3>;
+    static constexpr int LDS1 = std::max(R1W4::LDS, std::max(R1W2::LDS, R1W1::LDS));
+    static constexpr int LDS =
+        XR > 32 ? std::max(LDS1, std::max(R2W4::LDS, R2W2::LDS)) : LDS1;
+};
+
+template <int FMT, int XR>
+__global__ __launch_bounds__(NT, 4) void qgemm_kg_kernel(const GroupArgs args)
+{
+    using S = KgShapes<FMT, XR>;
+    __shared__ __align__(16) uint8_t ring[S::LDS];
+    const int p = (int)blockIdx.x;
+    LinDesc d = args.d[0];
+    int end = args.total_tiles;
+#pragma unroll
+    for (int t = 1; t < QL_MAX_GROUP; ++t) {
+        if (t < args.n && p >= args.d[t].tile_begin)
+            d = args.d[t];
+        if (t < args.n && p < args.d[t].tile_begin && end == args.total_tiles)
+            end = args.d[t].tile_begin;
+    }
+    const int tile = logical_tile(p - d.tile_begin, end - d.tile_begin);
+    switch (d.psteps) {  // shape (kg_plan)
+    case KG_R1W1:
+        kg_tile<typename S::R1W1>(d, tile, ring);
+        break;
+    case KG_R1W2:
+        kg_tile<typename S::R1W2>(d, tile, ring);
+        break;
+    case KG_R1W4:
+        kg_tile<typename S::R1W4>(d, tile, ring);
+        break;
+    default:
+        if constexpr (XR > 32) {
+            if (d.psteps == KG_R2W2)
+                kg_tile<typename S::R2W2>(d, tile, ring);
+            else
+                kg_tile<typename S::R2W4>(d, tile, ring);
+        }
+    }
+}
+
+template <int FMT>
+hipError_t launch_fmt(int maxM, const GroupArgs &a, hipStream_t s)
+{
+    const dim3 grid((unsigned)a.total_tiles), block(NT);
+    if (maxM > 32)
+        hipLaunchKernelGGL((qgemm_kg_kernel<FMT, 64>), grid, block, 0, s, a);
+    else if (maxM > 16)
+        hipLaunchKernelGGL((qgemm_kg_kernel<FMT, 32>), grid, block, 0, s, a);
+    else if (maxM > 8)
+        hipLaunchKernelGGL((qgemm_kg_kernel<FMT, 16>), grid, block, 0, s, a);
+    else
+        hipLaunchKernelGGL((qgemm_kg_kernel<FMT, 8>), grid, block, 0, s, a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_qgemm_kg(int fmt, int maxM, const GroupArgs &args, hipStream_t stream)
+{
+    return fmt == QL_FMT_INT8 ? launch_fmt<QL_FMT_INT8>(maxM, args, stream)
+                              : launch_fmt<QL_FMT_Q4>(maxM, args, stream);
+}
+
+}  // namespace qlk

@@ -473,7 +473,7 @@ StreamPlan stream_plan(int fmt, const LinDesc *ds, int n, int cus, int *S, int *
     // 15-25% slower on the d = 2048 block
     const int mx = M <= 8 ? 8 : M <= 16 ? 16 : 32;
     const double cb = fmt == QL_FMT_INT8 ? 1.0 : 0.5;
-    StreamPlan best{mx, 16, 4, 1, nbmax};
+    StreamPlan best{mx, 16, 4, 1, nbmax, 1e30};
     double best_t = 1e30;
     int bS[QL_MAX_GROUP], bP[QL_MAX_GROUP];
     for (int i = 0; i < n; ++i) {
@@ -526,7 +526,7 @@ StreamPlan stream_plan(int fmt, const LinDesc *ds, int n, int cus, int *S, int *
                     t += RT + SUM_LAUNCH + sum_bytes / SUM_RATE + PART_COST * Smax;
                 if (t < best_t * 0.97) {
                     best_t = t;
-                    best = StreamPlan{mx, rw, kw, Smax, L};
+                    best = StreamPlan{mx, rw, kw, Smax, L, t};
                     std::copy(Si, Si + n, bS);
                     std::copy(Pi, Pi + n, bP);
                 }

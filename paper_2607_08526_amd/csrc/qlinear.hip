@@ -251,6 +251,7 @@ int device_cus()
 struct SplitPlan {
     int S[QL_MAX_GROUP], psteps[QL_MAX_GROUP];
     bool ext;
+    double t;  // estimated time of the launch, in 64-k steps
 };
 
 constexpr int XCDS = 8;
@@ -331,7 +332,7 @@ SplitPlan plan_splits(int fmt, const LinDesc *d, int n)
         if (best_parts == 0 || t < best_t * 0.98 ||
             (t <= best_t * 1.02 && total_parts < best_parts)) {
             best = pl;
-            best_t = t;
+            best.t = best_t = t;
             best_parts = total_parts;
         }
     }
@@ -350,6 +351,7 @@ SplitPlan plan_splits(int fmt, const LinDesc *d, int n)
                                       (best.S[i] > 1 ? PART_STORE + TAIL_PER_PART * best.S[i] +
                                                            (epi_active(d[i].ep) ? EPI_TAIL : 0.0)
                                                      : 0.0));
+    best.t = best_t;
     std::vector<int> lens;
     for (int i = 0; i < n; ++i)
         for (int L = d[i].K / 64; L >= 4; L /= 2)
@@ -383,7 +385,7 @@ SplitPlan plan_splits(int fmt, const LinDesc *d, int n)
         const double t = longest + TILE_OVH + PART_STORE + EXT_GAP + sum_bytes / EXT_BYTES_PER_STEP;
         if (t < best_t * 0.95) {
             best = pl;
-            best_t = t;
+            best.t = best_t = t;
         }
     }
     return best;
@@ -395,7 +397,7 @@ SplitPlan cached_plan(int fmt, const LinDesc *d, int n)
 {
     struct Entry {
         int n, cus, slots;
-        int64_t shape[QL_MAX_GROUP][3];
+        int64_t shape[QL_MAX_GROUP][4];
         SplitPlan pl;
     };
     constexpr int SLOTS = 16;
@@ -410,12 +412,13 @@ SplitPlan cached_plan(int fmt, const LinDesc *d, int n)
         key.shape[i][0] = d[i].M;
         key.shape[i][1] = d[i].N;
         key.shape[i][2] = d[i].K;
+        key.shape[i][3] = epi_active(d[i].ep);  // it lengthens in-kernel reductions
     }
     {
         std::lock_guard<std::mutex> g(mu);
         for (int e = 0; e < used; ++e)
             if (cache[e].n == n && cache[e].cus == key.cus && cache[e].slots == key.slots &&
-                std::equal(&cache[e].shape[0][0], &cache[e].shape[0][0] + 3 * n, &key.shape[0][0]))
+                std::equal(&cache[e].shape[0][0], &cache[e].shape[0][0] + 4 * n, &key.shape[0][0]))
                 return cache[e].pl;
     }
     key.pl = plan_splits(fmt, d, n);
@@ -794,6 +797,193 @@ int launch_mid(const ql_linear_ep *const *ls, int n, WsSource &wsrc, hipStream_t
     return e == hipSuccess ? QL_OK : QL_ERR_HIP;
 }
 
+// The K-group kernel (qgemm_kg.hip): a shape (KgShape) per layer and the
+// estimated time of the launch in us.  A workgroup of a shape takes KG_BASE
+// plus its 256-k stages at the measured rate; one workgroup is resident per
+// CU.  For every bound on the longest workgroup, each layer takes the shape
+// of least total work within it; the launch then lasts the longest
+// workgroup, or, with more workgroups than CUs, the work per CU plus half
+// the longest one (the tail).  Within 10% of the measured time on most of
+// 160 single layers and blocks (d = 512 to 2048, 5 to 640 rows).
+struct KgPlan {
+    int shape[QL_MAX_GROUP];
+    double us;
+};
+
+// Below 4 rows the GEMV is ahead (a d = 2048 block at 4 rows: int8 22.5 us,
+// q4 streamed 17.1, against about 16 and 14 here); beyond the upper bound the
+// large-M kernel has a tile per CU for any layer of some width
+constexpr int64_t KG_MIN_M = 4, KG_MAX_M = 2048;
+
+// us per 256 k of a workgroup, measured on full launches (q4, int8), and the
+// share of it at 16 rows and below (fewer activation bytes)
+constexpr double KG_RATE[5][2] = {
+    {0.35, 0.43}, {0.55, 0.70}, {1.00, 1.00}, {0.85, 0.85}, {1.43, 1.40}};
+constexpr double KG_FEW = 0.75;
+constexpr double KG_BASE = 3.0, KG_LAUNCH = 1.2;
+
+KgPlan kg_plan(int fmt, const ql_linear_ep *const *ls, int n)
+{
+    const int f = fmt == QL_FMT_INT8 ? 1 : 0, cus = device_cus();
+    int64_t maxM = 0;
+    for (int i = 0; i < n; ++i)
+        maxM = std::max(maxM, ls[i]->lin.M);
+    const int shapes = maxM > 32 ? 5 : 3;
+    const double few = maxM <= 16 ? KG_FEW : 1.0;
+    double t[QL_MAX_GROUP][5], w[QL_MAX_GROUP][5];  // us of a workgroup, workgroups
+    for (int i = 0; i < n; ++i)
+        for (int s = 0; s < shapes; ++s) {
+            const ql_linear &l = ls[i]->lin;
+            t[i][s] = KG_BASE + (double)(l.K / 256) * KG_RATE[s][f] * few;
+            w[i][s] = (double)(((l.M + kg_tile_m(s) - 1) / kg_tile_m(s)) *
+                               ((l.N + kg_tile_n(s) - 1) / kg_tile_n(s)));
+        }
+    KgPlan best{};
+    best.us = 1e30;
+    for (int i = 0; i < n; ++i)
+        for (int s = 0; s < shapes; ++s) {
+            KgPlan p{};
+            double longest = 0.0, work = 0.0, wgs = 0.0;
+            bool ok = true;
+            for (int j = 0; j < n && ok; ++j) {
+                int c = -1;
+                for (int q = 0; q < shapes; ++q)
+                    if (t[j][q] <= t[i][s] && (c < 0 || w[j][q] * t[j][q] < w[j][c] * t[j][c]))
+                        c = q;
+                ok = c >= 0;
+                if (!ok)
+                    break;
+                p.shape[j] = c;
+                longest = std::max(longest, t[j][c]);
+                work += w[j][c] * t[j][c];
+                wgs += w[j][c];
+            }
+            if (!ok)
+                continue;
+            p.us = KG_LAUNCH +
+                   (wgs <= cus ? longest : std::max(longest, work / cus + 0.5 * longest));
+            if (p.us < best.us)
+                best = p;
+        }
+    return best;
+}
+
+// Whether a group (one quantized format, bf16 X, mid_fits each, ordered as
+// launched) goes to the K-group kernel, and its shapes.  Measured on q4 and
+// int8 single layers and blocks at 5 to 1000 rows, each against the kernel
+// that ran before:
+//   up to 32 rows: where its estimate is under 0.8 of the streaming kernel's
+//     (blocks 1.1-1.7 times faster; single layers, which cannot fill the GPU
+//     with whole reductions, mostly stay: 2048 x 8192 at 8 rows 9.0 us
+//     streamed against 11.6);
+//   33 to 64 rows: always (1.3-2.4 times faster than the mid-M kernel);
+//   above: where its estimate is under 8 us + 0.8 of the large-M plan's steps
+//     (up to 3 times faster: 768 x 768 at 500 rows 19.4 -> 5.9 us; no case
+//     of 260 where the rule picks the slower one).
+struct KgChoice {
+    bool use;
+    KgPlan plan;
+};
+
+KgChoice kg_choose(int fmt, const ql_linear_ep *const *ord, int n)
+{
+    int64_t maxM = 0;
+    for (int i = 0; i < n; ++i)
+        maxM = std::max(maxM, ord[i]->lin.M);
+    KgChoice c{};
+    c.plan = kg_plan(fmt, ord, n);
+    LinDesc ds[QL_MAX_GROUP] = {};
+    for (int i = 0; i < n; ++i) {
+        const ql_linear &l = ord[i]->lin;
+        ds[i].M = (int)l.M;
+        ds[i].N = (int)l.N;
+        ds[i].K = (int)l.K;
+        ds[i].ep = to_epilogue(ord[i]->ep);
+        ds[i].tiles_m = (int)((l.M + wide_tile_bm() - 1) / wide_tile_bm());
+        ds[i].tiles_n = (int)((l.N + wide_tile_bn() - 1) / wide_tile_bn());
+    }
+    if (maxM <= stream_max_m()) {
+        int S[QL_MAX_GROUP], P[QL_MAX_GROUP];
+        c.use = c.plan.us < 0.8 * stream_plan(fmt, ds, n, device_cus(), S, P).us;
+    } else {
+        c.use = maxM <= skinny_max_m() || c.plan.us < 8.0 + 0.8 * plan_splits(fmt, ds, n).t;
+    }
+    return c;
+}
+
+// Recently made choices, keyed by the group's shapes: the plans behind one
+// cost tens of microseconds of host time.
+KgChoice cached_kg_choice(int fmt, const ql_linear_ep *const *ord, int n)
+{
+    struct Entry {
+        int fmt, n, cus;
+        int64_t shape[QL_MAX_GROUP][4];
+        KgChoice c;
+    };
+    constexpr int SLOTS = 32;
+    static std::mutex mu;
+    static Entry cache[SLOTS];
+    static int used = 0, next = 0;
+    Entry key{};
+    key.fmt = fmt;
+    key.n = n;
+    key.cus = device_cus();
+    for (int i = 0; i < n; ++i) {
+        const ql_linear &l = ord[i]->lin;
+        key.shape[i][0] = l.M;
+        key.shape[i][1] = l.N;
+        key.shape[i][2] = l.K;
+        key.shape[i][3] = epi_active(to_epilogue(ord[i]->ep));
+    }
+    {
+        std::lock_guard<std::mutex> g(mu);
+        for (int e = 0; e < used; ++e)
+            if (cache[e].fmt == fmt && cache[e].n == n && cache[e].cus == key.cus &&
+                std::equal(&cache[e].shape[0][0], &cache[e].shape[0][0] + 4 * n, &key.shape[0][0]))
+                return cache[e].c;
+    }
+    key.c = kg_choose(fmt, ord, n);
+    std::lock_guard<std::mutex> g(mu);
+    cache[next] = key;
+    next = (next + 1) % SLOTS;
+    used = std::min(used + 1, SLOTS);
+    return key.c;
+}
+
+int launch_kg(const ql_linear_ep *const *ord, int n, const KgPlan &plan, WsSource &wsrc,
+              hipStream_t stream)
+{
+    GroupArgs a{};
+    a.n = n;
+    int64_t maxM = 0, total = 0;
+    for (int i = 0; i < n; ++i) {
+        LinDesc &d = a.d[i];
+        const ql_linear &l = ord[i]->lin;
+        maxM = std::max(maxM, l.M);
+        d.X = l.X;
+        d.codes = (const uint8_t *)l.codes;
+        d.scales = l.scales;
+        d.Y = l.Y;
+        d.ep = to_epilogue(ord[i]->ep);
+        d.M = (int)l.M;
+        d.N = (int)l.N;
+        d.K = (int)l.K;
+        d.ksplit = 1;
+        d.psteps = plan.shape[i];
+        d.tiles_m = (int)((l.M + kg_tile_m(d.psteps) - 1) / kg_tile_m(d.psteps));
+        d.tiles_n = (int)((l.N + kg_tile_n(d.psteps) - 1) / kg_tile_n(d.psteps));
+        d.tile_begin = (int)total;
+        total += (int64_t)d.tiles_m * d.tiles_n;
+    }
+    if (total >= I31)
+        return QL_ERR_UNSUPPORTED;
+    a.total_tiles = (int)total;
+    if (wsrc.dry_run)
+        return QL_OK;
+    return launch_qgemm_kg(ord[0]->lin.fmt, (int)maxM, a, stream) == hipSuccess ? QL_OK
+                                                                                : QL_ERR_HIP;
+}
+
 // One grouped launch over layers that share fmt and xdt (M > 0 each).
 int launch_group(const ql_linear_ep *const *ls, int n, WsSource &wsrc, hipStream_t stream)
 {
@@ -806,12 +996,22 @@ int launch_group(const ql_linear_ep *const *ls, int n, WsSource &wsrc, hipStream
     const bool f16 = ls[0]->lin.fmt == QL_FMT_F16;
     // fp16 weights have one kernel; a forced path applies to quantized ones
     const int forced = f16 ? QL_PATH_AUTO : g_forced_path.load(std::memory_order_relaxed);
-    // beyond the streaming kernel's rows the mid-M kernel takes every group
-    // it fits: at 33-64 rows it is 2.5-3x faster than the per-layer exact
-    // kernels (a d = 2048 block 37-43 us against 92-121)
+    // quantized weights, bf16 X, whole 256-k steps, 16-byte aligned operands
     bool all_mid = true;
     for (int i = 0; i < n; ++i)
         all_mid = all_mid && mid_fits(ls[i]->lin);
+    if (forced == QL_PATH_AUTO && !xf32 && !f16 && all_mid && maxM >= KG_MIN_M &&
+        maxM <= KG_MAX_M) {
+        // longest reduction first, so the long tiles start early
+        const ql_linear_ep *ord[QL_MAX_GROUP];
+        std::copy(ls, ls + n, ord);
+        std::stable_sort(ord, ord + n, [](const ql_linear_ep *x, const ql_linear_ep *y) {
+            return x->lin.K > y->lin.K;
+        });
+        const KgChoice c = cached_kg_choice(ls[0]->lin.fmt, ord, n);
+        if (c.use)
+            return launch_kg(ord, n, c.plan, wsrc, stream);
+    }
     const bool per_layer = forced == QL_PATH_AUTO
                           ? !xf32 && !f16 &&
                                 (maxM <= stream_max_m() || (maxM <= skinny_max_m() && !all_mid))
@@ -821,8 +1021,8 @@ int launch_group(const ql_linear_ep *const *ls, int n, WsSource &wsrc, hipStream
         return QL_ERR_UNSUPPORTED;  // the few-row kernels take bf16 activations
     if (per_layer)
         return launch_rows(ls, n, forced, wsrc, stream);
-    // a few hundred rows: the exact single-launch kernel where every layer
-    // fits it and the group's work is short (its 64-k steps of 128 x 128
+    // a few hundred rows that the K-group kernel leaves: the mid-M kernel
+    // where every layer fits it and the group's work is short (its 64-k steps of 128 x 128
     // tiles, per CU, at most MID_MAX_STEPS_PER_CU; beyond that the large-M
     // path's wider tiles outweigh its pre-pass)
     if (forced == QL_PATH_MID || (forced == QL_PATH_AUTO && !xf32 && !f16 && maxM <= MID_MAX_M)) {

@@ -1,0 +1,87 @@
+"""The K-group kernel (few to a few hundred bf16 rows) at the edges of its
+shapes, against the fp64 oracle, and against the tiled exact kernel on the
+same inputs.
+
+Both add each block's partial (at most 32 products of exact operands) in
+fp32, scaled by s, K / 32 times, and the K-group kernel adds up to 16 groups'
+sums: element by element |Y - Y_ref| <= (K / 32 + 32 + 16) * 2^-24 *
+(|X| |W_d|^T).
+"""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+from oracle import oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU (run with -m 'not gpu' on a CPU host)")
+    from paper_2607_08526_amd import qlinear as ql
+    ql.load()
+    return torch, ql
+
+
+def run(gpu, fmt, X, codes, scales, N, **ep):
+    torch, ql = gpu
+    dv = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    Y = ql.forward_ep(fmt, dv(X.view(np.int16)), dv(codes), dv(scales.view(np.int16)), N, **ep)
+    torch.cuda.synchronize()
+    return Y.float().cpu().numpy().astype(np.float64)
+
+
+# rows around every staging size and row tile, columns around 32, 64 and 128
+# and not a multiple of 4, one stage and a half-filled last stage (K = 256,
+# 768, 1280), long K
+@pytest.mark.parametrize("M,N,K", [(4, 33, 256), (8, 300, 8192), (9, 65, 768), (16, 129, 1024),
+                                   (17, 7, 512), (32, 1000, 1280), (33, 31, 256), (64, 130, 768),
+                                   (65, 258, 2048), (129, 4100, 512), (257, 96, 1024)])
+@pytest.mark.parametrize("fmt", [O.FMT_Q4, O.FMT_INT8])
+def test_kgroup_shapes(gpu, orc, fmt, M, N, K):
+    torch, ql = gpu
+    W, X = si.small_case(8100 + M + N + K, M, N, K)
+    codes, scales = orc.quantize(fmt, W)
+    codes.reshape(-1)[:8] = [0x80, 0x88, 0x08, 0x7F, 0xFF, 0xF8, 0x8F, 0x00]  # -128 / -8 too
+    Yr = orc.forward(fmt, X, O.DT_BF16, codes, scales, N)
+    Wd = np.abs(orc.dequantize(fmt, codes, scales, N, K))
+    B = (K // 32 + 48) * 2.0 ** -24 * (np.abs(si.bf16_bits_to_f32(X)).astype(np.float64) @ Wd.T)
+    Yg = run(gpu, fmt, X, codes, scales, N)
+    assert np.all(np.abs(Yg - Yr) <= B + 1e-30)
+    with ql.forced_path(ql.PATH_TILED):
+        Yt = run(gpu, fmt, X, codes, scales, N)
+    assert np.all(np.abs(Yg - Yt) <= 2 * B + 1e-30)
+
+
+@pytest.mark.parametrize("M", [7, 30, 107])
+def test_kgroup_block(gpu, orc, M):
+    """A block of layers of different lengths and epilogues in one launch,
+    every output NaN-filled; NaN and infinite activations stay in their rows."""
+    torch, ql = gpu
+    d = 512
+    rng = np.random.default_rng(8300 + M)
+    xs = {K: si.f32_to_bf16_bits(rng.standard_normal((M, K)).astype(np.float32)) for K in (d, 4 * d)}
+    xs[d][1, 5], xs[d][2, 9] = 0x7FC0, 0x7F80
+    dv = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    ents, refs = [], []
+    for i, (_, N, K) in enumerate(si.block_linears(d)):
+        codes, scales = orc.quantize(O.FMT_Q4, si.weights(rng, N, K))
+        bias = rng.standard_normal(N).astype(np.float32)
+        resid = rng.standard_normal((M, N)).astype(np.float32)
+        act = O.ACT_GELU if i == 2 else O.ACT_NONE
+        Y = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+        ents.append((ql.FMT_Q4, dv(xs[K].view(np.int16)), dv(codes), dv(scales.view(np.int16)), N,
+                     Y, dv(bias), act, dv(resid)))
+        keep = np.ones(M, bool)
+        keep[1:3] = K != d
+        P = orc.forward(O.FMT_Q4, xs[K][keep], O.DT_BF16, codes, scales, N)
+        refs.append((keep, orc.epilogue(P, bias, act, resid[keep]), np.abs(P).max()))
+    ql.block_forward_ep(ents)
+    torch.cuda.synchronize()
+    for e, (keep, ref, top) in zip(ents, refs):
+        Y = e[5].cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(Y[keep] - ref) <= 1e-5 * top + 2e-6 * np.abs(ref) + 1e-6)
+        assert not np.isfinite(Y[~keep]).any()
