@@ -137,18 +137,18 @@ int mid_tile_bn();
 int mid_wgs_per_cu();  // resident workgroups per CU
 hipError_t launch_qgemm_mid(int fmt, const GroupArgs &args, hipStream_t stream);
 
-// K-group kernel (qgemm_kg.hip: bf16 activations, int8 / q4 weights, exact,
-// no partials in memory); shape limits as the mid-M kernel's.  LinDesc::psteps
-// holds the layer's shape, and tiles_m, tiles_n count its tiles: rows 32 (R1)
-// or 64 (R2, only where some layer has more than 32 rows), columns 32, 64 or
-// 128 (W1, W2, W4).
-enum KgShape { KG_R1W1, KG_R1W2, KG_R1W4, KG_R2W2, KG_R2W4 };
-inline int kg_tile_m(int shape) { return shape >= KG_R2W2 ? 64 : 32; }
-inline int kg_tile_n(int shape)
-{
-    return shape == KG_R1W1 ? 32 : shape == KG_R1W2 || shape == KG_R2W2 ? 64 : 128;
-}
-hipError_t launch_qgemm_kg(int fmt, int maxM, const GroupArgs &args, hipStream_t stream);
+// K-group kernel (qgemm_kg.hip: exact, no partials in memory): bf16 or fp32
+// activations and int8 / q4 weights, with the mid-M kernel's limits on K and
+// alignment; or fp16 weights, with X and xexp those of launch_xprep.
+// LinDesc::psteps holds the layer's shape (a KgShape), and tiles_m, tiles_n
+// count its tiles (kg_tile_shape; {0, 0}: the launch has no such shape).
+enum KgShape { KG_R1W1, KG_R1W2, KG_R1W4, KG_R2W2, KG_R2W4, KG_SHAPES };
+struct KgTile {
+    int m, n;
+};
+KgTile kg_tile_shape(int fmt, bool xf32, int64_t maxM, int shape);
+hipError_t launch_qgemm_kg(int fmt, bool xf32, int maxM, const GroupArgs &args,
+                           hipStream_t stream);
 
 // Y[M][N] = sum over s < S of P[s][M][N], added in order s = 0, 1, ..., for
 // n (<= QL_MAX_GROUP) split layers in one launch

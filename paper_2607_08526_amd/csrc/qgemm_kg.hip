@@ -52,25 +52,26 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int WAVES = 16, NT = 64 * WAVES;
 
-template <int FMT_, int MI_, int XR_, int WN_, int BPW_, int NST_>
+template <int FMT_, bool XF32_, int XR_, int WN_, int BPW_, int NST_>
 struct KgGeo {
-    static constexpr int FMT = FMT_, MI = MI_, XR = XR_, WN = WN_, BPW = BPW_, NST = NST_;
+    static constexpr int FMT = FMT_, XR = XR_, WN = WN_, BPW = BPW_, NST = NST_;
+    static constexpr bool XF32 = XF32_;
+    static constexpr int MI = XR > 32 ? XR / 32 : 1;   // MFMA row blocks
     static constexpr int KG = WAVES / WN;
-    static constexpr int TM = 32 * MI, TN = 32 * WN;
+    static constexpr int TM = XR, TN = 32 * WN;
     static constexpr int EB = KG * BPW;                // 32-k blocks per stage
-    static constexpr int XRB = EB * 64, XCH = XRB / 16;  // activation bytes, chunks per row
-    static constexpr int CRB = FMT == QL_FMT_INT8 ? EB * 32 : EB * 16, CCH = CRB / 16;
-    static constexpr int SCH = EB / 8;                 // 16-byte scale chunks per column
+    static constexpr int XRB = EB * (XF32 ? 128 : 64), XCH = XRB / 16;  // activation bytes,
+                                                                        // chunks per row
+    static constexpr int CRB = FMT == QL_FMT_F16 ? EB * 64 : FMT == QL_FMT_INT8 ? EB * 32 : EB * 16;
+    static constexpr int CCH = CRB / 16;
+    static constexpr int SCH = FMT == QL_FMT_F16 ? 0 : EB / 8;  // 16-byte scale chunks per column
     static constexpr int XBYTES = XR * XRB, CBYTES = TN * CRB, SBYTES = TN * SCH * 16;
-    static constexpr int STAGE = XBYTES + CBYTES + SBYTES;
     // loads in units of one wavefront (1 KB); wavefront w takes units w, w +
     // 16, ..., the last ones repeated so that every wavefront counts the same
     static constexpr int XU = XBYTES / 1024, CU = CBYTES / 1024, SU = (SBYTES + 1023) / 1024;
     static constexpr int UNITS = XU + CU + SU, LOADS = (UNITS + WAVES - 1) / WAVES;
-    static constexpr int RROWS = XR < TM ? XR : TM;    // rows summed at the end
-    static constexpr int RED = KG * RROWS * TN * 4;
-    static constexpr int RING = NST * (XBYTES + CBYTES + SU * 1024);
-    static constexpr int SLOT = XBYTES + CBYTES + SU * 1024;
+    static constexpr int RED = KG * TM * TN * 4;       // the groups' sums at the end
+    static constexpr int SLOT = XBYTES + CBYTES + SU * 1024, RING = NST * SLOT;
     static constexpr int LDS = RING > RED ? RING : RED;
     static_assert(EB % 8 == 0 && XBYTES % 1024 == 0 && CBYTES % 1024 == 0, "whole loads");
     static_assert(LDS <= 160 * 1024, "LDS of a CU");
@@ -85,6 +86,12 @@ __device__ inline int cswz(int row)
     return CCH >= 16 ? row & 15 : (row >> 1) & 7;  // 128-byte rows: two per bank row
 }
 
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+__device__ inline f32x16 mfma_f16(u32x4 a, u32x4 b, f32x16 c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, a),
+                                                  __builtin_bit_cast(half8, b), c, 0, 0, 0);
+}
 __device__ inline f32x16 mfma(u32x4 a, u32x4 b, f32x16 c)
 {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
@@ -126,24 +133,46 @@ __device__ inline u32x4 cvt_q4(uint32_t w)
                  bf16_pair(sbyte(e, 2), sbyte(o, 2)), bf16_pair(sbyte(e, 3), sbyte(o, 3))};
 }
 
+// 8 fp32 activations as three bf16 planes whose sum they are exactly
+// (truncation: 8 + 8 + 8 significant bits)
+__device__ inline void split3(u32x4 v0, u32x4 v1, u32x4 &hi, u32x4 &mid, u32x4 &lo)
+{
+    uint32_t m[8], l[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const uint32_t x = e < 4 ? v0[e] : v1[e - 4];
+        const float r = __uint_as_float(x) - __uint_as_float(x & 0xFFFF0000u);
+        m[e] = __float_as_uint(r);
+        l[e] = __float_as_uint(r - __uint_as_float(m[e] & 0xFFFF0000u));
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t a = e < 2 ? v0[2 * e] : v1[2 * e - 4];
+        const uint32_t b = e < 2 ? v0[2 * e + 1] : v1[2 * e - 3];
+        hi[e] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+        mid[e] = __builtin_amdgcn_perm(m[2 * e + 1], m[2 * e], 0x07060302u);
+        lo[e] = __builtin_amdgcn_perm(l[2 * e + 1], l[2 * e], 0x07060302u);
+    }
+}
+
 // One output tile of layer d.
 template <class G>
 __device__ inline void kg_tile(const LinDesc &d, int tile, uint8_t *ring)
 {
-    constexpr int FMT = G::FMT, MI = G::MI;
-    constexpr bool Q4 = FMT == QL_FMT_Q4;
+    constexpr int FMT = G::FMT, MI = G::MI, XB = G::XF32 ? 4 : 2;
+    constexpr bool Q4 = FMT == QL_FMT_Q4, F16 = FMT == QL_FMT_F16;
     const int tm = tile % d.tiles_m, tn = tile / d.tiles_m;
     const int M = d.M, N = d.N, K = d.K, nb = K >> 5;
     const int m0 = tm * G::TM, n0 = tn * G::TN;
-    const int crow = Q4 ? K / 2 : K;
+    const int crow = Q4 ? K / 2 : F16 ? 2 * K : K;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = wave / G::WN, wn = (wave % G::WN) * 32;
 
     // this wavefront's loads: per unit a base, a per-lane offset within the
     // stage's first columns, and the bytes a stage advances.  Rows past M and
-    // N repeat the last one; chunks past K the last chunk (K % 512 == 256 and
-    // a 512-k stage; their scales are taken as 0).
+    // N repeat the last one; chunks past K (K % 512 == 256 and a 512-k stage)
+    // the last chunk, and are not used.
     const uint8_t *ub[G::LOADS];
     uint32_t urow[G::LOADS];
     int ucol[G::LOADS], ustep[G::LOADS], ulim[G::LOADS];
@@ -153,11 +182,11 @@ __device__ inline void kg_tile(const LinDesc &d, int tile, uint8_t *ring)
         const int u = min(q * WAVES + wave, G::UNITS - 1);  // wave-uniform
         if (u < G::XU) {
             const int slot = u * 64 + lane, row = slot / G::XCH;
-            ub[q] = reinterpret_cast<const uint8_t *>(d.X) + (int64_t)m0 * K * 2;
-            urow[q] = (uint32_t)((min(m0 + row, M - 1) - m0) * K * 2);
+            ub[q] = reinterpret_cast<const uint8_t *>(d.X) + (int64_t)m0 * K * XB;
+            urow[q] = (uint32_t)((min(m0 + row, M - 1) - m0) * K * XB);
             ucol[q] = ((slot % G::XCH) ^ xswz(row)) * 16;
             ustep[q] = G::XRB;
-            ulim[q] = K * 2 - 16;
+            ulim[q] = K * XB - 16;
             udst[q] = u * 1024;
         } else if (u < G::XU + G::CU) {
             const int slot = (u - G::XU) * 64 + lane, row = slot / G::CCH;
@@ -167,7 +196,7 @@ __device__ inline void kg_tile(const LinDesc &d, int tile, uint8_t *ring)
             ustep[q] = G::CRB;
             ulim[q] = crow - 16;
             udst[q] = u * 1024;
-        } else {
+        } else if constexpr (!F16) {
             // scales: chunk-major, [SCH][TN] of 16 bytes
             const int slot = ((u - G::XU - G::CU) * 64 + lane) % (G::TN * G::SCH);
             const int row = slot % G::TN;
@@ -193,12 +222,10 @@ __device__ inline void kg_tile(const LinDesc &d, int tile, uint8_t *ring)
 
     // accumulator registers that hold staged rows: 8 (r / 4) + 4 g + r % 4
     constexpr int AR = G::XR < 32 ? G::XR / 2 : 16;
-    float acc[MI][AR];
+    f32x16 acc[MI];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int r = 0; r < AR; ++r)
-            acc[i][r] = 0.0f;
+        acc[i] = f32x16{};
 
     auto step = [&](int it, auto refill) {
         constexpr bool REFILL = decltype(refill)::value;
@@ -214,24 +241,36 @@ __device__ inline void kg_tile(const LinDesc &d, int tile, uint8_t *ring)
 #pragma unroll
         for (int u = 0; u < G::BPW; ++u) {
             const int b = kg * G::BPW + u;  // block of the stage
-            uint32_t sw = *reinterpret_cast<const uint16_t *>(
-                st + G::XBYTES + G::CBYTES + ((b / 8) * G::TN + wn + l32) * 16 + (b % 8) * 2);
-            sw = it * G::EB + b < nb ? sw : 0u;
-            float s = f16_value(sw) * (Q4 ? 0.0625f : 1.0f);  // exact
-            dma_pin(s);
-            // the lane's codes of the block: 16 (int8) or 8 (q4) bytes
+            // past K (the last stage only, which refills nothing)
+            if constexpr (!REFILL)
+                if (it * G::EB + b >= nb)
+                    continue;
             const int wr = wn + l32;
+            const uint8_t *const wrow = st + G::XBYTES + wr * G::CRB;
+            float s = 1.0f;
             u32x4 wv[2];
-            if constexpr (Q4) {
-                const u32x2 c = *reinterpret_cast<const u32x2 *>(
-                    st + G::XBYTES + wr * G::CRB + (b ^ cswz<G::CCH>(wr)) * 16 + 8 * g);
-                wv[0] = cvt_q4(c[0]);
-                wv[1] = cvt_q4(c[1]);
+            if constexpr (F16) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    wv[h] = *reinterpret_cast<const u32x4 *>(
+                        wrow + ((4 * b + 2 * g + h) ^ cswz<G::CCH>(wr)) * 16);
             } else {
-                const u32x4 c = *reinterpret_cast<const u32x4 *>(
-                    st + G::XBYTES + wr * G::CRB + ((2 * b + g) ^ cswz<G::CCH>(wr)) * 16);
-                wv[0] = cvt_int8(c[0], c[1]);
-                wv[1] = cvt_int8(c[2], c[3]);
+                const uint32_t sw = *reinterpret_cast<const uint16_t *>(
+                    st + G::XBYTES + G::CBYTES + ((b / 8) * G::TN + wr) * 16 + (b % 8) * 2);
+                s = f16_value(sw) * (Q4 ? 0.0625f : 1.0f);  // exact
+                dma_pin(s);
+                // the lane's codes of the block: 16 (int8) or 8 (q4) bytes
+                if constexpr (Q4) {
+                    const u32x2 c = *reinterpret_cast<const u32x2 *>(
+                        wrow + (b ^ cswz<G::CCH>(wr)) * 16 + 8 * g);
+                    wv[0] = cvt_q4(c[0]);
+                    wv[1] = cvt_q4(c[1]);
+                } else {
+                    const u32x4 c = *reinterpret_cast<const u32x4 *>(
+                        wrow + ((2 * b + g) ^ cswz<G::CCH>(wr)) * 16);
+                    wv[0] = cvt_int8(c[0], c[1]);
+                    wv[1] = cvt_int8(c[2], c[3]);
+                }
             }
             if constexpr (REFILL)
 #pragma unroll
@@ -241,19 +280,43 @@ __device__ inline void kg_tile(const LinDesc &d, int tile, uint8_t *ring)
 #pragma unroll
             for (int i = 0; i < MI; ++i) {
                 const int xr = 32 * i + (l32 & (G::XR < 32 ? G::XR - 1 : 31));
-                u32x4 a[2];
+                const uint8_t *const xrow = st + xr * G::XRB;
+                if constexpr (G::XF32) {
+                    u32x4 hi[2], mid[2], lo[2];
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    a[h] = *reinterpret_cast<const u32x4 *>(
-                        st + xr * G::XRB + ((4 * b + 2 * g + h) ^ xswz(xr)) * 16);
-                p[i] = mfma(a[0], wv[0], f32x16{});
-                p[i] = mfma(a[1], wv[1], p[i]);
+                    for (int h = 0; h < 2; ++h) {
+                        const int lc = 8 * b + 4 * g + 2 * h;
+                        split3(*reinterpret_cast<const u32x4 *>(xrow + (lc ^ xswz(xr)) * 16),
+                               *reinterpret_cast<const u32x4 *>(xrow + ((lc + 1) ^ xswz(xr)) * 16),
+                               hi[h], mid[h], lo[h]);
+                    }
+                    p[i] = mfma(lo[0], wv[0], f32x16{});
+                    p[i] = mfma(lo[1], wv[1], p[i]);
+                    p[i] = mfma(mid[0], wv[0], p[i]);
+                    p[i] = mfma(mid[1], wv[1], p[i]);
+                    p[i] = mfma(hi[0], wv[0], p[i]);
+                    p[i] = mfma(hi[1], wv[1], p[i]);
+                } else {
+                    u32x4 a[2];
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        a[h] = *reinterpret_cast<const u32x4 *>(
+                            xrow + ((4 * b + 2 * g + h) ^ xswz(xr)) * 16);
+                    if constexpr (F16) {
+                        acc[i] = mfma_f16(a[0], wv[0], acc[i]);
+                        acc[i] = mfma_f16(a[1], wv[1], acc[i]);
+                    } else {
+                        p[i] = mfma(a[0], wv[0], f32x16{});
+                        p[i] = mfma(a[1], wv[1], p[i]);
+                    }
+                }
             }
+            if constexpr (!F16)
 #pragma unroll
-            for (int i = 0; i < MI; ++i)
+                for (int i = 0; i < MI; ++i)
 #pragma unroll
-                for (int r = 0; r < AR; ++r)
-                    acc[i][r] = __builtin_fmaf(s, p[i][r], acc[i][r]);
+                    for (int r = 0; r < AR; ++r)
+                        acc[i][r] = __builtin_fmaf(s, p[i][r], acc[i][r]);
         }
     };
     int it = 0;
@@ -275,12 +338,12 @@ __device__ inline void kg_tile(const LinDesc &d, int tile, uint8_t *ring)
     for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int r = 0; r < AR; ++r)
-            red[(kg * G::RROWS + 32 * i + 8 * (r >> 2) + 4 * g + (r & 3)) * G::TN + wn + l32] =
+            red[(kg * G::TM + 32 * i + 8 * (r >> 2) + 4 * g + (r & 3)) * G::TN + wn + l32] =
                 acc[i][r];
     __syncthreads();
     const bool vec = epi_vec_ok(d.ep, d.Y, N);
 #pragma unroll 1
-    for (int q = tid; q < G::RROWS * G::TN / 4; q += NT) {
+    for (int q = tid; q < G::TM * G::TN / 4; q += NT) {
         const int m = m0 + q / (G::TN / 4), n = n0 + 4 * (q % (G::TN / 4));
         if (m >= M || n >= N)
             continue;
@@ -288,7 +351,13 @@ __device__ inline void kg_tile(const LinDesc &d, int tile, uint8_t *ring)
         f32x4 v = src[0];
 #pragma unroll
         for (int k = 1; k < G::KG; ++k)
-            v += src[k * (G::RROWS * G::TN / 4)];
+            v += src[k * (G::TM * G::TN / 4)];
+        if constexpr (F16) {  // the activations' row shift
+            const int e = d.xexp[m];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                v[k] = __builtin_ldexpf(v[k], e);
+        }
         const int64_t idx = (int64_t)m * N + n;
         if (vec) {
             epi_store4(d.ep, d.Y, idx, n, v, false);
@@ -300,29 +369,59 @@ __device__ inline void kg_tile(const LinDesc &d, int tile, uint8_t *ring)
     }
 }
 
-// The shapes a launch may mix, XR = 8, 16 or 32 for launches of at most that
-// many rows and 64 above.
+// The shapes a launch may mix.  bf16 X and quantized weights: XR = 8, 16 or
+// 32 for launches of at most that many rows and 64 above.
 template <int FMT, int XR>
 struct KgShapes {
     static constexpr bool I8 = FMT == QL_FMT_INT8;
     static constexpr int XR1 = XR < 32 ? XR : 32;
     // up to 8 rows a stage is small: twice the k per stage, half the barriers
     static constexpr bool FEW = XR <= 8;
-    using R1W4 = KgGeo<FMT, 1, XR1, 4, FEW ? 4 : 2, FEW && I8 ? 2 : 3>;
-    using R1W2 = KgGeo<FMT, 1, XR1, 2, FEW ? 2 : 1, 3>;
-    using R1W1 = KgGeo<FMT, 1, XR1, 1, FEW ? 2 : 1, 3>;
-    using R2W4 = KgGeo<FMT, 2, 64, 4, 2, I8 ? 2 : 3>;
-    using R2W2 = KgGeo<FMT, 2, 64, 2, 1, 3>;
-    static constexpr int LDS1 = std::max(R1W4::LDS, std::max(R1W2::LDS, R1W1::LDS));
-    static constexpr int LDS =
-        XR > 32 ? std::max(LDS1, std::max(R2W4::LDS, R2W2::LDS)) : LDS1;
+    using R1W4 = KgGeo<FMT, false, XR1, 4, FEW ? 4 : 2, FEW && I8 ? 2 : 3>;
+    using R1W2 = KgGeo<FMT, false, XR1, 2, FEW ? 2 : 1, 3>;
+    using R1W1 = KgGeo<FMT, false, XR1, 1, FEW ? 2 : 1, 3>;
+    using R2W4 = KgGeo<FMT, false, 64, 4, 2, I8 ? 2 : 3>;
+    using R2W2 = KgGeo<FMT, false, 64, 2, 1, 3>;
+    static constexpr bool R2 = XR > 32;
+    static constexpr bool R2_W4 = R2;
+};
+// fp16 weights (X the fp16 copy of the pre-pass)
+template <int XR>
+struct KgShapes<QL_FMT_F16, XR> {
+    using R1W4 = KgGeo<QL_FMT_F16, false, 32, 4, 2, 2>;
+    using R1W2 = KgGeo<QL_FMT_F16, false, 32, 2, 1, 3>;
+    using R1W1 = KgGeo<QL_FMT_F16, false, 32, 1, 1, 2>;
+    using R2W2 = KgGeo<QL_FMT_F16, false, 64, 2, 1, 2>;
+    using R2W4 = R2W2;
+    static constexpr bool R2 = true, R2_W4 = false;
+};
+// fp32 X: row tiles of 16 and 32 (a stage of 64 fp32 rows leaves no room for
+// a second one)
+template <int FMT>
+struct KgShapesF32 {
+    using R1W4 = KgGeo<FMT, true, 32, 4, 2, FMT == QL_FMT_INT8 ? 2 : 3>;
+    using R1W2 = KgGeo<FMT, true, 32, 2, 1, 3>;
+    using R1W1 = KgGeo<FMT, true, 16, 1, 1, 3>;
+    using R2W2 = KgGeo<FMT, true, 16, 2, 1, 3>;
+    using R2W4 = R2W2;
+    static constexpr bool R2 = true, R2_W4 = false;
 };
 
-template <int FMT, int XR>
+template <class S>
+constexpr int kg_lds()
+{
+    int v = std::max(S::R1W4::LDS, std::max(S::R1W2::LDS, S::R1W1::LDS));
+    if constexpr (S::R2)
+        v = std::max(v, S::R2W2::LDS);
+    if constexpr (S::R2_W4)
+        v = std::max(v, S::R2W4::LDS);
+    return v;
+}
+
+template <class S>
 __global__ __launch_bounds__(NT, 4) void qgemm_kg_kernel(const GroupArgs args)
 {
-    using S = KgShapes<FMT, XR>;
-    __shared__ __align__(16) uint8_t ring[S::LDS];
+    __shared__ __align__(16) uint8_t ring[kg_lds<S>()];
     const int p = (int)blockIdx.x;
     LinDesc d = args.d[0];
     int end = args.total_tiles;
@@ -334,7 +433,7 @@ __global__ __launch_bounds__(NT, 4) void qgemm_kg_kernel(const GroupArgs args)
             end = args.d[t].tile_begin;
     }
     const int tile = logical_tile(p - d.tile_begin, end - d.tile_begin);
-    switch (d.psteps) {  // shape (kg_plan)
+    switch (d.psteps) {  // shape (the host's plan)
     case KG_R1W1:
         kg_tile<typename S::R1W1>(d, tile, ring);
         break;
@@ -344,37 +443,68 @@ __global__ __launch_bounds__(NT, 4) void qgemm_kg_kernel(const GroupArgs args)
     case KG_R1W4:
         kg_tile<typename S::R1W4>(d, tile, ring);
         break;
+    case KG_R2W2:
+        if constexpr (S::R2)
+            kg_tile<typename S::R2W2>(d, tile, ring);
+        break;
     default:
-        if constexpr (XR > 32) {
-            if (d.psteps == KG_R2W2)
-                kg_tile<typename S::R2W2>(d, tile, ring);
-            else
-                kg_tile<typename S::R2W4>(d, tile, ring);
-        }
+        if constexpr (S::R2_W4)
+            kg_tile<typename S::R2W4>(d, tile, ring);
     }
 }
 
-template <int FMT>
-hipError_t launch_fmt(int maxM, const GroupArgs &a, hipStream_t s)
+template <class S>
+hipError_t launch_shapes(const GroupArgs &a, hipStream_t s)
 {
-    const dim3 grid((unsigned)a.total_tiles), block(NT);
-    if (maxM > 32)
-        hipLaunchKernelGGL((qgemm_kg_kernel<FMT, 64>), grid, block, 0, s, a);
-    else if (maxM > 16)
-        hipLaunchKernelGGL((qgemm_kg_kernel<FMT, 32>), grid, block, 0, s, a);
-    else if (maxM > 8)
-        hipLaunchKernelGGL((qgemm_kg_kernel<FMT, 16>), grid, block, 0, s, a);
-    else
-        hipLaunchKernelGGL((qgemm_kg_kernel<FMT, 8>), grid, block, 0, s, a);
+    hipLaunchKernelGGL(qgemm_kg_kernel<S>, dim3((unsigned)a.total_tiles), dim3(NT), 0, s, a);
     return hipGetLastError();
+}
+
+template <int FMT>
+hipError_t launch_fmt(bool xf32, int maxM, const GroupArgs &a, hipStream_t s)
+{
+    if (xf32)
+        return launch_shapes<KgShapesF32<FMT>>(a, s);
+    return maxM > 32   ? launch_shapes<KgShapes<FMT, 64>>(a, s)
+           : maxM > 16 ? launch_shapes<KgShapes<FMT, 32>>(a, s)
+           : maxM > 8  ? launch_shapes<KgShapes<FMT, 16>>(a, s)
+                       : launch_shapes<KgShapes<FMT, 8>>(a, s);
+}
+
+// rows and columns of a shape's tile
+template <class S>
+KgTile tile_of(int shape)
+{
+    switch (shape) {
+    case KG_R1W1: return KgTile{S::R1W1::TM, S::R1W1::TN};
+    case KG_R1W2: return KgTile{S::R1W2::TM, S::R1W2::TN};
+    case KG_R1W4: return KgTile{S::R1W4::TM, S::R1W4::TN};
+    case KG_R2W2: return S::R2 ? KgTile{S::R2W2::TM, S::R2W2::TN} : KgTile{0, 0};
+    default: return S::R2_W4 ? KgTile{S::R2W4::TM, S::R2W4::TN} : KgTile{0, 0};
+    }
 }
 
 }  // namespace
 
-hipError_t launch_qgemm_kg(int fmt, int maxM, const GroupArgs &args, hipStream_t stream)
+KgTile kg_tile_shape(int fmt, bool xf32, int64_t maxM, int shape)
 {
-    return fmt == QL_FMT_INT8 ? launch_fmt<QL_FMT_INT8>(maxM, args, stream)
-                              : launch_fmt<QL_FMT_Q4>(maxM, args, stream);
+    // (the tiles of int8 and q4 are alike)
+    if (fmt == QL_FMT_F16)
+        return tile_of<KgShapes<QL_FMT_F16, 64>>(shape);
+    if (xf32)
+        return tile_of<KgShapesF32<QL_FMT_Q4>>(shape);
+    return maxM > 32   ? tile_of<KgShapes<QL_FMT_Q4, 64>>(shape)
+           : maxM > 16 ? tile_of<KgShapes<QL_FMT_Q4, 32>>(shape)
+           : maxM > 8  ? tile_of<KgShapes<QL_FMT_Q4, 16>>(shape)
+                       : tile_of<KgShapes<QL_FMT_Q4, 8>>(shape);
+}
+
+hipError_t launch_qgemm_kg(int fmt, bool xf32, int maxM, const GroupArgs &args, hipStream_t stream)
+{
+    if (fmt == QL_FMT_F16)
+        return launch_shapes<KgShapes<QL_FMT_F16, 64>>(args, stream);
+    return fmt == QL_FMT_INT8 ? launch_fmt<QL_FMT_INT8>(xf32, maxM, args, stream)
+                              : launch_fmt<QL_FMT_Q4>(xf32, maxM, args, stream);
 }
 
 }  // namespace qlk

@@ -671,6 +671,14 @@ bool mid_fits(const ql_linear &l)
            aligned(l.codes, 16) && aligned(l.scales, 16);
 }
 
+// the K-group kernel's limits: the same without the type of X, and fp16
+// weights, which have no scales
+bool kg_fits(const ql_linear &l)
+{
+    return l.K % 256 == 0 && l.K < ((int64_t)1 << 22) && aligned(l.X, 16) &&
+           aligned(l.codes, 16) && (l.fmt == QL_FMT_F16 || aligned(l.scales, 16));
+}
+
 void plan_mid(GroupArgs &a)
 {
     const int n = a.n;
@@ -800,8 +808,9 @@ int launch_mid(const ql_linear_ep *const *ls, int n, WsSource &wsrc, hipStream_t
 // The K-group kernel (qgemm_kg.hip): a shape (KgShape) per layer and the
 // estimated time of the launch in us.  A workgroup of a shape takes KG_BASE
 // plus its 256-k stages at the measured rate; one workgroup is resident per
-// CU.  For every bound on the longest workgroup, each layer takes the shape
-// of least total work within it; the launch then lasts the longest
+// CU.  For every shape of every layer, taken as the bound on the longest
+// workgroup, each other layer takes the shape of least total work within it;
+// the launch then lasts the longest
 // workgroup, or, with more workgroups than CUs, the work per CU plus half
 // the longest one (the tail).  Within 10% of the measured time on most of
 // 160 single layers and blocks (d = 512 to 2048, 5 to 640 rows).
@@ -810,33 +819,43 @@ struct KgPlan {
     double us;
 };
 
-// Below 4 rows the GEMV is ahead (a d = 2048 block at 4 rows: int8 22.5 us,
+// Below 4 bf16 rows the GEMV is ahead (a d = 2048 block at 4 rows: int8 22.5 us,
 // q4 streamed 17.1, against about 16 and 14 here); beyond the upper bound the
 // large-M kernel has a tile per CU for any layer of some width
 constexpr int64_t KG_MIN_M = 4, KG_MAX_M = 2048;
 
-// us per 256 k of a workgroup, measured on full launches (q4, int8), and the
-// share of it at 16 rows and below (fewer activation bytes)
-constexpr double KG_RATE[5][2] = {
-    {0.35, 0.43}, {0.55, 0.70}, {1.00, 1.00}, {0.85, 0.85}, {1.43, 1.40}};
+// us per 256 k of a workgroup of each shape, measured on full launches, by
+// kind: q4, int8, fp16 weights; q4 and int8 with fp32 X.  At 16 bf16 rows and
+// below, KG_FEW of it (fewer activation bytes).
+constexpr double KG_RATE[5][KG_SHAPES] = {{0.35, 0.55, 1.00, 0.85, 1.43},
+                                          {0.43, 0.70, 1.00, 0.85, 1.40},
+                                          {0.81, 0.88, 1.70, 1.35, 0.0},
+                                          {0.60, 1.17, 2.23, 1.15, 0.0},
+                                          {0.62, 1.17, 2.20, 1.10, 0.0}};
 constexpr double KG_FEW = 0.75;
-constexpr double KG_BASE = 3.0, KG_LAUNCH = 1.2;
+// us: a workgroup's start, sums and stores; the launch; the pre-pass launch of
+// fp16 weights
+constexpr double KG_BASE = 3.0, KG_LAUNCH = 1.2, KG_PREPASS = 4.0;
 
 KgPlan kg_plan(int fmt, const ql_linear_ep *const *ls, int n)
 {
-    const int f = fmt == QL_FMT_INT8 ? 1 : 0, cus = device_cus();
+    const int cus = device_cus();
     int64_t maxM = 0;
     for (int i = 0; i < n; ++i)
         maxM = std::max(maxM, ls[i]->lin.M);
-    const int shapes = maxM > 32 ? 5 : 3;
-    const double few = maxM <= 16 ? KG_FEW : 1.0;
-    double t[QL_MAX_GROUP][5], w[QL_MAX_GROUP][5];  // us of a workgroup, workgroups
+    const bool xf32 = ls[0]->lin.xdt == QL_DT_F32;
+    const int shapes = KG_SHAPES;
+    const double few = maxM <= 16 && fmt != QL_FMT_F16 && !xf32 ? KG_FEW : 1.0;
+    const double *const rate =
+        KG_RATE[fmt == QL_FMT_F16 ? 2 : (xf32 ? 3 : 0) + (fmt == QL_FMT_INT8 ? 1 : 0)];
+    const double launch = KG_LAUNCH + (fmt == QL_FMT_F16 ? KG_PREPASS : 0.0);
+    double t[QL_MAX_GROUP][KG_SHAPES], w[QL_MAX_GROUP][KG_SHAPES];  // us of a workgroup, workgroups
     for (int i = 0; i < n; ++i)
         for (int s = 0; s < shapes; ++s) {
             const ql_linear &l = ls[i]->lin;
-            t[i][s] = KG_BASE + (double)(l.K / 256) * KG_RATE[s][f] * few;
-            w[i][s] = (double)(((l.M + kg_tile_m(s) - 1) / kg_tile_m(s)) *
-                               ((l.N + kg_tile_n(s) - 1) / kg_tile_n(s)));
+            const KgTile kt = kg_tile_shape(fmt, xf32, maxM, s);
+            t[i][s] = kt.m ? KG_BASE + (double)(l.K / 256) * rate[s] * few : 1e30;
+            w[i][s] = kt.m ? (double)((l.M + kt.m - 1) / kt.m * ((l.N + kt.n - 1) / kt.n)) : 1.0;
         }
     KgPlan best{};
     best.us = 1e30;
@@ -846,8 +865,8 @@ KgPlan kg_plan(int fmt, const ql_linear_ep *const *ls, int n)
             double longest = 0.0, work = 0.0, wgs = 0.0;
             bool ok = true;
             for (int j = 0; j < n && ok; ++j) {
-                int c = -1;
-                for (int q = 0; q < shapes; ++q)
+                int c = j == i ? s : -1;
+                for (int q = 0; q < shapes && j != i; ++q)
                     if (t[j][q] <= t[i][s] && (c < 0 || w[j][q] * t[j][q] < w[j][c] * t[j][c]))
                         c = q;
                 ok = c >= 0;
@@ -860,7 +879,7 @@ KgPlan kg_plan(int fmt, const ql_linear_ep *const *ls, int n)
             }
             if (!ok)
                 continue;
-            p.us = KG_LAUNCH +
+            p.us = launch +
                    (wgs <= cus ? longest : std::max(longest, work / cus + 0.5 * longest));
             if (p.us < best.us)
                 best = p;
@@ -868,18 +887,24 @@ KgPlan kg_plan(int fmt, const ql_linear_ep *const *ls, int n)
     return best;
 }
 
-// Whether a group (one quantized format, bf16 X, mid_fits each, ordered as
-// launched) goes to the K-group kernel, and its shapes.  Measured on q4 and
-// int8 single layers and blocks at 5 to 1000 rows, each against the kernel
-// that ran before:
-//   up to 32 rows: where its estimate is under 0.8 of the streaming kernel's
-//     (blocks 1.1-1.7 times faster; single layers, which cannot fill the GPU
-//     with whole reductions, mostly stay: 2048 x 8192 at 8 rows 9.0 us
+// Whether a group (one format and activation type, kg_fits each, ordered as
+// launched) goes to the K-group kernel, and its shapes.  Measured on single
+// layers and blocks at 1 to 1000 rows, each against the kernel that ran
+// before:
+//   bf16 X, up to 32 rows: where its estimate is under 0.8 of the streaming
+//     kernel's (blocks 1.1-1.7 times faster; single layers, which cannot fill
+//     the GPU with whole reductions, mostly stay: 2048 x 8192 at 8 rows 9.0 us
 //     streamed against 11.6);
-//   33 to 64 rows: always (1.3-2.4 times faster than the mid-M kernel);
-//   above: where its estimate is under 8 us + 0.8 of the large-M plan's steps
-//     (up to 3 times faster: 768 x 768 at 500 rows 19.4 -> 5.9 us; no case
-//     of 260 where the rule picks the slower one).
+//   bf16 X, 33 to 64 rows: always (1.3-2.4 times faster than the mid-M kernel);
+//   bf16 X above: where its estimate is under 8 us + 0.8 of the large-M plan's
+//     steps (up to 3 times faster: 768 x 768 at 500 rows 19.4 -> 5.9 us; no
+//     case of 260 where the rule picks the slower one);
+//   fp16 weights: under 12 us + the plan's steps (that kernel has one
+//     workgroup per CU there: 4608 x 1536 at 214 rows 27.2 -> 14.9 us, 2048 x
+//     8192 at 400 rows stays, 41 against 50);
+//   fp32 X: where its estimate is under a fixed part plus 1.2 us per 64-k
+//     step of the tiled kernel's two workgroups per CU (1024 x 1024 at 64 rows
+//     15.9 -> 6.6 us; 2048 x 8192 at 8 rows stays, 20.6 against 23.0).
 struct KgChoice {
     bool use;
     KgPlan plan;
@@ -902,7 +927,17 @@ KgChoice kg_choose(int fmt, const ql_linear_ep *const *ord, int n)
         ds[i].tiles_m = (int)((l.M + wide_tile_bm() - 1) / wide_tile_bm());
         ds[i].tiles_n = (int)((l.N + wide_tile_bn() - 1) / wide_tile_bn());
     }
-    if (maxM <= stream_max_m()) {
+    if (ord[0]->lin.xdt == QL_DT_F32) {
+        const TileCfg tc = choose_tile(maxM, true);
+        double steps = 0.0;
+        for (int i = 0; i < n; ++i)
+            steps += (double)((ds[i].M + tile_bm(tc) - 1) / tile_bm(tc)) *
+                     ((ds[i].N + tile_bn(tc) - 1) / tile_bn(tc)) * (ds[i].K / 64);
+        c.use = c.plan.us < (maxM <= 32 ? 10.0 : 14.0) +
+                                1.2 * std::max(4.0, steps / (2.0 * device_cus()));
+    } else if (fmt == QL_FMT_F16) {
+        c.use = c.plan.us < 12.0 + plan_splits(fmt, ds, n).t;
+    } else if (maxM <= stream_max_m()) {
         int S[QL_MAX_GROUP], P[QL_MAX_GROUP];
         c.use = c.plan.us < 0.8 * stream_plan(fmt, ds, n, device_cus(), S, P).us;
     } else {
@@ -916,7 +951,7 @@ KgChoice kg_choose(int fmt, const ql_linear_ep *const *ord, int n)
 KgChoice cached_kg_choice(int fmt, const ql_linear_ep *const *ord, int n)
 {
     struct Entry {
-        int fmt, n, cus;
+        int fmt, xdt, n, cus;
         int64_t shape[QL_MAX_GROUP][4];
         KgChoice c;
     };
@@ -926,6 +961,7 @@ KgChoice cached_kg_choice(int fmt, const ql_linear_ep *const *ord, int n)
     static int used = 0, next = 0;
     Entry key{};
     key.fmt = fmt;
+    key.xdt = ord[0]->lin.xdt;
     key.n = n;
     key.cus = device_cus();
     for (int i = 0; i < n; ++i) {
@@ -938,7 +974,7 @@ KgChoice cached_kg_choice(int fmt, const ql_linear_ep *const *ord, int n)
     {
         std::lock_guard<std::mutex> g(mu);
         for (int e = 0; e < used; ++e)
-            if (cache[e].fmt == fmt && cache[e].n == n && cache[e].cus == key.cus &&
+            if (cache[e].fmt == fmt && cache[e].xdt == key.xdt && cache[e].n == n && cache[e].cus == key.cus &&
                 std::equal(&cache[e].shape[0][0], &cache[e].shape[0][0] + 4 * n, &key.shape[0][0]))
                 return cache[e].c;
     }
@@ -956,10 +992,11 @@ int launch_kg(const ql_linear_ep *const *ord, int n, const KgPlan &plan, WsSourc
     GroupArgs a{};
     a.n = n;
     int64_t maxM = 0, total = 0;
+    for (int i = 0; i < n; ++i)
+        maxM = std::max(maxM, ord[i]->lin.M);
     for (int i = 0; i < n; ++i) {
         LinDesc &d = a.d[i];
         const ql_linear &l = ord[i]->lin;
-        maxM = std::max(maxM, l.M);
         d.X = l.X;
         d.codes = (const uint8_t *)l.codes;
         d.scales = l.scales;
@@ -970,18 +1007,63 @@ int launch_kg(const ql_linear_ep *const *ord, int n, const KgPlan &plan, WsSourc
         d.K = (int)l.K;
         d.ksplit = 1;
         d.psteps = plan.shape[i];
-        d.tiles_m = (int)((l.M + kg_tile_m(d.psteps) - 1) / kg_tile_m(d.psteps));
-        d.tiles_n = (int)((l.N + kg_tile_n(d.psteps) - 1) / kg_tile_n(d.psteps));
+        const KgTile kt = kg_tile_shape(l.fmt, l.xdt == QL_DT_F32, maxM, d.psteps);
+        d.tiles_m = (int)((l.M + kt.m - 1) / kt.m);
+        d.tiles_n = (int)((l.N + kt.n - 1) / kt.n);
         d.tile_begin = (int)total;
         total += (int64_t)d.tiles_m * d.tiles_n;
     }
     if (total >= I31)
         return QL_ERR_UNSUPPORTED;
     a.total_tiles = (int)total;
+    // fp16 weights: the exact row-shifted fp16 copies of the distinct
+    // activation tensors first (layers reading the same X share one)
+    const bool f16 = ord[0]->lin.fmt == QL_FMT_F16;
+    int src[QL_MAX_GROUP];
+    size_t xoff[QL_MAX_GROUP], bytes = 0;
+    for (int i = 0; i < n && f16; ++i) {
+        const LinDesc &d = a.d[i];
+        src[i] = i;
+        for (int j = 0; j < i && src[i] == i; ++j)
+            if (a.d[j].X == d.X && a.d[j].M == d.M && a.d[j].K == d.K)
+                src[i] = j;
+        if (src[i] == i) {
+            xoff[i] = bytes;
+            bytes += round256((size_t)d.M * d.K * 2) + round256((size_t)d.M * 4);
+        }
+    }
+    wsrc.need = std::max(wsrc.need, bytes);
     if (wsrc.dry_run)
         return QL_OK;
-    return launch_qgemm_kg(ord[0]->lin.fmt, (int)maxM, a, stream) == hipSuccess ? QL_OK
-                                                                                : QL_ERR_HIP;
+    hipError_t e = hipSuccess;
+    Workspace ws{};
+    if (f16) {
+        if (!get_workspace(wsrc, bytes, stream, ws))
+            return wsrc.fixed ? QL_ERR_UNSUPPORTED : QL_ERR_HIP;
+        XprepJob jobs[QL_MAX_GROUP];
+        int njobs = 0;
+        for (int i = 0; i < n; ++i)
+            if (src[i] == i) {
+                const LinDesc &d = a.d[i];
+                uint8_t *const x = ws.ptr + xoff[i];
+                jobs[njobs++] = XprepJob{d.X, d.M, d.K, (uint16_t *)x,
+                                         (int *)(x + round256((size_t)d.M * d.K * 2))};
+            }
+        e = launch_xprep(jobs, njobs, nullptr, 0, false, nullptr, 0, stream);
+        for (int i = 0; i < n; ++i) {
+            const LinDesc &d = a.d[i];
+            a.d[i].X = ws.ptr + xoff[src[i]];
+            a.d[i].xexp = (const int *)(ws.ptr + xoff[src[i]] +
+                                        round256((size_t)d.M * d.K * 2));
+        }
+    }
+    if (e == hipSuccess)
+        e = launch_qgemm_kg(ord[0]->lin.fmt, ord[0]->lin.xdt == QL_DT_F32, (int)maxM, a, stream);
+    if (ws.own_alloc) {
+        const hipError_t ef = hipFreeAsync(ws.ptr, stream);
+        e = e == hipSuccess ? ef : e;
+    }
+    return e == hipSuccess ? QL_OK : QL_ERR_HIP;
 }
 
 // One grouped launch over layers that share fmt and xdt (M > 0 each).
@@ -1000,8 +1082,10 @@ int launch_group(const ql_linear_ep *const *ls, int n, WsSource &wsrc, hipStream
     bool all_mid = true;
     for (int i = 0; i < n; ++i)
         all_mid = all_mid && mid_fits(ls[i]->lin);
-    if (forced == QL_PATH_AUTO && !xf32 && !f16 && all_mid && maxM >= KG_MIN_M &&
-        maxM <= KG_MAX_M) {
+    bool all_kg = forced == QL_PATH_AUTO && maxM <= KG_MAX_M && (xf32 || f16 || maxM >= KG_MIN_M);
+    for (int i = 0; i < n; ++i)
+        all_kg = all_kg && kg_fits(ls[i]->lin);
+    if (all_kg) {
         // longest reduction first, so the long tiles start early
         const ql_linear_ep *ord[QL_MAX_GROUP];
         std::copy(ls, ls + n, ord);

@@ -56,6 +56,32 @@ def test_kgroup_shapes(gpu, orc, fmt, M, N, K):
     assert np.all(np.abs(Yg - Yt) <= 2 * B + 1e-30)
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 33, 256), (16, 65, 768), (17, 300, 1280), (64, 1024, 1024),
+                                   (70, 131, 512), (214, 4608, 512)])
+@pytest.mark.parametrize("kind", ["q4 f32", "int8 f32", "f16"])
+def test_kgroup_fp32_and_fp16(gpu, orc, kind, M, N, K):
+    """fp32 activations (three exact bf16 planes, six MFMAs per block) and fp16
+    weights (X shifted to fp16, exact up to 2^-29 of the row's maximum), the
+    same bound with 96 and 32 products per block."""
+    torch, ql = gpu
+    dv = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    f16 = kind == "f16"
+    W, X = si.small_case(8400 + M + N + K, M, N, K, O.DT_BF16 if f16 else O.DT_F32)
+    X[M - 1] = X[M - 1] if f16 else X[M - 1] * np.float32(1e-6)
+    if f16:
+        fmt, codes, scales, x = ql.FMT_F16, W.astype(np.float16), None, si.bf16_bits_to_f32(X)
+        Wd, xd = codes.astype(np.float64), dv(X.view(np.int16))
+    else:
+        fmt = ql.FMT_Q4 if kind[:2] == "q4" else ql.FMT_INT8
+        codes, scales = orc.quantize(fmt, W)
+        Wd, x, xd = orc.dequantize(fmt, codes, scales, N, K), X, dv(X)
+    Yr = x.astype(np.float64) @ Wd.T
+    B = (K // 32 + 112) * 2.0 ** -24 * (np.abs(x).astype(np.float64) @ np.abs(Wd).T)
+    Y = ql.forward(fmt, xd, dv(codes), None if f16 else dv(scales.view(np.int16)), N)
+    torch.cuda.synchronize()
+    assert np.all(np.abs(Y.cpu().numpy().astype(np.float64) - Yr) <= B + 1e-30)
+
+
 @pytest.mark.parametrize("M", [7, 30, 107])
 def test_kgroup_block(gpu, orc, M):
     """A block of layers of different lengths and epilogues in one launch,
