@@ -132,9 +132,9 @@ size_t qlinear_scales_bytes(int64_t N, int64_t K);
  * scale rounds to +inf (absmax / Q >= 65520); the outputs are then
  * unspecified.  Once it returns QL_OK the caller may free W: the codes and
  * scales replace the full-precision copy (paper: the compressed copy owns its
- * memory and the source is released once packed).  Allocates and frees one
- * 4-byte device status word per call (a load-time operation, not a per-step
- * one).  Sizes: N * K < 2^40. */
+ * memory and the source is released once packed).  Its status comes back
+ * through a word of pinned host memory (a 4 KB page per 64 concurrent calls,
+ * kept until the process ends).  Sizes: N * K < 2^40. */
 int qlinear_quantize(int fmt, const float *W, int64_t N, int64_t K,
                      void *codes, uint16_t *scales, hipStream_t stream);
 

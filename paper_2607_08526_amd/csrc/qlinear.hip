@@ -5,6 +5,7 @@
 #include <atomic>
 #include <functional>
 #include <mutex>
+#include <new>
 #include <queue>
 #include <vector>
 
@@ -1368,6 +1369,61 @@ uint8_t *scratch_base()
     return base[dev];
 }
 
+// Status words of the synchronous quantizer: pinned host memory that the
+// kernel writes into and the host reads after its wait.  (A device word cost
+// an allocation, a clear, a copy and a free per call, 20 of the 50 us of a
+// 8192 x 2048 weight.)  One page of words per concurrent page-full of calls,
+// kept until the process ends; a word belongs to one call at a time.
+struct StatusSlot {
+    int *word;
+    StatusSlot() : word(nullptr)
+    {
+        std::lock_guard<std::mutex> g(mutex());
+        if (!spare())
+            return;
+        std::vector<int *> &f = *spare();
+        if (f.empty()) {
+            constexpr int WORDS = 64, STRIDE = 16;  // a cache line each
+            void *p = nullptr;
+            if (hipHostMalloc(&p, WORDS * STRIDE * sizeof(int),
+                              hipHostMallocPortable | hipHostMallocMapped) != hipSuccess)
+                return;
+            try {
+                f.reserve(f.capacity() + WORDS);
+            } catch (...) {
+                (void)hipHostFree(p);  // already failing; nothing to report
+                return;
+            }
+            for (int i = 0; i < WORDS; ++i)
+                f.push_back((int *)p + i * STRIDE);
+        }
+        word = f.back();
+        f.pop_back();
+    }
+    ~StatusSlot()
+    {
+        if (!word)
+            return;
+        std::lock_guard<std::mutex> g(mutex());
+        spare()->push_back(word);  // within the reserved capacity
+    }
+    StatusSlot(const StatusSlot &) = delete;
+    StatusSlot &operator=(const StatusSlot &) = delete;
+
+private:
+    static std::mutex &mutex()
+    {
+        static std::mutex mu;
+        return mu;
+    }
+    // never destroyed: a call may still run while the process ends
+    static std::vector<int *> *spare()
+    {
+        static std::vector<int *> *f = new (std::nothrow) std::vector<int *>;
+        return f;
+    }
+};
+
 }  // namespace
 
 extern "C" {
@@ -1402,20 +1458,15 @@ int qlinear_quantize(int fmt, const float *W, int64_t N, int64_t K, void *codes,
     if (!aligned(W, 16) || !aligned(codes, 16) || !aligned(scales, 2))
         return QL_ERR_ALIGN;
 
-    int *dstatus = nullptr;
-    if (hipMalloc(&dstatus, sizeof(int)) != hipSuccess)
+    StatusSlot slot;
+    if (!slot.word)
         return QL_ERR_HIP;
-    int hstatus = QL_OK;
-    bool ok = hipMemsetAsync(dstatus, 0, sizeof(int), stream) == hipSuccess;
-    ok = ok && launch_quantize(fmt, W, N, K, (uint8_t *)codes, scales, dstatus, stream) ==
-                   hipSuccess;
-    ok = ok && hipMemcpyAsync(&hstatus, dstatus, sizeof(int), hipMemcpyDeviceToHost, stream) ==
-                   hipSuccess;
-    ok = ok && hipStreamSynchronize(stream) == hipSuccess;
-    ok = hipFree(dstatus) == hipSuccess && ok;
-    if (!ok)
-        return QL_ERR_HIP;
-    return hstatus;
+    *slot.word = QL_OK;
+    bool ok = launch_quantize(fmt, W, N, K, (uint8_t *)codes, scales, slot.word, stream) ==
+              hipSuccess;
+    // (waited for also after a failed launch: the word is given back below)
+    ok = hipStreamSynchronize(stream) == hipSuccess && ok;
+    return ok ? *(volatile int *)slot.word : QL_ERR_HIP;
 }
 
 int qlinear_forward_ep(int fmt, const void *X, int xdt, int64_t M, int64_t K, const void *codes,

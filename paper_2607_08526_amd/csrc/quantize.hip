@@ -7,10 +7,12 @@
 // rounding of the exact quotient, ties to even), code = nearest integer to
 // w / scale (ties to even) clamped to [-Q, Q]; Q = 127 (int8) or 7 (q4).
 //
-// Exactness: the quotients are formed in fp64 (w has 24 and the scale 11
-// significant bits, Q < 2^7), which keeps every rounding decision identical
-// to rounding the exact real quotient; fp64 -> fp16 is converted directly
-// from the fp64 bit pattern with integer arithmetic, never through fp32.
+// Exactness: neither quotient is formed.  An fp32 estimate of the scale is
+// corrected by comparing absmax with exact midpoints (scale_bits), one of a
+// code by its exact remainder (nearest_code).
+//
+// Bound: HBM (4.6 to 5.1 bytes per weight).  With an fp64 division per weight
+// the VALU bound it instead: 8192 x 2048 to q4 23.5 us, 14.3 us now (5.3 TB/s).
 //
 // Layout: 4 lanes per 32-weight block, 8 consecutive weights per lane (two
 // 16-byte loads); the 4 lanes of a block are adjacent in a wavefront and
@@ -20,56 +22,71 @@
 namespace qlk {
 namespace {
 
-// fp16 bit pattern nearest to the non-negative finite double q (ties to
-// even significand, subnormals kept, 0x7C00 when it rounds past 65504).
-__device__ inline uint32_t f64_to_f16_bits(double q)
+// Exact value of an fp16 bit pattern with the sign bit clear; 0x7C00 as 2^16,
+// where the next normal would be.
+__device__ inline float f16_value(uint32_t h)
 {
-    const uint64_t u = (uint64_t)__double_as_longlong(q);
-    const int ebits = (int)((u >> 52) & 0x7FF);
-    if (ebits == 0)
-        return 0;  // zero or an fp64 subnormal: far below half the fp16 quantum
-    const int E = ebits - 1023;                       // q in [2^E, 2^(E+1))
-    const uint64_t sig = (u & 0xFFFFFFFFFFFFFull) | (1ull << 52);  // 53 bits
-    if (E >= 16)
-        return 0x7C00;
-    if (E >= -14) {
-        // normal fp16: keep 11 significant bits
-        uint64_t keep = sig >> 42;
-        const uint64_t rem = sig & ((1ull << 42) - 1);
-        const uint64_t half = 1ull << 41;
-        if (rem > half || (rem == half && (keep & 1)))
-            ++keep;
-        int e = E;
-        if (keep == 2048) {
-            keep = 1024;
-            ++e;
-        }
-        if (e >= 16)
-            return 0x7C00;
-        return (uint32_t)(((e + 15) << 10) | (int)(keep - 1024));
-    }
-    // fp16 subnormal range: value / 2^-24 = sig * 2^(E - 28)
-    const int sh = 28 - E;  // >= 43
-    if (sh > 63)
-        return 0;  // below 2^-36, under half a quantum
-    uint64_t keep = sig >> sh;
-    const uint64_t rem = sig & ((1ull << sh) - 1);
-    const uint64_t half = 1ull << (sh - 1);
-    if (rem > half || (rem == half && (keep & 1)))
-        ++keep;
-    return (uint32_t)keep;  // 1024 encodes 2^-14, the smallest normal
+    return h >= 0x7C00u ? 65536.0f : (float)__builtin_bit_cast(_Float16, (uint16_t)h);
 }
 
-// Exact value of a finite fp16 bit pattern with the sign bit clear.
-__device__ inline double f16_bits_to_f64(uint32_t h)
+// fp16 bit pattern nearest to amax / Q for a finite fp32 amax >= 0 (ties to
+// even, subnormals kept, 0x7C00 when it rounds past 65504), exact: the fp32
+// product with 1 / Q rounds to the right pattern or to a neighbour, and the
+// midpoints to both neighbours times Q (12 and 7 significant bits) are exact
+// in fp32, to be compared with amax itself.
+template <int Q>
+__device__ inline uint32_t scale_bits(float amax)
 {
-    const uint32_t ex = (h >> 10) & 0x1F;
-    const uint32_t man = h & 0x3FF;
-    if (ex == 0)
-        return (double)man * 0x1p-24;
-    const uint64_t bits = ((uint64_t)(ex - 15 + 1023) << 52) | ((uint64_t)man << 42);
-    return __longlong_as_double((long long)bits);
+    const uint32_t h =
+        __builtin_bit_cast(uint16_t, (_Float16)(amax * (1.0f / (float)Q)));  // overflow: 0x7C00
+    const float v = f16_value(h);
+    const float hi = (v + f16_value(h + 1)) * (0.5f * Q);
+    const float lo = (v + f16_value(h - 1)) * (0.5f * Q);
+    const bool odd = h & 1;
+    if (h < 0x7C00u && (amax > hi || (amax == hi && odd)))
+        return h + 1;
+    if (h > 0 && (amax < lo || (amax == lo && odd)))
+        return h - 1;
+    return h;
 }
+
+// The integer nearest to w / s, ties to even, clamped to [-Q, Q], for s > 0 an
+// fp16 value, |w| <= (Q + 1) s and inv within 2 ulp of 1 / s; exact.
+//   n = rint(w * inv) is within one of it (the product is off by less than
+// 2^-21 of a quotient below 2^8).  The remainder w - n s is exact in fp32:
+// for n = 0 it is w; otherwise |w| > s / 4, so both w and n s (18 significant
+// bits) are multiples of u = min(ulp(w), ulp(s)) >= 2^-25 of the power of two
+// at or below s, and the remainder, below s, is a multiple of u small enough
+// for 24 bits wherever it decides (|r| <= s / 2 + 2^-13 s).  It is compared
+// with s / 2, exact as well: above, n moves towards w; at the tie, n moves if
+// it is odd.
+__device__ inline int nearest_code(float w, float s, float inv, float half_s, int Q)
+{
+    const float n = __builtin_rintf(w * inv);
+    const float r = __builtin_fmaf(-n, s, w);
+    const float a = __builtin_fabsf(r);
+    int c = (int)n;
+    if (a > half_s || (a == half_s && (c & 1)))
+        c += r > 0.0f ? 1 : -1;
+    c = c > Q ? Q : c;
+    return c < -Q ? -Q : c;
+}
+
+// The same for a bf16 x and Q = 127.  x has 8 significant bits, so a correctly
+// rounded fp32 quotient decides every rounding as the exact one would (a
+// non-half-integer quotient lies at least 2^-9 of its size from every
+// half-integer, and exact half-integers are representable); one Newton step
+// on x * inv with its exact remainder gives that quotient at every
+// half-integer, and within an ulp elsewhere.
+__device__ inline int nearest_code_bf16(float x, float s, float inv)
+{
+    const float q = x * inv;
+    const float r = __builtin_fmaf(__builtin_fmaf(-q, s, x), inv, q);
+    return (int)__builtin_amdgcn_fmed3f(__builtin_rintf(r), -127.0f, 127.0f);
+}
+
+// 1 / s for an fp16 s > 0 (2^-24 to 65504, so neither overflows nor underflows)
+__device__ inline float inverse(float s) { return __builtin_amdgcn_rcpf(s); }
 
 template <int FMT>
 __global__ __launch_bounds__(256) void quantize_kernel(const float *__restrict__ W,
@@ -120,27 +137,19 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float *__restrict__
         return;
     }
 
-    const double a = (double)__uint_as_float(amax);
-    const uint32_t sbits = f64_to_f16_bits(a / (double)Q);
+    const uint32_t sbits = scale_bits<Q>(__uint_as_float(amax));
     if (sbits == 0x7C00) {
         if (part == 0)
             *status = QL_ERR_RANGE;
         return;
     }
-    const double s = f16_bits_to_f64(sbits);
+    const float s = f16_value(sbits);
+    const float inv = inverse(s), half_s = 0.5f * s;
 
     int c[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        int v = 0;
-        if (s != 0.0) {
-            double r = rint((double)__uint_as_float(wb[j]) / s);
-            r = r > (double)Q ? (double)Q : r;
-            r = r < -(double)Q ? -(double)Q : r;
-            v = (int)r;
-        }
-        c[j] = v;
-    }
+    for (int j = 0; j < 8; ++j)
+        c[j] = sbits == 0 ? 0 : nearest_code(__uint_as_float(wb[j]), s, inv, half_s, Q);
 
     if (part == 0)
         scales[blk] = (uint16_t)sbits;
@@ -161,17 +170,18 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float *__restrict__
     }
 }
 
-// Per-token activation quantizer of the W8A8 path: one workgroup per row of
-// X.  Scale = fp16 nearest to (row absmax) / 127 and code = nearest integer
-// to x / scale clamped to [-127, 127] (the weight rules with the whole row as
-// the block).  bf16 activations have 8 significant bits, so a correctly
-// rounded fp32 quotient already decides every rounding as the exact one
-// would (a non-half-integer quotient lies at least 2^-9 of its size from
-// every half-integer, the fp32 error is below 2^-24 of it, and exact
-// half-integers are representable); fp32 activations use fp64 as the
-// weight quantizer does.  A row holding a NaN or Inf, or whose scale would
-// overflow fp16, gets the NaN scale 0x7E00 and zero codes, so its outputs
-// come out NaN.
+// Per-token activation quantizer of the W8A8 path.  Scale = fp16 nearest to
+// (row absmax) / 127 and code = nearest integer to x / scale clamped to
+// [-127, 127] (the weight rules with the whole row as the block).  A row
+// holding a NaN or Inf, or whose scale would overflow fp16, gets the NaN scale
+// 0x7E00 and zero codes, so its outputs come out NaN.
+//
+// Bound: HBM at many rows, the load latency at few.  A workgroup per row
+// keeps up to R groups of 8 columns per thread in registers between the
+// maximum and the codes, so rows up to 8192 columns are read once.  (A
+// wavefront per row was slower: 1290 x 1536 6.6 us.)  bf16, against two reads,
+// an fp64 scale and a division per element: 1290 x 1536 4.5 -> 3.9 us, 1290 x
+// 6144 9.4 -> 7.0 us (3.4 TB/s), 2048 x 8192 15.8 -> 12.3 us (4.1 TB/s).
 template <bool BF16>
 __device__ inline void load8(const void *X, int64_t e, uint32_t (&v)[8])
 {
@@ -191,74 +201,98 @@ __device__ inline void load8(const void *X, int64_t e, uint32_t (&v)[8])
     }
 }
 
-template <bool BF16>
+template <bool BF16, int R>
 __global__ __launch_bounds__(256) void act_quant_kernel(const void *__restrict__ X, int64_t K,
                                                         int8_t *__restrict__ q,
                                                         uint16_t *__restrict__ sx)
 {
-    __shared__ uint32_t wmax[4];
-    const int64_t row = (int64_t)blockIdx.x * K;
-    const int tid = threadIdx.x;
+    constexpr int T = 256;
+    __shared__ uint32_t wmax[T / 64];
+    const int64_t m = blockIdx.x, row = m * K;
+    const int t = threadIdx.x;
     const int64_t groups = K / 8;
+    uint32_t v[R][8];
     uint32_t amax = 0;  // |x| bit patterns compare like the values; NaN/Inf >= 0x7F800000
-    for (int64_t g = tid; g < groups; g += 256) {
-        uint32_t v[8];
-        load8<BF16>(X, row + 8 * g, v);
+    auto max8 = [&](const uint32_t(&x)[8]) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const uint32_t a = v[j] & 0x7FFFFFFFu;
+            const uint32_t a = x[j] & 0x7FFFFFFFu;
             amax = a > amax ? a : amax;
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int64_t g = t + (int64_t)i * T;
+        if (g < groups) {
+            load8<BF16>(X, row + 8 * g, v[i]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                v[i][j] = 0;
         }
     }
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = (uint32_t)__shfl_xor((int)amax, o);
-        amax = t > amax ? t : amax;
+    for (int i = 0; i < R; ++i)
+        max8(v[i]);
+    for (int64_t g = t + (int64_t)R * T; g < groups; g += T) {
+        uint32_t x[8];
+        load8<BF16>(X, row + 8 * g, x);
+        max8(x);
     }
-    if ((tid & 63) == 0)
-        wmax[tid >> 6] = amax;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t w = (uint32_t)__shfl_xor((int)amax, o);
+        amax = w > amax ? w : amax;
+    }
+    if ((t & 63) == 0)
+        wmax[t >> 6] = amax;
     __syncthreads();
     amax = wmax[0];
 #pragma unroll
-    for (int w = 1; w < 4; ++w)
+    for (int w = 1; w < T / 64; ++w)
         amax = wmax[w] > amax ? wmax[w] : amax;
 
     uint32_t sbits = 0x7C00;
     if (amax < 0x7F800000u)
-        sbits = f64_to_f16_bits((double)__uint_as_float(amax) / 127.0);
-    const bool bad = sbits == 0x7C00;
-    if (tid == 0)
-        sx[blockIdx.x] = (uint16_t)(bad ? 0x7E00 : sbits);
-    const double sd = f16_bits_to_f64(sbits);
-    const float sf = (float)sd;  // exact: an fp16 value
-    for (int64_t g = tid; g < groups; g += 256) {
-        uint32_t v[8];
-        load8<BF16>(X, row + 8 * g, v);
-        int c[8];
+        sbits = scale_bits<127>(__uint_as_float(amax));
+    const bool zero = sbits == 0x7C00 || sbits == 0;
+    if (t == 0)
+        sx[m] = (uint16_t)(sbits == 0x7C00 ? 0x7E00 : sbits);
+    const float s = zero ? 1.0f : f16_value(sbits);
+    const float inv = inverse(s), half_s = 0.5f * s;
+    auto put8 = [&](int64_t g, const uint32_t(&x)[8]) {
+        uint32_t c[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            int r = 0;
-            if (!bad && sbits != 0) {
-                const float x = __uint_as_float(v[j]);
-                float t;
-                if constexpr (BF16)
-                    t = rintf(__fdiv_rn(x, sf));
-                else
-                    t = (float)rint((double)x / sd);
-                t = t > 127.0f ? 127.0f : t;
-                t = t < -127.0f ? -127.0f : t;
-                r = (int)t;
-            }
-            c[j] = r;
-        }
-        uint32_t lo = 0, hi = 0;
+        for (int j = 0; j < 8; ++j)
+            c[j] = zero ? 0u
+                        : (uint32_t)(BF16 ? nearest_code_bf16(__uint_as_float(x[j]), s, inv)
+                                          : nearest_code(__uint_as_float(x[j]), s, inv, half_s,
+                                                         127)) & 0xFFu;
+        *reinterpret_cast<uint2 *>(q + row + 8 * g) =
+            make_uint2(c[0] | c[1] << 8 | c[2] << 16 | c[3] << 24,
+                       c[4] | c[5] << 8 | c[6] << 16 | c[7] << 24);
+    };
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            lo |= (uint32_t)(c[j] & 0xFF) << (8 * j);
-            hi |= (uint32_t)(c[j + 4] & 0xFF) << (8 * j);
-        }
-        *reinterpret_cast<uint2 *>(q + row + 8 * g) = make_uint2(lo, hi);
+    for (int i = 0; i < R; ++i)
+        if (t + (int64_t)i * T < groups)
+            put8(t + (int64_t)i * T, v[i]);
+    for (int64_t g = t + (int64_t)R * T; g < groups; g += T) {
+        uint32_t x[8];
+        load8<BF16>(X, row + 8 * g, x);
+        put8(g, x);
     }
+}
+
+template <bool BF16>
+void act_quant(const void *X, int64_t M, int64_t K, int8_t *q, uint16_t *sx, hipStream_t s)
+{
+    const dim3 grid((unsigned)M), block(256);
+    if (K <= 2048)
+        hipLaunchKernelGGL((act_quant_kernel<BF16, 1>), grid, block, 0, s, X, K, q, sx);
+    else if (K <= 4096)
+        hipLaunchKernelGGL((act_quant_kernel<BF16, 2>), grid, block, 0, s, X, K, q, sx);
+    else
+        hipLaunchKernelGGL((act_quant_kernel<BF16, 4>), grid, block, 0, s, X, K, q, sx);
 }
 
 }  // namespace
@@ -267,11 +301,9 @@ hipError_t launch_act_quant(const void *X, bool bf16, int64_t M, int64_t K, int8
                             uint16_t *sx, hipStream_t stream)
 {
     if (bf16)
-        hipLaunchKernelGGL(act_quant_kernel<true>, dim3((unsigned)M), dim3(256), 0, stream, X, K,
-                           q, sx);
+        act_quant<true>(X, M, K, q, sx, stream);
     else
-        hipLaunchKernelGGL(act_quant_kernel<false>, dim3((unsigned)M), dim3(256), 0, stream, X,
-                           K, q, sx);
+        act_quant<false>(X, M, K, q, sx, stream);
     return hipGetLastError();
 }
 
