@@ -142,7 +142,7 @@ hipError_t launch_qgemm_mid(int fmt, const GroupArgs &args, hipStream_t stream);
 // alignment; or fp16 weights, with X and xexp those of launch_xprep.
 // LinDesc::psteps holds the layer's shape (a KgShape), and tiles_m, tiles_n
 // count its tiles (kg_tile_shape; {0, 0}: the launch has no such shape).
-enum KgShape { KG_R1W1, KG_R1W2, KG_R1W4, KG_R2W2, KG_R2W4, KG_SHAPES };
+enum KgShape { KG_R1W1, KG_R1W2, KG_R1W4, KG_R2W2, KG_R2W4, KG_R1C16, KG_SHAPES };
 struct KgTile {
     int m, n;
 };

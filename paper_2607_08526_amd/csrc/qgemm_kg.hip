@@ -13,9 +13,11 @@
 // TM x TN output tile, each its share of every stage's k, and their sums are
 // added through LDS in group order at the end.
 //
-// Shapes (per layer, chosen by kg_plan): TM = 32 MI rows (MI = 1 up to 32
-// rows, 2 above), and WN x KG = 4 x 4, 2 x 8 or 1 x 16, i.e. TN = 128, 64 or
-// 32 columns; each wavefront owns 32 MI x 32 outputs.  Sixteen wavefronts
+// Shapes (per layer, chosen by kg_plan): TM = 32 or 64 rows, and WN x KG = 4 x
+// 4, 2 x 8 or 1 x 16, i.e. TN = 128, 64 or 32 columns; each wavefront owns
+// TM x 32 outputs.  One more has 16 columns (16 x 16 x 32 MFMAs), for long
+// reductions over few rows: twice the workgroups (a d = 1536 int8 block at 27
+// rows 18.5 -> 14.9 us with FFN-down in it).  Sixteen wavefronts
 // because one wavefront issues a VALU instruction every ~5 cycles at best
 // while a SIMD takes one every 2 to 4 from several.
 //
@@ -52,13 +54,14 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int WAVES = 16, NT = 64 * WAVES;
 
-template <int FMT_, bool XF32_, int XR_, int WN_, int BPW_, int NST_>
+template <int FMT_, bool XF32_, int XR_, int WN_, int BPW_, int CW_ = 32>
 struct KgGeo {
-    static constexpr int FMT = FMT_, XR = XR_, WN = WN_, BPW = BPW_, NST = NST_;
+    static constexpr int FMT = FMT_, XR = XR_, WN = WN_, BPW = BPW_;
+    static constexpr int CW = CW_;                     // columns per wavefront
     static constexpr bool XF32 = XF32_;
     static constexpr int MI = XR > 32 ? XR / 32 : 1;   // MFMA row blocks
     static constexpr int KG = WAVES / WN;
-    static constexpr int TM = XR, TN = 32 * WN;
+    static constexpr int TM = XR, TN = CW * WN;
     static constexpr int EB = KG * BPW;                // 32-k blocks per stage
     static constexpr int XRB = EB * (XF32 ? 128 : 64), XCH = XRB / 16;  // activation bytes,
                                                                         // chunks per row
@@ -71,8 +74,13 @@ struct KgGeo {
     static constexpr int XU = XBYTES / 1024, CU = CBYTES / 1024, SU = (SBYTES + 1023) / 1024;
     static constexpr int UNITS = XU + CU + SU, LOADS = (UNITS + WAVES - 1) / WAVES;
     static constexpr int RED = KG * TM * TN * 4;       // the groups' sums at the end
-    static constexpr int SLOT = XBYTES + CBYTES + SU * 1024, RING = NST * SLOT;
+    // two stages ahead (deeper rings were no faster, and a second workgroup
+    // fits a CU beside a small one)
+    static constexpr int SLOT = XBYTES + CBYTES + SU * 1024;
+    static constexpr int NST = std::min(3, 160 * 1024 / SLOT), RING = NST * SLOT;
+    static_assert(NST >= 2, "a stage ahead");
     static constexpr int LDS = RING > RED ? RING : RED;
+    static_assert(CW == 32 || (CW == 16 && !XF32 && FMT != QL_FMT_F16 && XR <= 32), "forms built");
     static_assert(EB % 8 == 0 && XBYTES % 1024 == 0 && CBYTES % 1024 == 0, "whole loads");
     static_assert(LDS <= 160 * 1024, "LDS of a CU");
 };
@@ -167,7 +175,7 @@ __device__ inline void kg_tile(const LinDesc &d, int tile, uint8_t *ring)
     const int crow = Q4 ? K / 2 : F16 ? 2 * K : K;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kg = wave / G::WN, wn = (wave % G::WN) * 32;
+    const int kg = wave / G::WN, wn = (wave % G::WN) * G::CW;
 
     // this wavefront's loads: per unit a base, a per-lane offset within the
     // stage's first columns, and the bytes a stage advances.  Rows past M and
@@ -226,6 +234,15 @@ __device__ inline void kg_tile(const LinDesc &d, int tile, uint8_t *ring)
 #pragma unroll
     for (int i = 0; i < MI; ++i)
         acc[i] = f32x16{};
+    // 16 columns: 16 x 16 tiles, register r of lane l holding row 16 i + 4 (l /
+    // 16) + r, column l % 16
+    constexpr bool C16 = G::CW == 16;
+    constexpr int MI16 = (G::XR + 15) / 16;
+    f32x4 acc16[MI16];
+#pragma unroll
+    for (int i = 0; i < MI16; ++i)
+        acc16[i] = f32x4{};
+    const int l16 = lane & 15, lg = lane >> 4;
 
     auto step = [&](int it, auto refill) {
         constexpr bool REFILL = decltype(refill)::value;
@@ -245,10 +262,42 @@ __device__ inline void kg_tile(const LinDesc &d, int tile, uint8_t *ring)
             if constexpr (!REFILL)
                 if (it * G::EB + b >= nb)
                     continue;
-            const int wr = wn + l32;
+            if constexpr (REFILL)
+#pragma unroll
+                for (int q = u; q < G::LOADS; q += G::BPW)
+                    issue(it + G::NST - 1, q);
+            const int wr = wn + (C16 ? l16 : l32);
             const uint8_t *const wrow = st + G::XBYTES + wr * G::CRB;
             float s = 1.0f;
             u32x4 wv[2];
+            if constexpr (C16) {
+                const uint32_t sw = *reinterpret_cast<const uint16_t *>(
+                    st + G::XBYTES + G::CBYTES + ((b / 8) * G::TN + wr) * 16 + (b % 8) * 2);
+                s = f16_value(sw) * (Q4 ? 0.0625f : 1.0f);  // exact
+                dma_pin(s);
+                // the lane's 8 codes of the block: k = 32 b + 8 (lane / 16) + e
+                if constexpr (Q4) {
+                    wv[0] = cvt_q4(*reinterpret_cast<const uint32_t *>(
+                        wrow + (b ^ cswz<G::CCH>(wr)) * 16 + 4 * lg));
+                } else {
+                    const u32x2 c = *reinterpret_cast<const u32x2 *>(
+                        wrow + ((2 * b + (lg >> 1)) ^ cswz<G::CCH>(wr)) * 16 + 8 * (lg & 1));
+                    wv[0] = cvt_int8(c[0], c[1]);
+                }
+#pragma unroll
+                for (int i = 0; i < MI16; ++i) {
+                    const int xr = 16 * i + (l16 & (G::XR < 16 ? G::XR - 1 : 15));
+                    const u32x4 x = *reinterpret_cast<const u32x4 *>(
+                        st + xr * G::XRB + ((4 * b + lg) ^ xswz(xr)) * 16);
+                    const f32x4 p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, wv[0]), f32x4{},
+                        0, 0, 0);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        acc16[i][r] = __builtin_fmaf(s, p[r], acc16[i][r]);
+                }
+                continue;
+            }
             if constexpr (F16) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
@@ -272,10 +321,6 @@ __device__ inline void kg_tile(const LinDesc &d, int tile, uint8_t *ring)
                     wv[1] = cvt_int8(c[2], c[3]);
                 }
             }
-            if constexpr (REFILL)
-#pragma unroll
-                for (int q = u; q < G::LOADS; q += G::BPW)
-                    issue(it + G::NST - 1, q);
             f32x16 p[MI];
 #pragma unroll
             for (int i = 0; i < MI; ++i) {
@@ -334,8 +379,16 @@ __device__ inline void kg_tile(const LinDesc &d, int tile, uint8_t *ring)
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     float *const red = reinterpret_cast<float *>(ring);
+    if constexpr (C16) {
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+        for (int i = 0; i < MI16; ++i)
+            if (16 * i + 4 * lg < G::TM)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    red[(kg * G::TM + 16 * i + 4 * lg + r) * G::TN + wn + l16] = acc16[i][r];
+    }
+#pragma unroll
+    for (int i = 0; i < MI && !C16; ++i)
 #pragma unroll
         for (int r = 0; r < AR; ++r)
             red[(kg * G::TM + 32 * i + 8 * (r >> 2) + 4 * g + (r & 3)) * G::TN + wn + l32] =
@@ -377,34 +430,36 @@ struct KgShapes {
     static constexpr int XR1 = XR < 32 ? XR : 32;
     // up to 8 rows a stage is small: twice the k per stage, half the barriers
     static constexpr bool FEW = XR <= 8;
-    using R1W4 = KgGeo<FMT, false, XR1, 4, FEW ? 4 : 2, FEW && I8 ? 2 : 3>;
-    using R1W2 = KgGeo<FMT, false, XR1, 2, FEW ? 2 : 1, 3>;
-    using R1W1 = KgGeo<FMT, false, XR1, 1, FEW ? 2 : 1, 3>;
-    using R2W4 = KgGeo<FMT, false, 64, 4, 2, I8 ? 2 : 3>;
-    using R2W2 = KgGeo<FMT, false, 64, 2, 1, 3>;
-    static constexpr bool R2 = XR > 32;
-    static constexpr bool R2_W4 = R2;
+    using R1W4 = KgGeo<FMT, false, XR1, 4, FEW ? 4 : 2>;
+    using R1W2 = KgGeo<FMT, false, XR1, 2, FEW ? 2 : 1>;
+    using R1W1 = KgGeo<FMT, false, XR1, 1, FEW ? 2 : 1>;
+    using R1C16 = KgGeo<FMT, false, XR1, 1, FEW ? 2 : 1, 16>;
+    using R2W4 = KgGeo<FMT, false, 64, 4, 2>;
+    using R2W2 = KgGeo<FMT, false, 64, 2, 1>;
+    static constexpr bool R2 = XR > 32, R2_W4 = R2, C16 = true;
 };
 // fp16 weights (X the fp16 copy of the pre-pass)
 template <int XR>
 struct KgShapes<QL_FMT_F16, XR> {
-    using R1W4 = KgGeo<QL_FMT_F16, false, 32, 4, 2, 2>;
-    using R1W2 = KgGeo<QL_FMT_F16, false, 32, 2, 1, 3>;
-    using R1W1 = KgGeo<QL_FMT_F16, false, 32, 1, 1, 2>;
-    using R2W2 = KgGeo<QL_FMT_F16, false, 64, 2, 1, 2>;
+    using R1W4 = KgGeo<QL_FMT_F16, false, 32, 4, 2>;
+    using R1W2 = KgGeo<QL_FMT_F16, false, 32, 2, 1>;
+    using R1W1 = KgGeo<QL_FMT_F16, false, 32, 1, 1>;
+    using R2W2 = KgGeo<QL_FMT_F16, false, 64, 2, 1>;
     using R2W4 = R2W2;
-    static constexpr bool R2 = true, R2_W4 = false;
+    using R1C16 = R1W1;
+    static constexpr bool R2 = true, R2_W4 = false, C16 = false;
 };
 // fp32 X: row tiles of 16 and 32 (a stage of 64 fp32 rows leaves no room for
 // a second one)
 template <int FMT>
 struct KgShapesF32 {
-    using R1W4 = KgGeo<FMT, true, 32, 4, 2, FMT == QL_FMT_INT8 ? 2 : 3>;
-    using R1W2 = KgGeo<FMT, true, 32, 2, 1, 3>;
-    using R1W1 = KgGeo<FMT, true, 16, 1, 1, 3>;
-    using R2W2 = KgGeo<FMT, true, 16, 2, 1, 3>;
+    using R1W4 = KgGeo<FMT, true, 32, 4, 2>;
+    using R1W2 = KgGeo<FMT, true, 32, 2, 1>;
+    using R1W1 = KgGeo<FMT, true, 16, 1, 1>;
+    using R2W2 = KgGeo<FMT, true, 16, 2, 1>;
     using R2W4 = R2W2;
-    static constexpr bool R2 = true, R2_W4 = false;
+    using R1C16 = R1W1;
+    static constexpr bool R2 = true, R2_W4 = false, C16 = false;
 };
 
 template <class S>
@@ -415,6 +470,8 @@ constexpr int kg_lds()
         v = std::max(v, S::R2W2::LDS);
     if constexpr (S::R2_W4)
         v = std::max(v, S::R2W4::LDS);
+    if constexpr (S::C16)
+        v = std::max(v, S::R1C16::LDS);
     return v;
 }
 
@@ -442,6 +499,10 @@ __global__ __launch_bounds__(NT, 4) void qgemm_kg_kernel(const GroupArgs args)
         break;
     case KG_R1W4:
         kg_tile<typename S::R1W4>(d, tile, ring);
+        break;
+    case KG_R1C16:
+        if constexpr (S::C16)
+            kg_tile<typename S::R1C16>(d, tile, ring);
         break;
     case KG_R2W2:
         if constexpr (S::R2)
@@ -479,6 +540,7 @@ KgTile tile_of(int shape)
     case KG_R1W1: return KgTile{S::R1W1::TM, S::R1W1::TN};
     case KG_R1W2: return KgTile{S::R1W2::TM, S::R1W2::TN};
     case KG_R1W4: return KgTile{S::R1W4::TM, S::R1W4::TN};
+    case KG_R1C16: return S::C16 ? KgTile{S::R1C16::TM, S::R1C16::TN} : KgTile{0, 0};
     case KG_R2W2: return S::R2 ? KgTile{S::R2W2::TM, S::R2W2::TN} : KgTile{0, 0};
     default: return S::R2_W4 ? KgTile{S::R2W4::TM, S::R2W4::TN} : KgTile{0, 0};
     }

@@ -827,13 +827,13 @@ constexpr int64_t KG_MIN_M = 4, KG_MAX_M = 2048;
 
 // us per 256 k of a workgroup of each shape, measured on full launches, by
 // kind: q4, int8, fp16 weights; q4 and int8 with fp32 X.  At 16 bf16 rows and
-// below, KG_FEW of it (fewer activation bytes).
-constexpr double KG_RATE[5][KG_SHAPES] = {{0.35, 0.55, 1.00, 0.85, 1.43},
-                                          {0.43, 0.70, 1.00, 0.85, 1.40},
-                                          {0.81, 0.88, 1.70, 1.35, 0.0},
-                                          {0.60, 1.17, 2.23, 1.15, 0.0},
-                                          {0.62, 1.17, 2.20, 1.10, 0.0}};
-constexpr double KG_FEW = 0.75;
+// below, KG_FEW of it (fewer activation bytes; KG_FEW_C16 with 16 columns).
+constexpr double KG_RATE[5][KG_SHAPES] = {{0.35, 0.55, 1.00, 0.85, 1.43, 0.33},
+                                          {0.48, 0.80, 1.15, 0.85, 1.40, 0.39},
+                                          {0.81, 0.88, 1.70, 1.35, 0.0, 0.0},
+                                          {0.60, 1.17, 2.23, 1.15, 0.0, 0.0},
+                                          {0.62, 1.17, 2.20, 1.10, 0.0, 0.0}};
+constexpr double KG_FEW = 0.75, KG_FEW_C16 = 0.85;
 // us: a workgroup's start, sums and stores; the launch; the pre-pass launch of
 // fp16 weights
 constexpr double KG_BASE = 3.0, KG_LAUNCH = 1.2, KG_PREPASS = 4.0;
@@ -846,7 +846,7 @@ KgPlan kg_plan(int fmt, const ql_linear_ep *const *ls, int n)
         maxM = std::max(maxM, ls[i]->lin.M);
     const bool xf32 = ls[0]->lin.xdt == QL_DT_F32;
     const int shapes = KG_SHAPES;
-    const double few = maxM <= 16 && fmt != QL_FMT_F16 && !xf32 ? KG_FEW : 1.0;
+    const bool few = maxM <= 16 && fmt != QL_FMT_F16 && !xf32;
     const double *const rate =
         KG_RATE[fmt == QL_FMT_F16 ? 2 : (xf32 ? 3 : 0) + (fmt == QL_FMT_INT8 ? 1 : 0)];
     const double launch = KG_LAUNCH + (fmt == QL_FMT_F16 ? KG_PREPASS : 0.0);
@@ -855,7 +855,8 @@ KgPlan kg_plan(int fmt, const ql_linear_ep *const *ls, int n)
         for (int s = 0; s < shapes; ++s) {
             const ql_linear &l = ls[i]->lin;
             const KgTile kt = kg_tile_shape(fmt, xf32, maxM, s);
-            t[i][s] = kt.m ? KG_BASE + (double)(l.K / 256) * rate[s] * few : 1e30;
+            const double r = rate[s] * (!few ? 1.0 : s == KG_R1C16 ? KG_FEW_C16 : KG_FEW);
+            t[i][s] = kt.m ? KG_BASE + (double)(l.K / 256) * r : 1e30;
             w[i][s] = kt.m ? (double)((l.M + kt.m - 1) / kt.m * ((l.N + kt.n - 1) / kt.n)) : 1.0;
         }
     KgPlan best{};

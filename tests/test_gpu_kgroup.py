@@ -37,7 +37,7 @@ def run(gpu, fmt, X, codes, scales, N, **ep):
 # rows around every staging size and row tile, columns around 32, 64 and 128
 # and not a multiple of 4, one stage and a half-filled last stage (K = 256,
 # 768, 1280), long K
-@pytest.mark.parametrize("M,N,K", [(4, 33, 256), (8, 300, 8192), (9, 65, 768), (16, 129, 1024),
+@pytest.mark.parametrize("M,N,K", [(4, 33, 256), (8, 300, 8192), (9, 65, 768), (24, 1000, 4096), (16, 129, 1024),
                                    (17, 7, 512), (32, 1000, 1280), (33, 31, 256), (64, 130, 768),
                                    (65, 258, 2048), (129, 4100, 512), (257, 96, 1024)])
 @pytest.mark.parametrize("fmt", [O.FMT_Q4, O.FMT_INT8])
