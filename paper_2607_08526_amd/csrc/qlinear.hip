@@ -837,6 +837,9 @@ constexpr double KG_FEW = 0.75, KG_FEW_C16 = 0.85;
 // us: a workgroup's start, sums and stores; the launch; the pre-pass launch of
 // fp16 weights
 constexpr double KG_BASE = 3.0, KG_LAUNCH = 1.2, KG_PREPASS = 4.0;
+// workgroups of 1024 threads: a launch holds fewer than 2^32 threads (very tall
+// matrices, of 2^27 rows at few activation rows, keep the other kernels)
+constexpr double KG_MAX_WGS = 4194303.0;
 
 KgPlan kg_plan(int fmt, const ql_linear_ep *const *ls, int n)
 {
@@ -879,7 +882,7 @@ KgPlan kg_plan(int fmt, const ql_linear_ep *const *ls, int n)
                 work += w[j][c] * t[j][c];
                 wgs += w[j][c];
             }
-            if (!ok)
+            if (!ok || wgs > KG_MAX_WGS)
                 continue;
             p.us = launch +
                    (wgs <= cus ? longest : std::max(longest, work / cus + 0.5 * longest));
@@ -943,7 +946,7 @@ KgChoice kg_choose(int fmt, const ql_linear_ep *const *ord, int n)
         int S[QL_MAX_GROUP], P[QL_MAX_GROUP];
         c.use = c.plan.us < 0.8 * stream_plan(fmt, ds, n, device_cus(), S, P).us;
     } else {
-        c.use = maxM <= skinny_max_m() || c.plan.us < 8.0 + 0.8 * plan_splits(fmt, ds, n).t;
+        c.use = c.plan.us < (maxM <= skinny_max_m() ? 1e30 : 8.0 + 0.8 * plan_splits(fmt, ds, n).t);
     }
     return c;
 }
