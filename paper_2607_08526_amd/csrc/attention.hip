@@ -23,8 +23,11 @@
 //    same key order, and since both operands use it the contraction over
 //    keys is unchanged.  The accumulator of query l % 32 stays in the lanes
 //    that hold its softmax state, so the per-query rescaling is local.
-// Per workgroup: 128 queries (4 wavefronts x 32) of one (b, h); keys in
-// tiles of 64, double-buffered in LDS.  K and V tiles move from global memory
+// Per workgroup: 4 wavefronts of 32 queries of one (b, h); keys in tiles of
+// 64, double-buffered in LDS.  KG = 1: 128 queries, every wavefront over all
+// the keys.  KG = 2: 64 queries and two groups of wavefronts, each with its own
+// buffers and every second tile; group 1 hands its maximum, sum and
+// accumulators over through LDS at the end.  K and V tiles move from global memory
 // to LDS with the direct-to-LDS loads (no registers, no LDS write
 // instructions), both row-major (one key per 128-byte row, 16-byte chunks
 // XOR-swizzled per row against bank conflicts).  The V^T operand is read
@@ -44,10 +47,9 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int DH = 64;             // head dimension
-constexpr int BQ = 128, BKEY = 64;  // queries per workgroup, keys per tile
+constexpr int BKEY = 64;            // keys per tile
 constexpr int THREADS = 256;
 constexpr int KBYTES = BKEY * DH * 2, VBYTES = BKEY * DH * 2;  // one tile, row-major
-constexpr int TLOADS = KBYTES / 16 / THREADS;  // 16-byte loads per thread per tile
 // physical 16-byte chunk = logical ^ swizzle(key row): the K fragment reads
 // (32 rows, one chunk) and the transposing V reads (8 rows, two chunk pairs)
 // spread over the banks
@@ -112,11 +114,17 @@ struct Flag {
 // two LDS buffers each, filled one tile apart: during step j the K buffer
 // of tile j (read in step j - 1) receives tile j + 2 and the V buffer of
 // tile j - 1 receives tile j + 1, so one barrier per step suffices.
+template <int KG>
 __global__ __launch_bounds__(THREADS, 2) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attention_kernel(const AttnArgs a)
 {
-    __shared__ __align__(16) uint8_t lds[2 * KBYTES + 2 * VBYTES];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    constexpr int GT = THREADS / KG, GW = GT / 64;  // threads, wavefronts of a key group
+    constexpr int BQ = 32 * GW;                     // queries of the workgroup
+    constexpr int TLOADS = KBYTES / 16 / GT;        // 16-byte loads per thread per tile
+    __shared__ __align__(16) uint8_t lds[KG * (2 * KBYTES + 2 * VBYTES)];
+    const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / GT);
+    const int group_lds = kg * (2 * KBYTES + 2 * VBYTES);
+    const int tid = (int)threadIdx.x - kg * GT, wave = tid >> 6, lane = tid & 63;
     const int l32 = lane & 31, hf = lane >> 5;
     // workgroup p runs on XCD p % 8; each XCD takes a contiguous range of
     // (sequence, head) pairs with all their query blocks, so each pair's
@@ -129,8 +137,8 @@ void attention_kernel(const AttnArgs a)
     const int bh = L / nq, qblk = L - bh * nq, b = bh / a.H, h = bh - b * a.H;
     const int64_t seq = (int64_t)b * T;  // first row of this sequence
     const int q = qblk * BQ + wave * 32 + l32;  // this lane's query
-    auto kbuf = [&](int i) { return lds + i * KBYTES; };
-    auto vbuf = [&](int i) { return lds + 2 * KBYTES + i * VBYTES; };
+    auto kbuf = [&](int i) { return lds + group_lds + i * KBYTES; };
+    auto vbuf = [&](int i) { return lds + group_lds + 2 * KBYTES + i * VBYTES; };
 
     // the query's B operands: head-dim chunk s, elements 16 s + 8 hf .. + 7
     bf16x8 qb[4];
@@ -144,7 +152,7 @@ void attention_kernel(const AttnArgs a)
     }
 
     // staging: the tile's 512 chunks of 16 bytes (K and V alike), slot
-    // i = j * 256 + t for thread t's load j: key row i / 8, physical chunk
+    // i = j * GT + t for thread t's load j: key row i / 8, physical chunk
     // i % 8, holding logical chunk (i % 8) ^ swizzle(row) of the row.  Offsets
     // are from the tile's first key row (a wave-uniform base); keys at or
     // beyond T repeat key T - 1 in the last tile (their probabilities are set
@@ -155,7 +163,7 @@ void attention_kernel(const AttnArgs a)
     auto offs = [&](int kt, int64_t ld, bool isk, uint32_t (&o)[TLOADS]) {
 #pragma unroll
         for (int j = 0; j < TLOADS; ++j) {
-            const int i = j * THREADS + tid, r = i >> 3;
+            const int i = j * GT + tid, r = i >> 3;
             const int lc = (i & 7) ^ (isk ? kswz(r) : vswz(r));
             const int key = min(kt * BKEY + r, T - 1) - kt * BKEY;
             o[j] = (uint32_t)((key * ld + 8 * lc) * 2);
@@ -175,7 +183,7 @@ void attention_kernel(const AttnArgs a)
         const uint8_t *const t = tbase + kt * tstep;
 #pragma unroll
         for (int j = 0; j < TLOADS; ++j)
-            dma16(t, o[j], lds_addr(buf) + (j * THREADS + wave * 64) * 16);
+            dma16(t, o[j], lds_addr(buf) + (j * GT + wave * 64) * 16);
     };
     auto fetch_k = [&](int kt, uint8_t *buf) { fetch(kt, kbase, ktile, a.ldk, true, kof, buf); };
     auto fetch_v = [&](int kt, uint8_t *buf) { fetch(kt, vbase, vtile, a.ldv, false, vof, buf); };
@@ -261,7 +269,8 @@ void attention_kernel(const AttnArgs a)
         auto valid = [&](int sub, int r) {
             return !TAIL || kt * BKEY + 32 * sub + 8 * (r >> 2) + 4 * hf + (r & 3) < T;
         };
-        const float mc = mrun * c;
+        // (a group of keys whose scores are all -inf adds nothing)
+        const float mc = KG > 1 && mrun == -INFINITY ? 0.0f : mrun * c;
         float ls[4];
         u32x4 pb[2][2];  // P^T operands: [sub][chunk], 8 bf16 each
 #pragma unroll
@@ -297,11 +306,17 @@ void attention_kernel(const AttnArgs a)
             }
     };
 
-    const int nkt = (T + BKEY - 1) / BKEY;
-    fetch_k(0, kbuf(0));
-    fetch_v(0, vbuf(0));
+    // this group's tiles: KG * j + kg for j < nkt; with an odd count group 1's
+    // last one lies past T (loaded as the last tile again, its p set to 0)
+    const int tiles = (T + BKEY - 1) / BKEY, nkt = (tiles + KG - 1) / KG;
+    auto tile_at = [&](int j) { return KG * j + kg; };
+    auto load_at = [&](int j) { return KG == 1 ? j : min(tile_at(j), tiles - 1); };
+    auto fetch_kj = [&](int j, uint8_t *buf) { fetch_k(load_at(j), buf); };
+    auto fetch_vj = [&](int j, uint8_t *buf) { fetch_v(load_at(j), buf); };
+    fetch_kj(0, kbuf(0));
+    fetch_vj(0, vbuf(0));
     if (nkt > 1)
-        fetch_k(1, kbuf(1));
+        fetch_kj(1, kbuf(1));
     // one step: tile kt (of parity ODD: its buffers are known at compile
     // time, so LDS addresses fold into offsets), whose scores are in cur (it
     // is full, and tile kt + 1 exists); the scores of tile kt + 1 go to nxt.
@@ -315,22 +330,23 @@ void attention_kernel(const AttnArgs a)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (kt + 2 < nkt)
-            fetch_k(kt + 2, kbuf(P));
-        fetch_v(kt + 1, vbuf(P ^ 1));
-        tile_max(Flag<false>{}, kt, cur);
+            fetch_kj(kt + 2, kbuf(P));
+        fetch_vj(kt + 1, vbuf(P ^ 1));
+        tile_max(Flag<false>{}, tile_at(kt), cur);
         scores(kbuf(P ^ 1), nxt);
-        tile_pv(Flag<false>{}, kt, cur, vbuf(P));
+        tile_pv(Flag<false>{}, tile_at(kt), cur, vbuf(P));
     };
     auto last = [&](auto oddc, int kt, const f32x16 (&cur)[2]) {
         constexpr int P = decltype(oddc)::value ? 1 : 0;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();  // V of the last tile is in LDS
-        if (nkt * BKEY > T) {
-            tile_max(Flag<true>{}, kt, cur);
-            tile_pv(Flag<true>{}, kt, cur, vbuf(P));
+        const int t = tile_at(kt);
+        if ((KG == 1 ? nkt : t + 1) * BKEY > T) {
+            tile_max(Flag<true>{}, t, cur);
+            tile_pv(Flag<true>{}, t, cur, vbuf(P));
         } else {
-            tile_max(Flag<false>{}, kt, cur);
-            tile_pv(Flag<false>{}, kt, cur, vbuf(P));
+            tile_max(Flag<false>{}, t, cur);
+            tile_pv(Flag<false>{}, t, cur, vbuf(P));
         }
     };
     // two score buffers in turn (no copies between steps)
@@ -348,6 +364,34 @@ void attention_kernel(const AttnArgs a)
         last(Flag<true>{}, kt + 1, sb);
     } else {
         last(Flag<false>{}, kt, sa);
+    }
+
+    if constexpr (KG == 2) {
+        // group 1's state to LDS (over the buffers, which every wavefront has
+        // finished with), [value][lane] per wavefront; group 0 merges it
+        __syncthreads();
+        float *const x = reinterpret_cast<float *>(lds) + wave * 34 * 64 + lane;
+        if (kg == 1) {
+            x[0] = mrun;
+            x[64] = lrun;
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    x[(2 + 16 * t + r) * 64] = oacc[t][r];
+        }
+        __syncthreads();
+        if (kg == 1)
+            return;
+        const float m1 = x[0], m = fmaxf(mrun, m1);
+        const float a0 = mrun == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((mrun - m) * c);
+        const float a1 = m1 == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m1 - m) * c);
+        lrun = a0 * lrun + a1 * x[64];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                oacc[t][r] = a0 * oacc[t][r] + a1 * x[(2 + 16 * t + r) * 64];
     }
 
     // normalize and store: channel 32 t + 8 (r / 4) + 4 hf + r % 4 of query q
@@ -373,10 +417,24 @@ void attention_kernel(const AttnArgs a)
 
 }  // namespace
 
-hipError_t launch_attention(const AttnArgs &a, hipStream_t stream)
+// Two key groups (KG = 2) while the 64-query workgroups fit the GPU at once:
+// each wavefront's chain of tiles is half as long, at twice the staging per
+// query.  Up to one workgroup per CU always from two tiles on, up to two per CU
+// where the chain is long enough to pay for the hand-over.  us per call, KG = 1
+// / KG = 2 (sequences x tokens, heads):
+//   1 x 2048, 8    28.4 / 17.3      1 x 1024, 16   16.8 / 10.9
+//   2 x 107, 16    5.3 / 4.7        2 x 1024, 16   17.7 / 16.4
+// and where KG = 1 stays:
+//   1 x 64, 16     3.7 / 4.6        4 x 300, 16    8.2 / 9.0
+//   2 x 1024, 32   27.2 / 30.5      2 x 645, 24    18.5 / 19.1
+hipError_t launch_attention(const AttnArgs &a, int cus, hipStream_t stream)
 {
-    const dim3 grid((unsigned)((int64_t)(a.T + BQ - 1) / BQ * a.B * a.H));
-    hipLaunchKernelGGL(attention_kernel, grid, dim3(THREADS), 0, stream, a);
+    const int64_t tiles = ((int64_t)a.T + BKEY - 1) / BKEY, pairs = (int64_t)a.B * a.H;
+    const int64_t w1 = ((int64_t)a.T + 127) / 128 * pairs, w2 = ((int64_t)a.T + 63) / 64 * pairs;
+    if (w2 <= cus ? tiles >= 2 : w2 <= 2 * (int64_t)cus && tiles >= 8)
+        hipLaunchKernelGGL(attention_kernel<2>, dim3((unsigned)w2), dim3(THREADS), 0, stream, a);
+    else
+        hipLaunchKernelGGL(attention_kernel<1>, dim3((unsigned)w1), dim3(THREADS), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -108,7 +108,7 @@ struct AttnArgs {
     float scale_log2e;  // scale * log2(e)
     int obf16;
 };
-hipError_t launch_attention(const AttnArgs &a, hipStream_t stream);
+hipError_t launch_attention(const AttnArgs &a, int cus, hipStream_t stream);
 
 // The steering injection alone, in place on h [M][N] fp32 (steer.hip).
 hipError_t launch_steer(float *h, int64_t M, int64_t N, const float *dir, float hnorm,

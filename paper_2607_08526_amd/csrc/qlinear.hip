@@ -1644,7 +1644,7 @@ int qlinear_attention(const uint16_t *q, int64_t ldq, const uint16_t *k, int64_t
     a.H = (int)H;
     a.scale_log2e = (float)((double)scale * 1.4426950408889634);
     a.obf16 = odt == QL_DT_BF16 ? 1 : 0;
-    return launch_attention(a, stream) == hipSuccess ? QL_OK : QL_ERR_HIP;
+    return launch_attention(a, device_cus(), stream) == hipSuccess ? QL_OK : QL_ERR_HIP;
 }
 
 int qlinear_force_path(int path)

@@ -70,6 +70,29 @@ def test_attention_ragged(gpu, orc, B, T, H):
         check(run(gpu, Q, K, V, B, T, H, dh, odt), Or, V, B, T, H, dh, odt == "bf16")
 
 
+# either side of each line of the choice between one and two key groups (256
+# CUs): two tiles; an odd tile count (group 1's last tile lies past T); 252 and
+# 260 workgroups of 64 queries at 4 and 5 tiles; 261 and 513 at 9
+@pytest.mark.parametrize("B,T,H", [(1, 65, 1), (1, 128, 2), (2, 129, 3), (1, 193, 63),
+                                   (1, 300, 52), (1, 513, 29), (1, 513, 57)])
+def test_attention_key_groups(gpu, orc, B, T, H):
+    """Both key groupings, with keys 64 to 127 (all but one of group 1's) at a
+    score of -inf: they take no weight and leave no NaN."""
+    dh = 64
+    rng = np.random.default_rng(9300 + T + H)
+    Q, K, V = (bf16(rng, (B * T, H * dh)) for _ in range(3))
+    check(run(gpu, Q, K, V, B, T, H, dh), orc.attention(Q, K, V, B, T, H, dh), V, B, T, H, dh,
+          False)
+    Q[:, ::dh] = 0x3F80  # 1
+    for b in range(B):
+        K[b * T + 64:b * T + min(T, 128), ::dh] = 0xFF80  # -inf
+    keep = np.concatenate([b * T + np.r_[0:64, min(T, 128):T] for b in range(B)])
+    n = len(keep) // B
+    Og = run(gpu, Q, K, V, B, T, H, dh, "bf16").reshape(B, T, -1)[:, :n].reshape(B * n, -1)
+    Qn = np.concatenate([Q[b * T:b * T + n] for b in range(B)])
+    check(Og, orc.attention(Qn, K[keep], V[keep], B, n, H, dh), V[keep], B, n, H, dh, True)
+
+
 def test_attention_peaked_and_flat(gpu, orc):
     """Large scores (a few keys take nearly all the weight: the running
     maximum moves across tiles) and zero scale (uniform weights: the mean of
