@@ -32,7 +32,9 @@
 // lane / 32, chunk h, element e), then acc += s * partial in fp32.  The codes
 // are converted as signed bytes (q4: nibbles in the high half of a byte, the
 // factor 16 taken out of the scale): exact in bf16 and without the offset
-// term, and its MFMAs, of the unsigned forms.
+// term, and its MFMAs, of the unsigned forms.  With fp32 activations, whose
+// other kernel takes the q4 codes as they are, so does this one: 16 times them
+// would overflow a block's partial sum at 1/16 of the activations.
 //
 // Requirements (checked by the host): K % 256 == 0, K < 2^23, 16-byte
 // aligned X, codes and scales.
@@ -137,6 +139,18 @@ __device__ inline u32x4 cvt_int8(uint32_t w0, uint32_t w1)
 __device__ inline u32x4 cvt_q4(uint32_t w)
 {
     const uint32_t e = (w << 4) & 0xF0F0F0F0u, o = w & 0xF0F0F0F0u;  // even, odd k
+    return u32x4{bf16_pair(sbyte(e, 0), sbyte(o, 0)), bf16_pair(sbyte(e, 1), sbyte(o, 1)),
+                 bf16_pair(sbyte(e, 2), sbyte(o, 2)), bf16_pair(sbyte(e, 3), sbyte(o, 3))};
+}
+
+// the q4 codes themselves (fp32 activations): each nibble to a signed byte as
+// (n ^ 8) - 8, bit 7 of the byte taking the borrow
+__device__ inline u32x4 cvt_q4_plain(uint32_t w)
+{
+    auto bytes = [](uint32_t n) {
+        return (((n & 0x0F0F0F0Fu) ^ 0x88888888u) - 0x08080808u) ^ 0x80808080u;
+    };
+    const uint32_t e = bytes(w), o = bytes(w >> 4);  // even, odd k
     return u32x4{bf16_pair(sbyte(e, 0), sbyte(o, 0)), bf16_pair(sbyte(e, 1), sbyte(o, 1)),
                  bf16_pair(sbyte(e, 2), sbyte(o, 2)), bf16_pair(sbyte(e, 3), sbyte(o, 3))};
 }
@@ -306,14 +320,14 @@ __device__ inline void kg_tile(const LinDesc &d, int tile, uint8_t *ring)
             } else {
                 const uint32_t sw = *reinterpret_cast<const uint16_t *>(
                     st + G::XBYTES + G::CBYTES + ((b / 8) * G::TN + wr) * 16 + (b % 8) * 2);
-                s = f16_value(sw) * (Q4 ? 0.0625f : 1.0f);  // exact
+                s = f16_value(sw) * (Q4 && !G::XF32 ? 0.0625f : 1.0f);  // exact
                 dma_pin(s);
                 // the lane's codes of the block: 16 (int8) or 8 (q4) bytes
                 if constexpr (Q4) {
                     const u32x2 c = *reinterpret_cast<const u32x2 *>(
                         wrow + (b ^ cswz<G::CCH>(wr)) * 16 + 8 * g);
-                    wv[0] = cvt_q4(c[0]);
-                    wv[1] = cvt_q4(c[1]);
+                    wv[0] = G::XF32 ? cvt_q4_plain(c[0]) : cvt_q4(c[0]);
+                    wv[1] = G::XF32 ? cvt_q4_plain(c[1]) : cvt_q4(c[1]);
                 } else {
                     const u32x4 c = *reinterpret_cast<const u32x4 *>(
                         wrow + ((2 * b + g) ^ cswz<G::CCH>(wr)) * 16);

@@ -111,3 +111,28 @@ def test_kgroup_block(gpu, orc, M):
         Y = e[5].cpu().numpy().astype(np.float64)
         assert np.all(np.abs(Y[keep] - ref) <= 1e-5 * top + 2e-6 * np.abs(ref) + 1e-6)
         assert not np.isfinite(Y[~keep]).any()
+
+
+@pytest.mark.parametrize("fmt", [O.FMT_Q4, O.FMT_INT8])
+def test_kgroup_fp32_large_activations(gpu, orc, fmt):
+    """Activations so large that a block's sum of x * c, at most 32 of them,
+    only just stays below the largest fp32 value: finite, and within the bound
+    of test_kgroup_fp32_and_fp16.  (The tiled kernel takes them too.)"""
+    torch, ql = gpu
+    dv = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    M, N, K = 64, 1024, 1024
+    W, X = si.small_case(8600 + fmt, M, N, K, O.DT_F32)
+    codes, scales = orc.quantize(fmt, W)
+    top = 3.4e38 / (32 * (7 if fmt == O.FMT_Q4 else 127))
+    X = (X * (0.95 * top / np.abs(X).max())).astype(np.float32)
+    Wd = orc.dequantize(fmt, codes, scales, N, K)
+    Yr = X.astype(np.float64) @ Wd.T
+    B = (K // 32 + 112) * 2.0 ** -24 * (np.abs(X).astype(np.float64) @ np.abs(Wd).T)
+    outs = [ql.forward(fmt, dv(X), dv(codes), dv(scales.view(np.int16)), N)]
+    with ql.forced_path(ql.PATH_TILED):
+        outs.append(ql.forward(fmt, dv(X), dv(codes), dv(scales.view(np.int16)), N))
+    torch.cuda.synchronize()
+    for Y in outs:
+        Y = Y.cpu().numpy().astype(np.float64)
+        assert np.isfinite(Y).all()
+        assert np.all(np.abs(Y - Yr) <= B)
