@@ -95,6 +95,16 @@ struct W8Args {
     int M, N, K;
     int tiles_m, tiles_n;
 };
+// the kernel (and shape) a product takes, its workgroups and their threads;
+// a launch holds at most W8_MAX_THREADS
+enum W8Kernel { W8_GENERAL, W8_LARGE, W8_MID, W8_SMALL };
+constexpr int64_t W8_MAX_THREADS = ((int64_t)1 << 32) - 1;
+struct W8Plan {
+    W8Kernel kernel;
+    int64_t wgs;
+    int threads;
+};
+W8Plan w8a8_plan(const W8Args &a, int cus);
 hipError_t launch_qgemm_w8a8(const W8Args &a, int cus, hipStream_t stream);
 
 // Fused self-attention (attention.hip), head dimension 64: Q, K, V bf16

@@ -483,14 +483,11 @@ __global__ __launch_bounds__(G::NT, G::OCC) void qgemm_w8a8_pipe_kernel(const W8
 }
 
 template <class G>
-hipError_t launch_pipe(W8Args &b, hipStream_t stream)
+hipError_t launch_pipe(W8Args &b, const W8Plan &p, hipStream_t stream)
 {
-    b.tiles_m = (b.M + G::TM - 1) / G::TM;
-    b.tiles_n = (b.N + G::TN - 1) / G::TN;
-    const int64_t T = (int64_t)b.tiles_m * b.tiles_n;
-    if (T <= 0 || T >= ((int64_t)1 << 31))
-        return hipErrorInvalidValue;
-    hipLaunchKernelGGL(qgemm_w8a8_pipe_kernel<G>, dim3((unsigned)T), dim3(G::NT), 0, stream, b);
+    b.tiles_m = (int)(((int64_t)b.M + G::TM - 1) / G::TM);
+    b.tiles_n = (int)(((int64_t)b.N + G::TN - 1) / G::TN);
+    hipLaunchKernelGGL(qgemm_w8a8_pipe_kernel<G>, dim3((unsigned)p.wgs), dim3(G::NT), 0, stream, b);
     return hipGetLastError();
 }
 
@@ -512,31 +509,52 @@ using PipeSmall = PipeGeo<1, 1, 2, 8, 1, 2, 4>;
 //   2048 x 8192 x 2048   84.3 / 105  / 126      (116)
 //   64 x 4608 x 1536     17.8 / 10.5 / 7.5      (38.7)
 template <class G>
-double pipe_us(const W8Args &a, double per_step, double fixed, int cus)
+void pipe_candidate(const W8Args &a, W8Kernel kernel, double per_step, double fixed, double launch,
+                    int cus, W8Plan &best, double &best_us)
 {
-    const int64_t T = (int64_t)((a.M + G::TM - 1) / G::TM) * ((a.N + G::TN - 1) / G::TN);
-    return (double)((T + cus - 1) / cus) * (a.K / 64 * per_step + fixed);
+    const int64_t T = (((int64_t)a.M + G::TM - 1) / G::TM) * (((int64_t)a.N + G::TN - 1) / G::TN);
+    const double us =
+        (double)((T + cus - 1) / cus) * (a.K / 64 * per_step + fixed) + launch;
+    if (T <= W8_MAX_THREADS / G::NT && us < best_us) {
+        best = W8Plan{kernel, T, G::NT};
+        best_us = us;
+    }
 }
 
 }  // namespace
 
+// The pipelined kernel in its fastest shape by the estimate, where it takes
+// the operands and a shape's launch stays within the threads of a grid (2^30
+// rows of one column tile pass it in all three shapes); else the general
+// kernel.
+W8Plan w8a8_plan(const W8Args &a, int cus)
+{
+    const int64_t tm = ((int64_t)a.M + BM - 1) / BM, tn = ((int64_t)a.N + BN - 1) / BN;
+    W8Plan p{W8_GENERAL, tm * tn, THREADS};
+    if (a.K % 64 == 0 && a.K < (1 << 23) && ((uintptr_t)a.scales & 3) == 0) {
+        double us = 1e300;
+        pipe_candidate<PipeLarge>(a, W8_LARGE, 0.62, 0.0, 4.0, cus, p, us);
+        pipe_candidate<PipeMid>(a, W8_MID, 0.32, 2.8, 2.0, cus, p, us);
+        pipe_candidate<PipeSmall>(a, W8_SMALL, 0.20, 1.9, 2.0, cus, p, us);
+    }
+    return p;
+}
+
 hipError_t launch_qgemm_w8a8(const W8Args &a, int cus, hipStream_t stream)
 {
     W8Args b = a;
-    if (a.K % 64 == 0 && a.K < (1 << 23) && ((uintptr_t)a.scales & 3) == 0) {
-        const double large = pipe_us<PipeLarge>(a, 0.62, 0.0, cus) + 4.0;
-        const double mid = pipe_us<PipeMid>(a, 0.32, 2.8, cus) + 2.0;
-        const double small = pipe_us<PipeSmall>(a, 0.20, 1.9, cus) + 2.0;
-        if (large <= mid && large <= small)
-            return launch_pipe<PipeLarge>(b, stream);
-        return mid <= small ? launch_pipe<PipeMid>(b, stream) : launch_pipe<PipeSmall>(b, stream);
-    }
-    b.tiles_m = (a.M + BM - 1) / BM;
-    b.tiles_n = (a.N + BN - 1) / BN;
-    const int64_t T = (int64_t)b.tiles_m * b.tiles_n;
-    if (T <= 0 || T >= ((int64_t)1 << 31))
+    const W8Plan p = w8a8_plan(a, cus);
+    if (p.wgs <= 0 || p.wgs >= ((int64_t)1 << 31))
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(qgemm_w8a8_kernel, dim3((unsigned)T), dim3(THREADS), 0, stream, b);
+    switch (p.kernel) {
+    case W8_LARGE: return launch_pipe<PipeLarge>(b, p, stream);
+    case W8_MID: return launch_pipe<PipeMid>(b, p, stream);
+    case W8_SMALL: return launch_pipe<PipeSmall>(b, p, stream);
+    default: break;
+    }
+    b.tiles_m = (int)(((int64_t)a.M + BM - 1) / BM);
+    b.tiles_n = (int)(((int64_t)a.N + BN - 1) / BN);
+    hipLaunchKernelGGL(qgemm_w8a8_kernel, dim3((unsigned)p.wgs), dim3(THREADS), 0, stream, b);
     return hipGetLastError();
 }
 

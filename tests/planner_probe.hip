@@ -6,10 +6,11 @@
 //
 //   wide <fmt> <epi> <M> <N1> <K1> [<N2> <K2> ...]  -> plan_splits (large M)
 //   stream <fmt> <M> <N1> <K1> [...]                 -> stream_plan (few rows)
+//   w8a8 <address of the scales> <M> <N> <K>         -> w8a8_plan
 //
 // Output, one line per input: "wide ext S1 ps1 S2 ps2 ..." (layers in the
 // order the library launches them: longest reduction first) or
-// "stream rw kw mx S1 pb1 S2 pb2 ...".
+// "stream rw kw mx S1 pb1 S2 pb2 ..." or "w8a8 kernel workgroups threads".
 #include "../paper_2607_08526_amd/csrc/qlinear.hip"
 
 #include <cstdio>
@@ -25,7 +26,17 @@ int main()
         std::istringstream in(line);
         std::string kind;
         int fmt = 0, epi = 0, M = 0;
-        in >> kind >> fmt;
+        in >> kind;
+        if (kind == "w8a8") {
+            W8Args a{};
+            uintptr_t scales = 0;
+            in >> scales >> a.M >> a.N >> a.K;
+            a.scales = reinterpret_cast<const uint16_t *>(scales);
+            const W8Plan p = w8a8_plan(a, device_cus());
+            std::printf("w8a8 %d %lld %d\n", (int)p.kernel, (long long)p.wgs, p.threads);
+            continue;
+        }
+        in >> fmt;
         if (kind == "wide")
             in >> epi;
         in >> M;

@@ -153,3 +153,21 @@ def test_stream_plans_of_the_documented_workloads(probe):
     assert i8[0] >= 16 and i8[2] == 8, out[0]
     assert q4[0] == 32 and q4[2] == 8, out[1]
     assert i8_32[0] == 32 and i8_32[2] == 32, out[2]
+
+
+def test_w8a8_launches_fit_a_grid(probe):
+    """A launch holds fewer than 2^32 threads: a product whose pipelined shapes
+    all pass that keeps the general kernel, and any other one stays on the
+    fastest shape that fits.  Scales at an odd 2-byte address, and K that is not
+    whole 64-k steps, take the general kernel."""
+    GENERAL, LARGE, MID, SMALL = range(4)
+    cases = [((0, 2 ** 30, 1, 64), GENERAL), ((0, 2 ** 30, 64, 64), GENERAL),
+             ((0, 2 ** 30 - 128, 1, 64), LARGE), ((0, 2 ** 27, 128, 4096), LARGE),
+             ((0, 2048, 8192, 2048), LARGE), ((0, 1290, 1536, 1536), MID),
+             ((0, 64, 4608, 1536), SMALL), ((2, 1290, 1536, 1536), GENERAL),
+             ((0, 1290, 1536, 1504), GENERAL)]
+    out = probe(["w8a8 " + " ".join(map(str, c)) for c, _ in cases])
+    for (c, kernel), t in zip(cases, out):
+        k, wgs, threads = map(int, t[1:])
+        assert k == kernel, (c, t)
+        assert wgs * threads < 2 ** 32, (c, t)
