@@ -473,12 +473,31 @@ StreamPlan stream_plan(int fmt, const LinDesc *ds, int n, int cus, int *S, int *
     // 15-25% slower on the d = 2048 block
     const int mx = M <= 8 ? 8 : M <= 16 ? 16 : 32;
     const double cb = fmt == QL_FMT_INT8 ? 1.0 : 0.5;
-    StreamPlan best{mx, 16, 4, 1, nbmax, 1e30};
+    // the plan of a group with a layer of fewer than 16 blocks, which no
+    // candidate below can cut (8 blocks per wavefront, at least 2 wavefronts):
+    // every layer whole
+    StreamPlan best{mx, 16, 4, 1, nbmax, 0.0};
     double best_t = 1e30;
     int bS[QL_MAX_GROUP], bP[QL_MAX_GROUP];
-    for (int i = 0; i < n; ++i) {
-        bS[i] = 1;
-        bP[i] = ds[i].K / 32;
+    {
+        int stage = 0, ring = 0;
+        const int wave = stream_geo(fmt, mx, best.rw, stage, ring);
+        const int per_cu = std::min(160 * 1024 / (best.kw * wave), 2048 / (64 * best.kw));
+        int64_t wgs = 0;
+        double trips_max = 0.0, total_bytes = 0.0;
+        for (int i = 0; i < n; ++i) {
+            const int nb = ds[i].K / 32, busy = std::min(best.kw, nb / 8);  // wavefronts with work
+            const int64_t wi = (ds[i].N + best.rw - 1) / best.rw;
+            const double bytes = (double)nb * 32 * (mx * 2 + best.rw * cb);
+            bS[i] = 1;
+            bP[i] = nb;
+            wgs += wi;
+            total_bytes += (double)wi * bytes;
+            trips_max = std::max(trips_max,
+                                 std::ceil(bytes / ((double)busy * (ring - 1) * stage)) + 1);
+        }
+        const double rounds = std::ceil((double)wgs / ((double)cus * per_cu));
+        best.us = std::max(rounds * trips_max * RT, total_bytes / STREAM_RATE);
     }
     for (int rw : {8, 16, 32, 64}) {
         int stage = 0, ring = 0;

@@ -6,11 +6,14 @@
 //
 //   wide <fmt> <epi> <M> <N1> <K1> [<N2> <K2> ...]  -> plan_splits (large M)
 //   stream <fmt> <M> <N1> <K1> [...]                 -> stream_plan (few rows)
+//   kg <fmt> <fp32 X> <epi> <M> <N1> <K1> [...]      -> kg_choose
 //   w8a8 <address of the scales> <M> <N> <K>         -> w8a8_plan
 //
 // Output, one line per input: "wide ext S1 ps1 S2 ps2 ..." (layers in the
 // order the library launches them: longest reduction first) or
-// "stream rw kw mx S1 pb1 S2 pb2 ..." or "w8a8 kernel workgroups threads".
+// "stream rw kw mx S1 pb1 S2 pb2 ...", "w8a8 kernel workgroups threads"
+// or "kg use K1 shape1 rows1 columns1 ..." (use 1: the K-group kernel runs;
+// the tile of each layer's shape).
 #include "../paper_2607_08526_amd/csrc/qlinear.hip"
 
 #include <cstdio>
@@ -37,11 +40,42 @@ int main()
             continue;
         }
         in >> fmt;
-        if (kind == "wide")
+        int xf32 = 0;
+        if (kind == "kg")
+            in >> xf32;
+        if (kind == "wide" || kind == "kg")
             in >> epi;
         in >> M;
         LinDesc d[QL_MAX_GROUP]{};
         int n = 0, N, K;
+        if (kind == "kg") {
+            ql_linear_ep l[QL_MAX_GROUP];
+            const ql_linear_ep *o[QL_MAX_GROUP];
+            while (n < QL_MAX_GROUP && in >> N >> K) {
+                l[n] = ql_linear_ep{};
+                l[n].ep = NO_EPILOGUE;
+                if (epi)
+                    l[n].ep.bias = reinterpret_cast<const float *>(16);
+                l[n].lin.fmt = fmt;
+                l[n].lin.xdt = xf32 ? QL_DT_F32 : QL_DT_BF16;
+                l[n].lin.M = M;
+                l[n].lin.N = N;
+                l[n].lin.K = K;
+                o[n] = &l[n];
+                ++n;
+            }
+            std::stable_sort(o, o + n, [](const ql_linear_ep *a, const ql_linear_ep *b) {
+                return a->lin.K > b->lin.K;
+            });
+            const KgChoice c = kg_choose(fmt, o, n);
+            std::printf("kg %d", c.use ? 1 : 0);
+            for (int i = 0; i < n; ++i) {
+                const KgTile t = kg_tile_shape(fmt, xf32 != 0, M, c.plan.shape[i]);
+                std::printf(" %d %d %d %d", (int)o[i]->lin.K, c.plan.shape[i], t.m, t.n);
+            }
+            std::printf("\n");
+            continue;
+        }
         while (n < QL_MAX_GROUP && in >> N >> K) {
             LinDesc &x = d[n++];
             x.M = M;

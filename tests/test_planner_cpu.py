@@ -155,6 +155,31 @@ def test_stream_plans_of_the_documented_workloads(probe):
     assert i8_32[0] == 32 and i8_32[2] == 32, out[2]
 
 
+def kg_choices(probe, calls):
+    """calls: (fmt, fp32 X, epilogue, M, [(N, K), ...]) -> [(use, [(K, shape,
+    tile rows, tile columns), ...])]; use: the K-group kernel runs."""
+    out = probe([f"kg {f} {int(x)} {int(e)} {M} " + " ".join(f"{N} {K}" for N, K in ls)
+                 for f, x, e, M, ls in calls])
+    res = []
+    for t in out:
+        assert t[0] == "kg"
+        v = list(map(int, t[2:]))
+        res.append((int(t[1]), [tuple(v[i:i + 4]) for i in range(0, len(v), 4)]))
+    return res
+
+
+def test_one_stage_layers_at_few_rows(probe):
+    """K = 256 at few rows: the streaming kernel's whole-layer plan (about 4.2
+    us) is ahead of the K-group kernel (about 5), except where the columns fill
+    the GPU several times over."""
+    calls = [(f, 0, 0, M, ls) for f in (Q4, INT8) for M in (5, 8, 16, 32)
+             for ls in ([(893, 256)], [(64, 256)], [(3000, 256)], block(256))]
+    for c, (use, _) in zip(calls, kg_choices(probe, calls)):
+        assert not use, c
+    wide_n = [(INT8, 0, 0, 32, [(8775, 256)]), (Q4, 0, 0, 7, [(7552, 256)] * 3)]
+    assert all(use for use, _ in kg_choices(probe, wide_n))
+
+
 def test_w8a8_launches_fit_a_grid(probe):
     """A launch holds fewer than 2^32 threads: a product whose pipelined shapes
     all pass that keeps the general kernel, and any other one stays on the
