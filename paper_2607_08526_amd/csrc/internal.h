@@ -247,6 +247,8 @@ struct LayerGroup {
 };
 // The GEMV over a group of layers with one row count M (gemv_ok for each).
 hipError_t launch_qgemv(int fmt, const LayerGroup &g, hipStream_t stream);
+// its estimated us for int8 layers at four rows (gemv_ok for each)
+double gemv4_int8_us(const LinDesc *d, int n, int cus);
 hipError_t launch_qgemm_stream(int fmt, const StreamPlan &p, const LayerGroup &g,
                                hipStream_t stream);
 

@@ -283,6 +283,25 @@ void launch_one(const LayerGroup &g, dim3 grid, size_t lds, hipStream_t s)
                            s, g);
 }
 
+// workgroups of a layer: rows per wavefront as the group kernel takes them
+int layer_wgs(const LinDesc &d, int n, int bpl, int rpw)
+{
+    const int r = n > 1 && bpl > 1 && d.K / 32 <= 64 ? 2 * rpw : rpw;
+    return (d.N + WAVES * r - 1) / (WAVES * r);
+}
+
+// whether a launch gives every wavefront two weight rows (one otherwise):
+// while that still leaves two workgroups per CU; q4 at two activation rows
+// keeps one (a d = 2048 block 14.6 -> 13.0 us; int8 at two rows and both
+// formats at three and four measured slower with one)
+bool two_rows(int fmt, const LinDesc *d, int n)
+{
+    int64_t rows = 0;
+    for (int i = 0; i < n; ++i)
+        rows += d[i].N;
+    return !(fmt == QL_FMT_Q4 && d[0].M == 2) && (rows + 2 * WAVES - 1) / (2 * WAVES) >= 512;
+}
+
 template <int FMT, int MM, int RPW>
 hipError_t launch_bpl(const LayerGroup &g0, hipStream_t s)
 {
@@ -297,12 +316,9 @@ hipError_t launch_bpl(const LayerGroup &g0, hipStream_t s)
                                 (FMT == QL_FMT_Q4 ? (size_t)d.M * nb * 4 : 0));
     }
     const int bpl = (nbmax + 63) / 64;
-    // workgroups per layer: rows per wavefront as the group kernel takes them
     g.begin[0] = 0;
-    for (int i = 0; i < g.n; ++i) {
-        const int rpw = g.n > 1 && bpl > 1 && g.d[i].K / 32 <= 64 ? 2 * RPW : RPW;
-        g.begin[i + 1] = g.begin[i] + (g.d[i].N + WAVES * rpw - 1) / (WAVES * rpw);
-    }
+    for (int i = 0; i < g.n; ++i)
+        g.begin[i + 1] = g.begin[i] + layer_wgs(g.d[i], g.n, bpl, RPW);
     const dim3 grid((unsigned)g.begin[g.n]);
     switch (bpl) {
     case 1: launch_one<FMT, MM, RPW, 1>(g, grid, lds, s); break;
@@ -317,15 +333,7 @@ hipError_t launch_bpl(const LayerGroup &g0, hipStream_t s)
 template <int FMT>
 hipError_t launch_fmt(const LayerGroup &g, hipStream_t s)
 {
-    // two weight rows per wavefront while that still leaves two workgroups
-    // per CU, one otherwise; q4 at two activation rows keeps one (a d = 2048
-    // block 14.6 -> 13.0 us; int8 at two rows and both formats at three and
-    // four measured slower with one)
-    int64_t rows = 0;
-    for (int i = 0; i < g.n; ++i)
-        rows += g.d[i].N;
-    const bool two = !(FMT == QL_FMT_Q4 && g.d[0].M == 2) &&
-                     (rows + 2 * WAVES - 1) / (2 * WAVES) >= 512;
+    const bool two = two_rows(FMT, g.d, g.n);
     switch (g.d[0].M) {
     case 1: return two ? launch_bpl<FMT, 1, 2>(g, s) : launch_bpl<FMT, 1, 1>(g, s);
     case 2: return two ? launch_bpl<FMT, 2, 2>(g, s) : launch_bpl<FMT, 2, 1>(g, s);
@@ -340,6 +348,30 @@ hipError_t launch_fmt(const LayerGroup &g, hipStream_t s)
 bool gemv_ok(const LinDesc &d)
 {
     return d.M >= 1 && d.M <= 4 && d.K % 256 == 0 && d.K <= 8192 && (int64_t)d.M * d.K <= XMAX;
+}
+
+// Estimated us of one launch over int8 layers at four rows (the one case where
+// another kernel may be ahead of it): a fixed part, the code bytes and, with
+// two rows per wavefront, the workgroups per CU, by the blocks per lane of the
+// longest layer.  Within 10% of 1106 of 1229 measured single layers and groups
+// (K 256 to 8192, 32 to 27000 weight rows).
+double gemv4_int8_us(const LinDesc *d, int n, int cus)
+{
+    static const double FIT[4][3] = {{4.8, 0.09, 0.56}, {5.3, 0.36, 0.98}, {6.3, 0.06, 1.63},
+                                     {6.2, 0.13, 1.95}};
+    int nbmax = 0, wgs = 0;
+    double mb = 0.0;
+    for (int i = 0; i < n; ++i) {
+        nbmax = std::max(nbmax, d[i].K / 32);
+        mb += (double)d[i].N * d[i].K * 1e-6;
+    }
+    const int bpl = (nbmax + 63) / 64;
+    if (!two_rows(QL_FMT_INT8, d, n))
+        return 3.4 + 0.5 * bpl + 0.28 * mb;
+    for (int i = 0; i < n; ++i)
+        wgs += layer_wgs(d[i], n, bpl, 2);
+    const double *const f = FIT[bpl - 1];
+    return f[0] + f[1] * mb + f[2] * wgs / cus;
 }
 
 hipError_t launch_qgemv(int fmt, const LayerGroup &g, hipStream_t stream)

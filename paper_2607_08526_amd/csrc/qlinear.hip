@@ -900,6 +900,10 @@ KgPlan kg_plan(int fmt, const ql_linear_ep *const *ls, int n)
 //     kernel's (blocks 1.1-1.7 times faster; single layers, which cannot fill
 //     the GPU with whole reductions, mostly stay: 2048 x 8192 at 8 rows 9.0 us
 //     streamed against 11.6);
+//   int8, bf16 X, four rows, where the streaming kernel is not the
+//     alternative: where 1.1 of its estimate (1.25 with K <= 2048, where it is
+//     low) and a margin are under the GEMV's (gemv4_int8_us; a d = 512 block
+//     6.6 us there against 7.5, d = 1024 12.5 against 9.6);
 //   bf16 X, 33 to 64 rows: always (1.3-2.4 times faster than the mid-M kernel);
 //   bf16 X above: where its estimate is under 8 us + 0.8 of the large-M plan's
 //     steps (up to 3 times faster: 768 x 768 at 500 rows 19.4 -> 5.9 us; no
@@ -923,11 +927,15 @@ KgChoice kg_choose(int fmt, const ql_linear_ep *const *ord, int n)
     KgChoice c{};
     c.plan = kg_plan(fmt, ord, n);
     LinDesc ds[QL_MAX_GROUP] = {};
+    int64_t maxK = 0;
+    bool all_gemv = fmt == QL_FMT_INT8;  // the GEMV takes every layer (of four rows)
     for (int i = 0; i < n; ++i) {
         const ql_linear &l = ord[i]->lin;
         ds[i].M = (int)l.M;
         ds[i].N = (int)l.N;
         ds[i].K = (int)l.K;
+        maxK = std::max(maxK, l.K);
+        all_gemv = all_gemv && l.M == 4 && gemv_ok(ds[i]);
         ds[i].ep = to_epilogue(ord[i]->ep);
         ds[i].tiles_m = (int)((l.M + wide_tile_bm() - 1) / wide_tile_bm());
         ds[i].tiles_n = (int)((l.N + wide_tile_bn() - 1) / wide_tile_bn());
@@ -942,6 +950,9 @@ KgChoice kg_choose(int fmt, const ql_linear_ep *const *ord, int n)
                                 1.2 * std::max(4.0, steps / (2.0 * device_cus()));
     } else if (fmt == QL_FMT_F16) {
         c.use = c.plan.us < 12.0 + plan_splits(fmt, ds, n).t;
+    } else if (all_gemv) {
+        const double us = gemv4_int8_us(ds, n, device_cus());
+        c.use = (maxK <= 2048 ? 1.25 * c.plan.us + 0.3 : 1.1 * c.plan.us + 0.6) < us;
     } else if (maxM <= stream_max_m()) {
         int S[QL_MAX_GROUP], P[QL_MAX_GROUP];
         c.use = c.plan.us < 0.8 * stream_plan(fmt, ds, n, device_cus(), S, P).us;

@@ -180,6 +180,17 @@ def test_one_stage_layers_at_few_rows(probe):
     assert all(use for use, _ in kg_choices(probe, wide_n))
 
 
+def test_int8_four_rows(probe):
+    """int8 at four rows: the alternative is the GEMV, ahead on small launches
+    (a d = 512 block 6.6 us against 7.5, one-stage layers 4.0 against 5.0); the
+    larger blocks take the K-group kernel."""
+    stay = [block(512), block(256), [(893, 256)], [(64, 256)], [(5605, 1280)], [(2048, 8192)]]
+    take = [block(768), block(1024), block(1536), block(2048), [(4500, 256)], [(8198, 4096)]]
+    calls = [(INT8, 0, 0, 4, ls) for ls in stay + take]
+    got = [use for use, _ in kg_choices(probe, calls)]
+    assert got == [0] * len(stay) + [1] * len(take), got
+
+
 def test_w8a8_launches_fit_a_grid(probe):
     """A launch holds fewer than 2^32 threads: a product whose pipelined shapes
     all pass that keeps the general kernel, and any other one stays on the
