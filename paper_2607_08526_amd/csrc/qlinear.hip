@@ -585,34 +585,73 @@ int launch_rows(const ql_linear_ep *const *ls, int n, int forced, WsSource &wsrc
     return QL_OK;
 }
 
-// The tiled exact kernel over a group (LinDescs set up with ksplit = 1).
-// A group with too few tiles for two workgroups per CU has its reductions
-// cut into parts of one common length (at least 4 steps of 64 k), each
-// layer into ceil(steps / length) parts; the parts' plain partial outputs
-// are added, in part order, by the split-sum launch, which also applies
-// the layers' epilogues.
+// K parts of the tiled exact kernel over a group (LinDescs with their tiles;
+// sets ksplit and psteps).  A group with too few tiles for two workgroups per
+// CU has its reductions cut into parts of one common length (at least 4 steps
+// of 64 k), each layer into ceil(steps / length) parts.
+void plan_tiled(LinDesc *ds, int n)
+{
+    const int64_t target = 2 * (int64_t)device_cus();
+    int64_t work = 0;
+    for (int i = 0; i < n; ++i)
+        work += (int64_t)ds[i].tiles_m * ds[i].tiles_n * ((ds[i].K / 32 + 1) / 2);
+    const int64_t L = std::max<int64_t>(4, (work + target - 1) / target);
+    for (int i = 0; i < n; ++i) {
+        LinDesc &d = ds[i];
+        const int ns = (d.K / 32 + 1) / 2;  // 64-k steps, the last one possibly half
+        const int S = (int)std::min<int64_t>(EXT_MAX_SPLIT, (ns + L - 1) / L);
+        d.psteps = (ns + S - 1) / S;
+        d.ksplit = (ns + d.psteps - 1) / d.psteps;
+    }
+}
+
+// Estimated us of such a launch with fp32 activations: its 64-k steps, the
+// longest part's or those of two workgroups per CU, the sum launch and, up to
+// 32 rows, the weight bytes.  Within 15% of nine in ten of 546 layers and
+// groups at up to 32 rows, within 20% of as many above.
+double tiled_f32_us(const LinDesc *ds, int n, int64_t maxM, int fmt)
+{
+    LinDesc d[QL_MAX_GROUP];
+    const TileCfg t = choose_tile(maxM, true);
+    for (int i = 0; i < n; ++i) {
+        d[i] = ds[i];
+        d[i].tiles_m = (d[i].M + tile_bm(t) - 1) / tile_bm(t);
+        d[i].tiles_n = (d[i].N + tile_bn(t) - 1) / tile_bn(t);
+    }
+    plan_tiled(d, n);
+    double longest = 0.0, steps = 0.0, sum_bytes = 0.0, mb = 0.0;
+    for (int i = 0; i < n; ++i) {
+        const double parts = (double)d[i].tiles_m * d[i].tiles_n * d[i].ksplit;
+        longest = std::max(longest, (double)d[i].psteps);
+        steps += parts * d[i].psteps;
+        if (d[i].ksplit > 1)
+            sum_bytes += (d[i].ksplit + 1) * (double)d[i].M * d[i].N * 4;
+        mb += (double)d[i].N * d[i].K * (fmt == QL_FMT_INT8 ? 1e-6 : 0.5e-6);
+    }
+    steps = std::max(longest, steps / (2.0 * device_cus()));
+    if (maxM > 32)
+        return 8.5 + 1.4 * steps + 0.8e-6 * sum_bytes;
+    return (sum_bytes > 0.0 ? 6.0 + 0.3 * (n - 1) : 2.6) + 1.05 * steps +
+           (maxM <= 16 ? 2.0e-6 : 1.4e-6) * sum_bytes + 0.3 * std::max(0.0, mb - 2.0);
+}
+
+// The tiled exact kernel over a group (LinDescs set up with ksplit = 1); the
+// parts' plain partial outputs are added, in part order, by the split-sum
+// launch, which also applies the layers' epilogues.
 int launch_tiled(int fmt, bool xf32, TileCfg t, GroupArgs &a, WsSource &wsrc,
                  hipStream_t stream)
 {
     const int n = a.n;
-    const int64_t target = 2 * (int64_t)device_cus();
-    int64_t work = 0;
-    for (int i = 0; i < n; ++i)
-        work += (int64_t)a.d[i].tiles_m * a.d[i].tiles_n * ((a.d[i].K / 32 + 1) / 2);
-    const int64_t L = std::max<int64_t>(4, (work + target - 1) / target);
+    plan_tiled(a.d, n);
     int64_t total = 0;
     size_t part_off[QL_MAX_GROUP], bytes = 0;
     for (int i = 0; i < n; ++i) {
         LinDesc &d = a.d[i];
-        const int ns = (d.K / 32 + 1) / 2;  // 64-k steps, the last one possibly half
-        int S = (int)std::min<int64_t>(EXT_MAX_SPLIT, (ns + L - 1) / L);
-        d.psteps = (ns + S - 1) / S;
-        d.ksplit = S = (ns + d.psteps - 1) / d.psteps;
         d.tile_begin = (int)total;
-        total += (int64_t)d.tiles_m * d.tiles_n * S;
+        total += (int64_t)d.tiles_m * d.tiles_n * d.ksplit;
         part_off[i] = bytes;
-        if (S > 1)
-            bytes += round256((size_t)S * d.M * d.N * 4);
+        if (d.ksplit > 1)
+            bytes += round256((size_t)d.ksplit * d.M * d.N * 4);
     }
     if (total >= I31)
         return QL_ERR_UNSUPPORTED;
@@ -911,9 +950,13 @@ KgPlan kg_plan(int fmt, const ql_linear_ep *const *ls, int n)
 //   fp16 weights: under 12 us + the plan's steps (that kernel has one
 //     workgroup per CU there: 4608 x 1536 at 214 rows 27.2 -> 14.9 us, 2048 x
 //     8192 at 400 rows stays, 41 against 50);
-//   fp32 X: where its estimate is under a fixed part plus 1.2 us per 64-k
-//     step of the tiled kernel's two workgroups per CU (1024 x 1024 at 64 rows
-//     15.9 -> 6.6 us; 2048 x 8192 at 8 rows stays, 20.6 against 23.0).
+//   fp32 X, up to 32 rows: where its estimate and 1 us are under the tiled
+//     kernel's (4608 x 1536 at 16 rows 14.5 -> 8.9 us; 91 x 4352 at one row
+//     stays, 10.9 against 15.2, as does 2048 x 8192 at 8, 20.8 against 23.0);
+//   fp32 X above: where its estimate is under 14 us + 1.2 us per 64-k step of
+//     the tiled kernel's two workgroups per CU, and under 1.05 of the tiled
+//     kernel's own (1024 x 1024 at 64 rows 15.9 -> 6.8 us; 5855 x 256 at 416
+//     stays, 18.7 against 22.0).
 struct KgChoice {
     bool use;
     KgPlan plan;
@@ -941,13 +984,18 @@ KgChoice kg_choose(int fmt, const ql_linear_ep *const *ord, int n)
         ds[i].tiles_n = (int)((l.N + wide_tile_bn() - 1) / wide_tile_bn());
     }
     if (ord[0]->lin.xdt == QL_DT_F32) {
-        const TileCfg tc = choose_tile(maxM, true);
-        double steps = 0.0;
-        for (int i = 0; i < n; ++i)
-            steps += (double)((ds[i].M + tile_bm(tc) - 1) / tile_bm(tc)) *
-                     ((ds[i].N + tile_bn(tc) - 1) / tile_bn(tc)) * (ds[i].K / 64);
-        c.use = c.plan.us < (maxM <= 32 ? 10.0 : 14.0) +
-                                1.2 * std::max(4.0, steps / (2.0 * device_cus()));
+        const double us = tiled_f32_us(ds, n, maxM, fmt);
+        if (maxM <= 32) {
+            c.use = c.plan.us + 1.0 < us;
+        } else {
+            const TileCfg tc = choose_tile(maxM, true);
+            double steps = 0.0;
+            for (int i = 0; i < n; ++i)
+                steps += (double)((ds[i].M + tile_bm(tc) - 1) / tile_bm(tc)) *
+                         ((ds[i].N + tile_bn(tc) - 1) / tile_bn(tc)) * (ds[i].K / 64);
+            c.use = c.plan.us < std::min(1.05 * us,
+                                         14.0 + 1.2 * std::max(4.0, steps / (2.0 * device_cus())));
+        }
     } else if (fmt == QL_FMT_F16) {
         c.use = c.plan.us < 12.0 + plan_splits(fmt, ds, n).t;
     } else if (all_gemv) {

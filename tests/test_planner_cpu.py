@@ -191,6 +191,22 @@ def test_int8_four_rows(probe):
     assert got == [0] * len(stay) + [1] * len(take), got
 
 
+def test_fp32_activations(probe):
+    """fp32 activations: few rows and a reduction of a few thousand, or many
+    rows of one stage, stay with the tiled kernel (2816 to 4352 long at one to
+    eight rows 9.5 to 12 us against 11 to 15); wider or shorter layers and the
+    blocks take the K-group kernel."""
+    stay = [(1, [(91, 4352)]), (8, [(754, 4096)]), (3, [(199, 3840)]), (15, [(97, 4352)]),
+            (29, [(497, 4352)]), (8, [(2048, 8192)]), (518, [(2213, 256)] * 2),
+            (416, [(5855, 256)]), (976, [(705, 256)] * 3)]
+    take = [(64, [(1024, 1024)]), (16, [(4608, 1536)]), (1, [(63, 768)]), (8, block(1024)),
+            (32, block(2048)), (30, block(256)), (200, [(2048, 2048)])]
+    for fmt in (Q4, INT8):
+        calls = [(fmt, 1, 0, M, ls) for M, ls in stay + take]
+        got = [use for use, _ in kg_choices(probe, calls)]
+        assert got == [0] * len(stay) + [1] * len(take), (fmt, got)
+
+
 def test_w8a8_launches_fit_a_grid(probe):
     """A launch holds fewer than 2^32 threads: a product whose pipelined shapes
     all pass that keeps the general kernel, and any other one stays on the
