@@ -938,7 +938,8 @@ KgPlan kg_plan(int fmt, const ql_linear_ep *const *ls, int n)
 //   bf16 X, up to 32 rows: where its estimate is under 0.8 of the streaming
 //     kernel's (blocks 1.1-1.7 times faster; single layers, which cannot fill
 //     the GPU with whole reductions, mostly stay: 2048 x 8192 at 8 rows 9.0 us
-//     streamed against 11.6);
+//     streamed against 11.6).  For q4 at up to 16 rows its estimate is 0.5 us
+//     low: 1025 x 1280 at 9 rows stays, 5.5 us against 6.0;
 //   int8, bf16 X, four rows, where the streaming kernel is not the
 //     alternative: where 1.1 of its estimate (1.25 with K <= 2048, where it is
 //     low) and a margin are under the GEMV's (gemv4_int8_us; a d = 512 block
@@ -1003,7 +1004,8 @@ KgChoice kg_choose(int fmt, const ql_linear_ep *const *ord, int n)
         c.use = (maxK <= 2048 ? 1.25 * c.plan.us + 0.3 : 1.1 * c.plan.us + 0.6) < us;
     } else if (maxM <= stream_max_m()) {
         int S[QL_MAX_GROUP], P[QL_MAX_GROUP];
-        c.use = c.plan.us < 0.8 * stream_plan(fmt, ds, n, device_cus(), S, P).us;
+        const double low = fmt == QL_FMT_Q4 && maxM <= 16 ? 0.5 : 0.0;
+        c.use = c.plan.us + low < 0.8 * stream_plan(fmt, ds, n, device_cus(), S, P).us;
     } else {
         c.use = c.plan.us < (maxM <= skinny_max_m() ? 1e30 : 8.0 + 0.8 * plan_splits(fmt, ds, n).t);
     }

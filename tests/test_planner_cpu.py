@@ -180,6 +180,17 @@ def test_one_stage_layers_at_few_rows(probe):
     assert all(use for use, _ in kg_choices(probe, wide_n))
 
 
+def test_q4_up_to_sixteen_rows(probe):
+    """q4 at up to 16 rows: reductions of 1280 to 1536 stay streamed (5.4 to
+    5.7 us against 5.9 to 6.4); shorter ones and the blocks take the K-group
+    kernel."""
+    calls = [(Q4, 0, 0, M, ls) for M in (9, 13, 16)
+             for ls in ([(1025, 1280)], [(1574, 1536)], [(129, 1280)] * 3)]
+    assert not any(use for use, _ in kg_choices(probe, calls))
+    calls = [(Q4, 0, 0, M, ls) for M in (9, 16) for ls in (block(512), block(2048), [(300, 768)])]
+    assert all(use for use, _ in kg_choices(probe, calls))
+
+
 def test_int8_four_rows(probe):
     """int8 at four rows: the alternative is the GEMV, ahead on small launches
     (a d = 512 block 6.6 us against 7.5, one-stage layers 4.0 against 5.0); the
