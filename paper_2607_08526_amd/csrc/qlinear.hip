@@ -392,42 +392,92 @@ SplitPlan plan_splits(int fmt, const LinDesc *d, int n)
     return best;
 }
 
-// Recently used plans, keyed by the group's shapes (the search above costs
-// tens of microseconds of host time).
+// What a plan depends on: format, shapes, epilogues, CUs.
+struct PlanKey {
+    int64_t v[4 * QL_MAX_GROUP + 4];
+    int len;
+    void add(int64_t x) { v[len++] = x; }
+    void add_layer(int64_t M, int64_t N, int64_t K, bool epi)
+    {
+        add(M);
+        add(N);
+        add(K);
+        add(epi);
+    }
+    bool operator==(const PlanKey &o) const
+    {
+        return len == o.len && std::equal(v, v + len, o.v);
+    }
+    uint64_t hash() const  // FNV-1a over the words, high bits folded in
+    {
+        uint64_t h = 14695981039346656037ull;
+        for (int i = 0; i < len; ++i)
+            h = (h ^ (uint64_t)v[i]) * 1099511628211ull;
+        return h ^ (h >> 29);
+    }
+};
+
+// Plans by their keys (a search costs up to 200 us of host time), for any
+// thread: SETS sets of WAYS, the oldest entry of a set replaced.  A program
+// with a few hundred shapes (some clip lengths, each with a model's layers)
+// keeps them all.
+template <class Plan>
+class PlanCache {
+    static constexpr int SETS = 128, WAYS = 8;
+    struct Entry {
+        PlanKey key;
+        Plan plan;
+    };
+    std::mutex mu_;
+    Entry entry_[SETS][WAYS] = {};
+    uint8_t next_[SETS] = {};
+
+public:
+    bool find(const PlanKey &k, Plan &p)
+    {
+        const int set = (int)(k.hash() % SETS);
+        std::lock_guard<std::mutex> g(mu_);
+        for (const Entry &e : entry_[set])
+            if (e.key == k) {
+                p = e.plan;
+                return true;
+            }
+        return false;
+    }
+    void put(const PlanKey &k, const Plan &p)
+    {
+        const int set = (int)(k.hash() % SETS);
+        std::lock_guard<std::mutex> g(mu_);
+        entry_[set][next_[set]] = Entry{k, p};
+        next_[set] = (uint8_t)((next_[set] + 1) % WAYS);
+    }
+};
+
+PlanCache<SplitPlan> &wide_plans()
+{
+    static PlanCache<SplitPlan> c;
+    return c;
+}
+
+PlanKey wide_key(int fmt, const LinDesc *d, int n)
+{
+    PlanKey k{};
+    k.add(device_cus());
+    k.add(wide_wgs_per_cu(fmt));
+    for (int i = 0; i < n; ++i)  // (an epilogue lengthens in-kernel reductions)
+        k.add_layer(d[i].M, d[i].N, d[i].K, epi_active(d[i].ep));
+    return k;
+}
+
 SplitPlan cached_plan(int fmt, const LinDesc *d, int n)
 {
-    struct Entry {
-        int n, cus, slots;
-        int64_t shape[QL_MAX_GROUP][4];
-        SplitPlan pl;
-    };
-    constexpr int SLOTS = 16;
-    static std::mutex mu;
-    static Entry cache[SLOTS];
-    static int used = 0, next = 0;
-    Entry key{};
-    key.n = n;
-    key.cus = device_cus();
-    key.slots = wide_wgs_per_cu(fmt);
-    for (int i = 0; i < n; ++i) {
-        key.shape[i][0] = d[i].M;
-        key.shape[i][1] = d[i].N;
-        key.shape[i][2] = d[i].K;
-        key.shape[i][3] = epi_active(d[i].ep);  // it lengthens in-kernel reductions
+    const PlanKey k = wide_key(fmt, d, n);
+    SplitPlan p;
+    if (!wide_plans().find(k, p)) {
+        p = plan_splits(fmt, d, n);
+        wide_plans().put(k, p);
     }
-    {
-        std::lock_guard<std::mutex> g(mu);
-        for (int e = 0; e < used; ++e)
-            if (cache[e].n == n && cache[e].cus == key.cus && cache[e].slots == key.slots &&
-                std::equal(&cache[e].shape[0][0], &cache[e].shape[0][0] + 4 * n, &key.shape[0][0]))
-                return cache[e].pl;
-    }
-    key.pl = plan_splits(fmt, d, n);
-    std::lock_guard<std::mutex> g(mu);
-    cache[next] = key;
-    next = (next + 1) % SLOTS;
-    used = std::min(used + 1, SLOTS);
-    return key.pl;
+    return p;
 }
 
 TileCfg choose_tile(int64_t M, bool xf32)
@@ -998,7 +1048,7 @@ KgChoice kg_choose(int fmt, const ql_linear_ep *const *ord, int n)
                                          14.0 + 1.2 * std::max(4.0, steps / (2.0 * device_cus())));
         }
     } else if (fmt == QL_FMT_F16) {
-        c.use = c.plan.us < 12.0 + plan_splits(fmt, ds, n).t;
+        c.use = c.plan.us < 12.0 + cached_plan(fmt, ds, n).t;
     } else if (all_gemv) {
         const double us = gemv4_int8_us(ds, n, device_cus());
         c.use = (maxK <= 2048 ? 1.25 * c.plan.us + 0.3 : 1.1 * c.plan.us + 0.6) < us;
@@ -1007,49 +1057,39 @@ KgChoice kg_choose(int fmt, const ql_linear_ep *const *ord, int n)
         const double low = fmt == QL_FMT_Q4 && maxM <= 16 ? 0.5 : 0.0;
         c.use = c.plan.us + low < 0.8 * stream_plan(fmt, ds, n, device_cus(), S, P).us;
     } else {
-        c.use = c.plan.us < (maxM <= skinny_max_m() ? 1e30 : 8.0 + 0.8 * plan_splits(fmt, ds, n).t);
+        // (cached_plan: the launch finds the plan there if it takes it)
+        c.use = c.plan.us < (maxM <= skinny_max_m() ? 1e30 : 8.0 + 0.8 * cached_plan(fmt, ds, n).t);
     }
     return c;
 }
 
-// Recently made choices, keyed by the group's shapes: the plans behind one
-// cost tens of microseconds of host time.
+PlanCache<KgChoice> &kg_choices()
+{
+    static PlanCache<KgChoice> c;
+    return c;
+}
+
+PlanKey kg_key(int fmt, const ql_linear_ep *const *ord, int n)
+{
+    PlanKey k{};
+    k.add(device_cus());
+    k.add(fmt);
+    k.add(ord[0]->lin.xdt);
+    for (int i = 0; i < n; ++i)
+        k.add_layer(ord[i]->lin.M, ord[i]->lin.N, ord[i]->lin.K,
+                    epi_active(to_epilogue(ord[i]->ep)));
+    return k;
+}
+
 KgChoice cached_kg_choice(int fmt, const ql_linear_ep *const *ord, int n)
 {
-    struct Entry {
-        int fmt, xdt, n, cus;
-        int64_t shape[QL_MAX_GROUP][4];
-        KgChoice c;
-    };
-    constexpr int SLOTS = 32;
-    static std::mutex mu;
-    static Entry cache[SLOTS];
-    static int used = 0, next = 0;
-    Entry key{};
-    key.fmt = fmt;
-    key.xdt = ord[0]->lin.xdt;
-    key.n = n;
-    key.cus = device_cus();
-    for (int i = 0; i < n; ++i) {
-        const ql_linear &l = ord[i]->lin;
-        key.shape[i][0] = l.M;
-        key.shape[i][1] = l.N;
-        key.shape[i][2] = l.K;
-        key.shape[i][3] = epi_active(to_epilogue(ord[i]->ep));
+    const PlanKey k = kg_key(fmt, ord, n);
+    KgChoice c;
+    if (!kg_choices().find(k, c)) {
+        c = kg_choose(fmt, ord, n);
+        kg_choices().put(k, c);
     }
-    {
-        std::lock_guard<std::mutex> g(mu);
-        for (int e = 0; e < used; ++e)
-            if (cache[e].fmt == fmt && cache[e].xdt == key.xdt && cache[e].n == n && cache[e].cus == key.cus &&
-                std::equal(&cache[e].shape[0][0], &cache[e].shape[0][0] + 4 * n, &key.shape[0][0]))
-                return cache[e].c;
-    }
-    key.c = kg_choose(fmt, ord, n);
-    std::lock_guard<std::mutex> g(mu);
-    cache[next] = key;
-    next = (next + 1) % SLOTS;
-    used = std::min(used + 1, SLOTS);
-    return key.c;
+    return c;
 }
 
 int launch_kg(const ql_linear_ep *const *ord, int n, const KgPlan &plan, WsSource &wsrc,

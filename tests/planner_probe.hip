@@ -12,8 +12,9 @@
 // Output, one line per input: "wide ext S1 ps1 S2 ps2 ..." (layers in the
 // order the library launches them: longest reduction first) or
 // "stream rw kw mx S1 pb1 S2 pb2 ...", "w8a8 kernel workgroups threads"
-// or "kg use K1 shape1 rows1 columns1 ..." (use 1: the K-group kernel runs;
-// the tile of each layer's shape).
+// or "kg kept planned use K1 shape1 rows1 columns1 ..." (kept: the choice was
+// in its cache; planned: afterwards the large-M plan is in its own; use 1: the
+// K-group kernel runs; the tile of each layer's shape).
 #include "../paper_2607_08526_amd/csrc/qlinear.hip"
 
 #include <cstdio>
@@ -67,8 +68,20 @@ int main()
             std::stable_sort(o, o + n, [](const ql_linear_ep *a, const ql_linear_ep *b) {
                 return a->lin.K > b->lin.K;
             });
-            const KgChoice c = kg_choose(fmt, o, n);
-            std::printf("kg %d", c.use ? 1 : 0);
+            // whether the choice was kept, then, after it, the large-M plan
+            KgChoice c{};
+            const bool kept = kg_choices().find(kg_key(fmt, o, n), c);
+            c = cached_kg_choice(fmt, o, n);
+            for (int i = 0; i < n; ++i) {
+                d[i].M = M;
+                d[i].N = (int)o[i]->lin.N;
+                d[i].K = (int)o[i]->lin.K;
+                if (epi)
+                    d[i].ep.bias = reinterpret_cast<const float *>(16);
+            }
+            SplitPlan sp{};
+            const bool planned = wide_plans().find(wide_key(fmt, d, n), sp);
+            std::printf("kg %d %d %d", kept, planned, c.use ? 1 : 0);
             for (int i = 0; i < n; ++i) {
                 const KgTile t = kg_tile_shape(fmt, xf32 != 0, M, c.plan.shape[i]);
                 std::printf(" %d %d %d %d", (int)o[i]->lin.K, c.plan.shape[i], t.m, t.n);

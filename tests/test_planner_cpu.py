@@ -163,9 +163,23 @@ def kg_choices(probe, calls):
     res = []
     for t in out:
         assert t[0] == "kg"
-        v = list(map(int, t[2:]))
-        res.append((int(t[1]), [tuple(v[i:i + 4]) for i in range(0, len(v), 4)]))
+        v = list(map(int, t[4:]))
+        res.append((int(t[3]), [tuple(v[i:i + 4]) for i in range(0, len(v), 4)]))
     return res
+
+
+def test_plans_are_made_once(probe):
+    """A program's shapes (a model's layers and blocks at 40 clip lengths) are
+    looked up, not planned again, and where the choice needed the large-M plan
+    the launch finds that one too."""
+    calls = [f"kg {Q4} 0 {e} {M} " + " ".join(f"{N} {K}" for N, K in ls)
+             for M in range(70, 2030, 50) for e, ls in
+             [(0, block(1024))] + [(1, [l]) for l in block(1536)]]
+    out = probe(calls + calls)
+    first, second = out[:len(calls)], out[len(calls):]
+    assert all(t[1] == "0" for t in first)
+    assert all(t[2] == "1" for t in first)
+    assert all(t[1] == "1" for t in second)
 
 
 def test_one_stage_layers_at_few_rows(probe):
