@@ -526,12 +526,17 @@ void pipe_candidate(const W8Args &a, W8Kernel kernel, double per_step, double fi
 // The pipelined kernel in its fastest shape by the estimate, where it takes
 // the operands and a shape's launch stays within the threads of a grid (2^30
 // rows of one column tile pass it in all three shapes); else the general
-// kernel.
+// kernel.  A single 64-k step has nothing to pipeline: the general kernel keeps
+// up to 8 rows (2 x 1191 x 64 5.0 us, pipelined 5.8) and, where outputs go out
+// one at a time (N % 4), grids between one and two of its workgroups per CU
+// (1410 x 3915 x 64 18.2 against 20.1; at half the grid 15.5 against 13.7).
 W8Plan w8a8_plan(const W8Args &a, int cus)
 {
     const int64_t tm = ((int64_t)a.M + BM - 1) / BM, tn = ((int64_t)a.N + BN - 1) / BN;
     W8Plan p{W8_GENERAL, tm * tn, THREADS};
-    if (a.K % 64 == 0 && a.K < (1 << 23) && ((uintptr_t)a.scales & 3) == 0) {
+    const bool one_step =
+        a.K == 64 && (a.M <= 8 || (a.N % 4 != 0 && p.wgs > cus && p.wgs <= 2 * (int64_t)cus));
+    if (a.K % 64 == 0 && a.K < (1 << 23) && ((uintptr_t)a.scales & 3) == 0 && !one_step) {
         double us = 1e300;
         pipe_candidate<PipeLarge>(a, W8_LARGE, 0.62, 0.0, 4.0, cus, p, us);
         pipe_candidate<PipeMid>(a, W8_MID, 0.32, 2.8, 2.0, cus, p, us);

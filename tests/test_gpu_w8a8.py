@@ -111,7 +111,8 @@ def test_forward_w8a8_ragged(gpu, orc, M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K", [
-    (1, 1, 64), (63, 65, 192), (65, 129, 1152), (200, 130, 512),      # 64 x 64 tiles
+    (1, 1, 64), (1411, 3915, 64),                        # one step: the general kernel
+    (9, 1, 64), (1, 1, 128), (63, 65, 192), (65, 129, 1152), (200, 130, 512),  # 64 x 64 tiles
     (1000, 1030, 128), (1290, 1540, 320),                              # 64 x 128 tiles
     (1153, 2049, 64), (2050, 4097, 192)])                              # 128 x 128 tiles
 def test_forward_w8a8_pipelined(gpu, orc, M, N, K):

@@ -235,10 +235,14 @@ def test_fp32_activations(probe):
 def test_w8a8_launches_fit_a_grid(probe):
     """A launch holds fewer than 2^32 threads: a product whose pipelined shapes
     all pass that keeps the general kernel, and any other one stays on the
-    fastest shape that fits.  Scales at an odd 2-byte address, and K that is not
-    whole 64-k steps, take the general kernel."""
+    fastest shape that fits.  Scales at an odd 2-byte address, K that is not
+    whole 64-k steps, and the single-step products that the general kernel is
+    ahead on, take the general kernel."""
     GENERAL, LARGE, MID, SMALL = range(4)
-    cases = [((0, 2 ** 30, 1, 64), GENERAL), ((0, 2 ** 30, 64, 64), GENERAL),
+    cases = [((0, 8, 1191, 64), GENERAL), ((0, 1, 168, 64), GENERAL), ((0, 9, 1191, 64), SMALL),
+             ((0, 8, 1191, 128), SMALL), ((0, 1410, 3915, 64), GENERAL),
+             ((0, 1410, 3916, 64), LARGE), ((0, 1759, 1097, 64), LARGE),
+             ((0, 2 ** 30, 1, 64), GENERAL), ((0, 2 ** 30, 64, 64), GENERAL),
              ((0, 2 ** 30 - 128, 1, 64), LARGE), ((0, 2 ** 27, 128, 4096), LARGE),
              ((0, 2048, 8192, 2048), LARGE), ((0, 1290, 1536, 1536), MID),
              ((0, 64, 4608, 1536), SMALL), ((2, 1290, 1536, 1536), GENERAL),
