@@ -450,7 +450,9 @@ struct KgShapes {
     using R1C16 = KgGeo<FMT, false, XR1, 1, FEW ? 2 : 1, 16>;
     using R2W4 = KgGeo<FMT, false, 64, 4, 2>;
     using R2W2 = KgGeo<FMT, false, 64, 2, 1>;
-    static constexpr bool R2 = XR > 32, R2_W4 = R2, C16 = true;
+    // (16 columns of q4 at up to 16 rows cost more per workgroup than 32 and
+    // there are twice as many: no plan takes them)
+    static constexpr bool R2 = XR > 32, R2_W4 = R2, C16 = I8 || XR > 16;
 };
 // fp16 weights (X the fp16 copy of the pre-pass)
 template <int XR>
@@ -560,19 +562,25 @@ KgTile tile_of(int shape)
     }
 }
 
+template <int FMT>
+KgTile tile_fmt(bool xf32, int64_t maxM, int shape)
+{
+    if (xf32)
+        return tile_of<KgShapesF32<FMT>>(shape);
+    return maxM > 32   ? tile_of<KgShapes<FMT, 64>>(shape)
+           : maxM > 16 ? tile_of<KgShapes<FMT, 32>>(shape)
+           : maxM > 8  ? tile_of<KgShapes<FMT, 16>>(shape)
+                       : tile_of<KgShapes<FMT, 8>>(shape);
+}
+
 }  // namespace
 
 KgTile kg_tile_shape(int fmt, bool xf32, int64_t maxM, int shape)
 {
-    // (the tiles of int8 and q4 are alike)
     if (fmt == QL_FMT_F16)
         return tile_of<KgShapes<QL_FMT_F16, 64>>(shape);
-    if (xf32)
-        return tile_of<KgShapesF32<QL_FMT_Q4>>(shape);
-    return maxM > 32   ? tile_of<KgShapes<QL_FMT_Q4, 64>>(shape)
-           : maxM > 16 ? tile_of<KgShapes<QL_FMT_Q4, 32>>(shape)
-           : maxM > 8  ? tile_of<KgShapes<QL_FMT_Q4, 16>>(shape)
-                       : tile_of<KgShapes<QL_FMT_Q4, 8>>(shape);
+    return fmt == QL_FMT_INT8 ? tile_fmt<QL_FMT_INT8>(xf32, maxM, shape)
+                              : tile_fmt<QL_FMT_Q4>(xf32, maxM, shape);
 }
 
 hipError_t launch_qgemm_kg(int fmt, bool xf32, int maxM, const GroupArgs &args, hipStream_t stream)

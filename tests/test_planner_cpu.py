@@ -168,6 +168,35 @@ def kg_choices(probe, calls):
     return res
 
 
+def test_every_kgroup_shape_built_is_reached(probe):
+    """Every shape that a launch of the K-group kernel holds is one that some
+    call takes (single layers and groups of up to 8), and no call takes one it
+    does not hold: bf16 X by the rows staged, fp32 X, fp16 weights."""
+    rng = np.random.default_rng(4)
+    calls = []
+    for _ in range(4000):
+        fmt, f32 = [(Q4, 0), (INT8, 0), (Q4, 1), (INT8, 1), (16, 0)][int(rng.integers(5))]
+        M = int(round(np.exp(rng.uniform(0, np.log(600)))))
+        n = int(rng.choice([1, 1, 2, 4, 8]))
+        ls = [(int(np.exp(rng.uniform(3, 9.5))), 256 * int(np.exp(rng.uniform(0, 4))))
+              for _ in range(n)]
+        calls.append((fmt, f32, 0, M, ls))
+    seen = {}
+    for (fmt, f32, _, M, _), (use, layers) in zip(calls, kg_choices(probe, calls)):
+        if use:
+            rows = "f32" if f32 else "f16" if fmt == 16 else min(r for r in (8, 16, 32, 4096)
+                                                                 if M <= r)
+            for _, shape, tm, tn in layers:
+                assert tm > 0 and tn > 0, (fmt, f32, M)
+                seen.setdefault((fmt, rows), set()).add(shape)
+    for fmt in (Q4, INT8):
+        for rows in (8, 16, 32):
+            assert seen[fmt, rows] == ({0, 1, 2} if fmt == Q4 and rows < 32 else {0, 1, 2, 5})
+        assert seen[fmt, 4096] == set(range(6))
+        assert seen[fmt, "f32"] == {0, 1, 2, 3}
+    assert seen[16, "f16"] == {0, 1, 2, 3}
+
+
 def test_plans_are_made_once(probe):
     """A program's shapes (a model's layers and blocks at 40 clip lengths) are
     looked up, not planned again, and where the choice needed the large-M plan
