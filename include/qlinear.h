@@ -328,12 +328,13 @@ int qlinear_attention(const uint16_t *q, int64_t ldq, const uint16_t *k, int64_t
  *   QL_PATH_TILED   tiled exact MFMA kernel: any M, bf16 or fp32 X
  *   QL_PATH_WIDE    the large-M fp16 path: bf16 X, K % 256 == 0,
  *                   K < 2^23, 16-byte aligned scales
- *   QL_PATH_MID     the mid-M exact kernel (the normal choice for
- *                   32 < M <= 256): bf16 X, K % 256 == 0, K < 2^23,
+ *   QL_PATH_MID     the mid-M exact kernel: bf16 X, K % 256 == 0, K < 2^23,
  *                   16-byte aligned X, codes and scales
+ * The kernel that the library itself takes at few to a few hundred rows (K cut
+ * among the wavefronts of a workgroup) has no value here.
  * A call whose layers a forced kernel cannot take returns
- * QL_ERR_UNSUPPORTED and enqueues nothing.  fp16 weights (QL_FMT_F16) are
- * not affected.  The setting is process-wide (not per thread or stream);
+ * QL_ERR_UNSUPPORTED and enqueues nothing.  fp16 weights (QL_FMT_F16) follow
+ * QL_PATH_WIDE, at any M, and are not affected by the others.  The setting is process-wide (not per thread or stream);
  * QL_PATH_AUTO restores the normal choice.  Returns QL_ERR_INVALID for an
  * unknown value. */
 typedef enum {

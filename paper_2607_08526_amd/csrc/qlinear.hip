@@ -506,6 +506,17 @@ bool stream_fits(const LinDesc &d)
            aligned(d.scales, 16);
 }
 
+// the GEMV's time grows with the rows, the streaming kernel's hardly below 8:
+// at four rows of q4 the streaming kernel is ahead (a d = 2048 block 17.1
+// against 19.7 us); int8, with twice the code bytes per row, keeps the GEMV up
+// to four rows (22.5 / 23.0)
+RowPath auto_row_path(int fmt, const LinDesc &d)
+{
+    return gemv_ok(d) && !(fmt == QL_FMT_Q4 && d.M == 4 && stream_fits(d)) ? RowPath::GEMV
+           : stream_fits(d)                                                ? RowPath::STREAM
+                                                                           : RowPath::SKINNY;
+}
+
 // the large-M kernel's shape limits (bf16 X): whole 256-k steps, 16-byte
 // scale chunks, 32-bit row offsets within a tile
 bool wide_fits(const ql_linear &l)
@@ -549,13 +560,7 @@ int launch_rows(const ql_linear_ep *const *ls, int n, int forced, WsSource &wsrc
             path[i] = RowPath::SKINNY;
             break;
         default:
-            // the GEMV's time grows with the rows, the streaming kernel's
-            // hardly below 8: at four rows of q4 the streaming kernel is ahead
-            // (a d = 2048 block 17.1 against 19.7 us); int8, with twice the
-            // code bytes per row, keeps the GEMV up to four rows (22.5 / 23.0)
-            path[i] = gemv_ok(d) && !(fmt == QL_FMT_Q4 && d.M == 4 && stream_fits(d))
-                          ? RowPath::GEMV
-                          : stream_fits(d) ? RowPath::STREAM : RowPath::SKINNY;
+            path[i] = auto_row_path(fmt, d);
         }
     }
     // the streaming layers: one launch over all of them, their K parts
@@ -829,15 +834,11 @@ void plan_mid(GroupArgs &a)
     }
 }
 
-// ls: layers of one quantized format with bf16 X, mid_fits each.
-int launch_mid(const ql_linear_ep *const *ls, int n, WsSource &wsrc, hipStream_t stream)
+// ord: layers of one quantized format with bf16 X, mid_fits each, in launch
+// order.
+int launch_mid(const ql_linear_ep *const *ord, int n, WsSource &wsrc, hipStream_t stream)
 {
     const int bm = mid_tile_bm(), bn = mid_tile_bn();
-    // longest reduction first, so the long tiles start early
-    const ql_linear_ep *ord[QL_MAX_GROUP];
-    std::copy(ls, ls + n, ord);
-    std::stable_sort(ord, ord + n,
-                     [](const ql_linear_ep *x, const ql_linear_ep *y) { return x->lin.K > y->lin.K; });
     GroupArgs a{};
     a.n = n;
     for (int i = 0; i < n; ++i) {
@@ -1172,93 +1173,110 @@ int launch_kg(const ql_linear_ep *const *ord, int n, const KgPlan &plan, WsSourc
     return e == hipSuccess ? QL_OK : QL_ERR_HIP;
 }
 
+// layers in launch order: longest reduction first, so the long tiles start
+// early
+void launch_order(const ql_linear_ep *const *ls, int n, const ql_linear_ep **ord)
+{
+    std::copy(ls, ls + n, ord);
+    std::stable_sort(ord, ord + n, [](const ql_linear_ep *x, const ql_linear_ep *y) {
+        return x->lin.K > y->lin.K;
+    });
+}
+
+// The kernel family a group (one fmt and xdt) goes to.
+enum class GroupPath { KG, ROWS, MID, WIDE, TILED, REFUSED };
+
+// forced: the path set by qlinear_force_path.  kg receives the K-group
+// kernel's plan where that is the choice.
+GroupPath choose_path(const ql_linear_ep *const *ls, int n, int forced, KgPlan &kg)
+{
+    const bool xf32 = ls[0]->lin.xdt == QL_DT_F32;
+    const bool f16 = ls[0]->lin.fmt == QL_FMT_F16;
+    if (f16 && forced != QL_PATH_WIDE)
+        forced = QL_PATH_AUTO;  // the other forced kernels do not take fp16 weights
+    int64_t maxM = 0;
+    // all_mid: quantized weights, bf16 X, whole 256-k steps, 16-byte aligned
+    // operands
+    bool all_mid = true, all_kg = true, all_wide = true;
+    double steps = 0.0;  // 64-k steps of 128 x 128 tiles
+    for (int i = 0; i < n; ++i) {
+        const ql_linear &l = ls[i]->lin;
+        maxM = std::max(maxM, l.M);
+        all_mid = all_mid && mid_fits(l);
+        all_kg = all_kg && kg_fits(l);
+        all_wide = all_wide && wide_fits(l);
+        steps += (double)((l.M + mid_tile_bm() - 1) / mid_tile_bm()) *
+                 ((l.N + mid_tile_bn() - 1) / mid_tile_bn()) * (l.K / 64);
+    }
+    switch (forced) {
+    case QL_PATH_GEMV:
+    case QL_PATH_STREAM:
+    case QL_PATH_SKINNY:
+        // the few-row kernels take bf16 activations
+        return xf32 ? GroupPath::REFUSED : GroupPath::ROWS;
+    case QL_PATH_MID:
+        return all_mid ? GroupPath::MID : GroupPath::REFUSED;
+    case QL_PATH_WIDE:
+        return all_wide ? GroupPath::WIDE : GroupPath::REFUSED;
+    case QL_PATH_TILED:
+        return GroupPath::TILED;
+    default:
+        break;
+    }
+    if (all_kg && maxM <= KG_MAX_M && (xf32 || f16 || maxM >= KG_MIN_M)) {
+        const ql_linear_ep *ord[QL_MAX_GROUP];
+        launch_order(ls, n, ord);
+        const KgChoice c = cached_kg_choice(ls[0]->lin.fmt, ord, n);
+        if (c.use) {
+            kg = c.plan;
+            return GroupPath::KG;
+        }
+    }
+    if (f16)
+        return GroupPath::WIDE;  // (its limits are checked by check_linear)
+    if (xf32)
+        return GroupPath::TILED;
+    if (maxM <= stream_max_m() || (maxM <= skinny_max_m() && !all_mid))
+        return GroupPath::ROWS;
+    // a few hundred rows that the K-group kernel leaves: the mid-M kernel
+    // where every layer fits it and the group's work is short (its steps per
+    // CU at most MID_MAX_STEPS_PER_CU; beyond that the large-M path's wider
+    // tiles outweigh its pre-pass).  At most 64 rows the alternative is not the
+    // large-M path but the tiled exact kernel, slower at any length.
+    const bool tall = choose_tile(maxM, false) == TILE_M128;
+    if (maxM <= MID_MAX_M && all_mid &&
+        !(all_wide && tall && steps > MID_MAX_STEPS_PER_CU * device_cus()))
+        return GroupPath::MID;
+    // the fp16 path's kernel reads each weight row's scales as 16-byte
+    // chunks and addresses a tile's rows with 32-bit offsets
+    return tall && all_wide ? GroupPath::WIDE : GroupPath::TILED;
+}
+
 // One grouped launch over layers that share fmt and xdt (M > 0 each).
 int launch_group(const ql_linear_ep *const *ls, int n, WsSource &wsrc, hipStream_t stream)
 {
     if (n == 0)
         return QL_OK;
     const bool xf32 = ls[0]->lin.xdt == QL_DT_F32;
+    const int forced = g_forced_path.load(std::memory_order_relaxed);
+    const ql_linear_ep *ord[QL_MAX_GROUP];
+    launch_order(ls, n, ord);
+    KgPlan kg{};
+    const GroupPath path = choose_path(ls, n, forced, kg);
+    switch (path) {
+    case GroupPath::KG: return launch_kg(ord, n, kg, wsrc, stream);
+    case GroupPath::ROWS: return launch_rows(ls, n, forced, wsrc, stream);
+    case GroupPath::MID: return launch_mid(ord, n, wsrc, stream);
+    case GroupPath::REFUSED: return QL_ERR_UNSUPPORTED;
+    default: break;
+    }
     int64_t maxM = 0;
     for (int i = 0; i < n; ++i)
         maxM = std::max(maxM, ls[i]->lin.M);
-    const bool f16 = ls[0]->lin.fmt == QL_FMT_F16;
-    // fp16 weights have one kernel; a forced path applies to quantized ones
-    const int forced = f16 ? QL_PATH_AUTO : g_forced_path.load(std::memory_order_relaxed);
-    // quantized weights, bf16 X, whole 256-k steps, 16-byte aligned operands
-    bool all_mid = true;
-    for (int i = 0; i < n; ++i)
-        all_mid = all_mid && mid_fits(ls[i]->lin);
-    bool all_kg = forced == QL_PATH_AUTO && maxM <= KG_MAX_M && (xf32 || f16 || maxM >= KG_MIN_M);
-    for (int i = 0; i < n; ++i)
-        all_kg = all_kg && kg_fits(ls[i]->lin);
-    if (all_kg) {
-        // longest reduction first, so the long tiles start early
-        const ql_linear_ep *ord[QL_MAX_GROUP];
-        std::copy(ls, ls + n, ord);
-        std::stable_sort(ord, ord + n, [](const ql_linear_ep *x, const ql_linear_ep *y) {
-            return x->lin.K > y->lin.K;
-        });
-        const KgChoice c = cached_kg_choice(ls[0]->lin.fmt, ord, n);
-        if (c.use)
-            return launch_kg(ord, n, c.plan, wsrc, stream);
-    }
-    const bool per_layer = forced == QL_PATH_AUTO
-                          ? !xf32 && !f16 &&
-                                (maxM <= stream_max_m() || (maxM <= skinny_max_m() && !all_mid))
-                          : forced == QL_PATH_GEMV || forced == QL_PATH_STREAM ||
-                                forced == QL_PATH_SKINNY;
-    if (per_layer && xf32)
-        return QL_ERR_UNSUPPORTED;  // the few-row kernels take bf16 activations
-    if (per_layer)
-        return launch_rows(ls, n, forced, wsrc, stream);
-    // a few hundred rows that the K-group kernel leaves: the mid-M kernel
-    // where every layer fits it and the group's work is short (its 64-k steps of 128 x 128
-    // tiles, per CU, at most MID_MAX_STEPS_PER_CU; beyond that the large-M
-    // path's wider tiles outweigh its pre-pass)
-    if (forced == QL_PATH_MID || (forced == QL_PATH_AUTO && !xf32 && !f16 && maxM <= MID_MAX_M)) {
-        bool ok = true, wide_ok = true;
-        double steps = 0.0;
-        for (int i = 0; i < n; ++i) {
-            const ql_linear &l = ls[i]->lin;
-            ok = ok && mid_fits(l);
-            wide_ok = wide_ok && wide_fits(l);
-            steps += (double)((l.M + mid_tile_bm() - 1) / mid_tile_bm()) *
-                     ((l.N + mid_tile_bn() - 1) / mid_tile_bn()) * (l.K / 64);
-        }
-        // (at most 64 rows the alternative is not the large-M path but the
-        // tiled exact kernel, slower at any length)
-        if (forced == QL_PATH_AUTO && wide_ok && choose_tile(maxM, false) == TILE_M128 &&
-            steps > MID_MAX_STEPS_PER_CU * device_cus())
-            ok = false;
-        if (ok)
-            return launch_mid(ls, n, wsrc, stream);
-        if (forced == QL_PATH_MID)
-            return QL_ERR_UNSUPPORTED;
-    }
-    if (forced == QL_PATH_WIDE)
-        for (int i = 0; i < n; ++i)
-            if (!wide_fits(ls[i]->lin))
-                return QL_ERR_UNSUPPORTED;
-    maxM = 0;
-    for (int i = 0; i < n; ++i)
-        maxM = std::max(maxM, ls[i]->lin.M);
     const TileCfg t = choose_tile(maxM, xf32);
-    // the fp16 path's kernel reads each weight row's scales as 16-byte
-    // chunks and addresses a tile's rows with 32-bit offsets
-    bool wide = !xf32 && t == TILE_M128;
-    for (int i = 0; i < n; ++i)
-        wide = wide && wide_fits(ls[i]->lin);
-    if (forced == QL_PATH_WIDE || forced == QL_PATH_TILED)
-        wide = forced == QL_PATH_WIDE;
-    wide = wide || f16;  // fp16 weights: this kernel at every M (checked by check_linear)
+    const bool wide = path == GroupPath::WIDE;
     const int bm = wide ? wide_tile_bm() : tile_bm(t);
     const int bn = wide ? wide_tile_bn() : tile_bn(t);
-
-    // longest reduction first, so the long tiles start early
-    const ql_linear_ep *ord[QL_MAX_GROUP];
-    std::copy(ls, ls + n, ord);
-    std::stable_sort(ord, ord + n,
-                     [](const ql_linear_ep *a, const ql_linear_ep *b) { return a->lin.K > b->lin.K; });
 
     GroupArgs a{};
     int64_t total = 0;

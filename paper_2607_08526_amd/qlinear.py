@@ -510,7 +510,8 @@ def attention(q, k, v, B, T, H, dh=64, scale=None, O=None, odtype=torch.float32,
 class forced_path:
     """Context manager: every quantized forward call inside it runs on one
     kernel (PATH_GEMV, PATH_STREAM, PATH_SKINNY, PATH_TILED, PATH_WIDE or PATH_MID;
-    qlinear_force_path).  Process-wide; restores automatic choice on exit."""
+    qlinear_force_path; fp16 weights follow PATH_WIDE only).  Process-wide;
+    restores automatic choice on exit."""
 
     def __init__(self, path):
         self.path = path

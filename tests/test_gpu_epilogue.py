@@ -116,8 +116,8 @@ def test_epilogue_every_path(gpu, orc, fmt, xdt, M, N, K):
 
 
 def test_epilogue_f16_weights(gpu, orc):
-    """fp16 weights take the same epilogue (the fp16 path's kernel at small
-    and large M, with and without K parts)."""
+    """fp16 weights take the same epilogue, as the library chooses and on the
+    large-M kernel (at small and large M, with and without K parts)."""
     torch, ql = gpu
     for (M, N, K) in ((2, 40, 256), (214, 520, 1280), (128, 64, 8192)):
         W, X = si.small_case(3100 + M + N + K, M, N, K)
@@ -129,8 +129,10 @@ def test_epilogue_f16_weights(gpu, orc):
         resid = rng.standard_normal((M, N)).astype(np.float32)
         for act, ydt in ((O.ACT_GELU, "f32"), (O.ACT_GELU, "bf16")):
             Yr = orc.epilogue(Pr, bias, act, resid)
-            Yg = run_ep(gpu, ql.FMT_F16, X, O.DT_BF16, wd, None, N, bias, act, resid, ydt)
-            check(Yg, Pr, Yr, bias, O.DT_BF16, ydt == "bf16", (M, N, K, ydt))
+            for path in (ql.PATH_AUTO, ql.PATH_WIDE):
+                with ql.forced_path(path):
+                    Yg = run_ep(gpu, ql.FMT_F16, X, O.DT_BF16, wd, None, N, bias, act, resid, ydt)
+                check(Yg, Pr, Yr, bias, O.DT_BF16, ydt == "bf16", (M, N, K, ydt, path))
 
 
 @pytest.mark.parametrize("M", [3, 16, 40, 200])

@@ -550,25 +550,26 @@ def f16_bits(W):
 
 
 def test_forward_f16_weights(gpu, orc):
-    """fp16 weights (QL_FMT_F16) against the oracle's unquantized product:
-    ragged row and column counts, one to several 64-k steps, small M (the
-    same kernel serves every M), a split long reduction; results repeat bit
-    for bit."""
+    """fp16 weights (QL_FMT_F16) against the oracle's unquantized product, as
+    the library chooses and on the large-M kernel: ragged row and column
+    counts, one to several 64-k steps, small M (both kernels take every M), a
+    split long reduction; results repeat bit for bit."""
     torch, ql = gpu
     for (M, N, K) in ((1, 40, 256), (65, 200, 512), (300, 520, 1280), (129, 17, 1024),
                       (214, 3072, 1024), (128, 64, 8192)):
         W, X = si.small_case(500 + M + N + K, M, N, K)
         W16 = f16_bits(W)
         wd = torch.from_numpy(W16.view(np.int16)).cuda()
-        Y = ql.forward(ql.FMT_F16, dev_x(torch, X, O.DT_BF16), wd, None, N)
-        torch.cuda.synchronize()
-        Yg = Y.cpu().numpy()
         Yr = orc.forward_f16(X, O.DT_BF16, W16)
-        e = rel_err(Yg, Yr)
-        assert e <= TOL[O.DT_BF16], (M, N, K, e)
-        Y2 = ql.forward(ql.FMT_F16, dev_x(torch, X, O.DT_BF16), wd, None, N)
-        torch.cuda.synchronize()
-        assert np.array_equal(Yg, Y2.cpu().numpy())
+        for path in (ql.PATH_AUTO, ql.PATH_WIDE):
+            with ql.forced_path(path):
+                Ys = [ql.forward(ql.FMT_F16, dev_x(torch, X, O.DT_BF16), wd, None, N)
+                      for _ in range(2)]
+                torch.cuda.synchronize()
+            Yg = Ys[0].cpu().numpy()
+            e = rel_err(Yg, Yr)
+            assert e <= TOL[O.DT_BF16], (M, N, K, path, e)
+            assert np.array_equal(Yg, Ys[1].cpu().numpy())
 
 
 def test_forward_f16_block_and_errors(gpu, orc):

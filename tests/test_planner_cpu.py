@@ -211,6 +211,44 @@ def test_plans_are_made_once(probe):
     assert all(t[1] == "1" for t in second)
 
 
+def routes(probe, calls):
+    """calls: (fmt, fp32 X, epilogue, forced path, [(M, N, K), ...]) ->
+    [(kernel, [(K, shape or K parts), ...] in launch order)]"""
+    out = probe([f"route {f} {int(x)} {int(e)} {p} " + " ".join(f"{M} {N} {K}" for M, N, K in ls)
+                 for f, x, e, p, ls in calls])
+    res = []
+    for t in out:
+        assert t[0] == "route"
+        v = list(map(int, t[2:]))
+        res.append((t[1], list(zip(v[::2], v[1::2]))))
+    return res
+
+
+AUTO, GEMV, STREAM, SKINNY, TILED, WIDE, MID = range(7)  # forced paths
+F16 = 16
+
+
+def test_forced_paths_reach_their_kernels(probe):
+    """Each forced path, by format and activation type; fp16 weights follow the
+    large-M path's value at any M and no other."""
+    one = lambda M=8, N=300, K=1024: [(M, N, K)]
+    for fmt in (Q4, INT8):
+        want = [(GEMV, one(4), "rows", 0), (STREAM, one(), "rows", 1), (SKINNY, one(), "rows", 2),
+                (TILED, one(), "tiled", None), (WIDE, one(), "wideext", None),
+                (MID, one(), "mid", None), (MID, one(8, 300, 96), "refused", None),
+                (WIDE, one(8, 300, 96), "refused", None)]
+        got = routes(probe, [(fmt, 0, 0, p, ls) for p, ls, _, _ in want])
+        for (p, ls, kernel, v), (k, vs) in zip(want, got):
+            assert k == kernel and (v is None or vs[0][1] == v), (fmt, p, ls, k, vs)
+        got = routes(probe, [(fmt, 1, 0, p, one()) for p in range(1, 7)])
+        assert [k for k, _ in got] == ["refused"] * 3 + ["tiled"] + ["refused"] * 2
+    for M in (1, 65, 300):
+        auto = routes(probe, [(F16, 0, 0, AUTO, one(M))])
+        got = routes(probe, [(F16, 0, 0, p, one(M)) for p in range(1, 7)])
+        assert [g for g in got[:4] + got[5:]] == auto * 5
+        assert got[4][0] in ("wide", "wideext")
+
+
 def test_one_stage_layers_at_few_rows(probe):
     """K = 256 at few rows: the streaming kernel's whole-layer plan (about 4.2
     us) is ahead of the K-group kernel (about 5), except where the columns fill
