@@ -57,17 +57,24 @@ def check(Yg, Pr, Yr, bias, xdt, ybf16, what):
     assert not bad.any(), (what, np.argwhere(bad)[:4], Yg[bad][:4], Yr[bad][:4])
 
 
-# (fmt, xdt, M, N, K): one shape per kernel that stores final outputs
+# (fmt, xdt, M, N, K, forced path): one shape per kernel that stores final
+# outputs; AUTO: the library's own choice, checked on the CPU
+# (test_planner_cpu.py)
+AUTO, GEMV, STREAM, SKINNY, TILED, WIDE, MID = range(7)
 PATHS = [
-    (O.FMT_Q4, O.DT_BF16, 3, 4097, 2048),     # wavefront GEMV (M <= 4)
-    (O.FMT_INT8, O.DT_BF16, 16, 4100, 512),   # weight streaming, one K part
-    (O.FMT_Q4, O.DT_BF16, 8, 2049, 8192),     # weight streaming, K parts + sum launch
-    (O.FMT_INT8, O.DT_BF16, 20, 70, 320),     # small-M MFMA (K % 256 != 0)
-    (O.FMT_Q4, O.DT_F32, 40, 200, 320),       # MFMA kernel, fp32 activations
-    (O.FMT_INT8, O.DT_BF16, 200, 77, 288),    # MFMA kernel, 128-row tiles
-    (O.FMT_Q4, O.DT_BF16, 300, 520, 1280),    # fp16 path, no split
-    (O.FMT_INT8, O.DT_BF16, 300, 520, 4096),  # fp16 path, K parts + sum launch
-    (O.FMT_Q4, O.DT_BF16, 129, 17, 1024),     # fp16 path, ragged tiles, N % 4 != 0
+    (O.FMT_Q4, O.DT_BF16, 3, 4097, 2048, GEMV),      # wavefront GEMV (M <= 4)
+    (O.FMT_INT8, O.DT_BF16, 16, 4100, 512, STREAM),  # weight streaming, one K part
+    (O.FMT_Q4, O.DT_BF16, 8, 2049, 8192, STREAM),    # weight streaming, K parts + sum launch
+    (O.FMT_INT8, O.DT_BF16, 20, 70, 320, SKINNY),    # small-M MFMA (K % 256 != 0)
+    (O.FMT_Q4, O.DT_F32, 40, 200, 320, TILED),       # MFMA kernel, fp32 activations
+    (O.FMT_INT8, O.DT_BF16, 200, 77, 288, TILED),    # MFMA kernel, 128-row tiles
+    (O.FMT_Q4, O.DT_BF16, 300, 520, 1280, WIDE),     # large-M kernel
+    (O.FMT_INT8, O.DT_BF16, 300, 520, 4096, WIDE),   # large-M kernel, K parts + sum launch
+    (O.FMT_Q4, O.DT_BF16, 129, 17, 1024, WIDE),      # large-M, ragged tiles, N % 4 != 0
+    (O.FMT_INT8, O.DT_BF16, 100, 129, 8192, MID),    # mid-M kernel, K parts, N % 4 != 0
+    (O.FMT_Q4, O.DT_BF16, 300, 520, 1280, AUTO),     # K-group kernel
+    (O.FMT_Q4, O.DT_BF16, 129, 17, 1024, AUTO),      # K-group, 16 columns, N % 4 != 0
+    (O.FMT_INT8, O.DT_F32, 64, 1024, 1024, AUTO),    # K-group kernel, fp32 activations
 ]
 
 # (bias, act, residual, Y dtype): every operation, each store width
@@ -97,8 +104,8 @@ def run_ep(gpu, fmt, X, xdt, cd, sd, N, bias, act, resid, ydt):
     return host_y(torch, Y)
 
 
-@pytest.mark.parametrize("fmt,xdt,M,N,K", PATHS)
-def test_epilogue_every_path(gpu, orc, fmt, xdt, M, N, K):
+@pytest.mark.parametrize("fmt,xdt,M,N,K,path", PATHS)
+def test_epilogue_every_path(gpu, orc, fmt, xdt, M, N, K, path):
     torch, ql = gpu
     W, X = si.small_case(3000 + M + N + K + fmt, M, N, K, xdt)
     cd, sd = ql.quantize(fmt, dev_f32(torch, W))
@@ -110,8 +117,9 @@ def test_epilogue_every_path(gpu, orc, fmt, xdt, M, N, K):
         bias = (rng.standard_normal(N) * 0.5).astype(np.float32) if use_b else None
         resid = rng.standard_normal((M, N)).astype(np.float32) if use_r else None
         Yr = orc.epilogue(Pr, bias, act, resid)
-        Yg = run_ep(gpu, fmt, X, xdt, cd, sd, N, bias, act, resid,
-                    "inplace" if use_r == "inplace" else ydt)
+        with ql.forced_path(path):
+            Yg = run_ep(gpu, fmt, X, xdt, cd, sd, N, bias, act, resid,
+                        "inplace" if use_r == "inplace" else ydt)
         check(Yg, Pr, Yr, bias, xdt, ydt == "bf16", (M, N, K, use_b, act, use_r, ydt))
 
 
@@ -184,14 +192,20 @@ def test_epilogue_gelu_special_values(gpu, orc):
     assert np.max(np.abs(Yg - Yr)) <= 4e-6 * np.max(np.abs(Yr))
 
 
+# M, (N, K), forced path
+EP_GROUPS = [(M, ls, p) for M, ls, ps in ((384, [(700, 512), (256, 4096), (1000, 512)], (WIDE, AUTO)),
+                                          (24, [(3072, 1024), (1024, 4096), (4096, 1024)],
+                                           (STREAM, AUTO))) for p in ps]
+
+
 def test_block_forward_ep_grouped(gpu, orc):
-    """One grouped call with a different epilogue per layer: the fp16 path's
-    grouped launch with K parts (mixed reduction lengths over two
+    """One grouped call with a different epilogue per layer: the large-M
+    kernel's grouped launch with K parts (mixed reduction lengths over two
     activations; summed by the separate launch, which applies the
-    epilogues), and a small-M group on the streaming kernels."""
+    epilogues), a small-M group on the streaming kernel, and both as the
+    library chooses."""
     torch, ql = gpu
-    for M, shapes in ((384, [(700, 512), (256, 4096), (1000, 512)]),
-                      (24, [(3072, 1024), (1024, 4096), (4096, 1024)])):
+    for M, shapes, path in EP_GROUPS:
         for fmt in (O.FMT_INT8, O.FMT_Q4):
             _, xa = si.small_case(3300 + M, M, 1, 1024 if M == 24 else 512)
             _, xb = si.small_case(3301 + M, M, 1, 4096)
@@ -217,10 +231,14 @@ def test_block_forward_ep_grouped(gpu, orc):
                 entries.append((fmt, dev_x(torch, X, O.DT_BF16), cd, sd, N, Y, bd, act, rd))
                 Pr = orc.forward(fmt, X, O.DT_BF16, cr, sr, N)
                 refs.append((Pr, orc.epilogue(Pr, bias, act, resid), bias, ydt == "bf16"))
-            ql.block_forward_ep(entries)
+            with ql.forced_path(path):
+                ql.block_forward_ep(entries)
             torch.cuda.synchronize()
             for e, (Pr, Yr, bias, yb) in zip(entries, refs):
-                check(host_y(torch, e[5]), Pr, Yr, bias, O.DT_BF16, yb, (M, fmt, e[4]))
+                check(host_y(torch, e[5]), Pr, Yr, bias, O.DT_BF16, yb, (M, fmt, e[4], path))
+
+
+ROUTED_GROUP = [(702, 512), (256, 4096), (1000, 512), (257, 4096)]
 
 
 def test_block_forward_ep_routed_layers(gpu, orc):
@@ -233,7 +251,7 @@ def test_block_forward_ep_routed_layers(gpu, orc):
     _, xa = si.small_case(3400, M, 1, 512)
     _, xb = si.small_case(3401, M, 1, 4096)
     rng = np.random.default_rng(3402)
-    shapes = [(702, 512), (256, 4096), (1000, 512), (257, 4096)]
+    shapes = ROUTED_GROUP
     entries, refs = [], []
     for fmt in (O.FMT_Q4, O.FMT_INT8):
         entries.clear()
@@ -255,14 +273,15 @@ def test_block_forward_ep_routed_layers(gpu, orc):
             entries.append((fmt, dev_x(torch, X, O.DT_BF16), cd, sd, N, Y, bd, act, Y))
             P = orc.forward(fmt, X, O.DT_BF16, cr, sr, N)
             refs.append((P, orc.epilogue(P, bias, act, resid), bias))
-        ql.block_forward_ep(entries)
+        with ql.forced_path(ql.PATH_WIDE):
+            ql.block_forward_ep(entries)
         torch.cuda.synchronize()
         for e, (P, Yr, bias) in zip(entries, refs):
             check(host_y(torch, e[5]), P, Yr, bias, O.DT_BF16, False, (fmt, e[4]))
 
 
-@pytest.mark.parametrize("fmt,xdt,M,N,K", PATHS)
-def test_epilogue_bf16_copy_every_path(gpu, orc, fmt, xdt, M, N, K):
+@pytest.mark.parametrize("fmt,xdt,M,N,K,path", PATHS)
+def test_epilogue_bf16_copy_every_path(gpu, orc, fmt, xdt, M, N, K, path):
     """The bf16 copy of an fp32 output (the residual stream's copy that the
     next linear reads), on every store path: an in-place residual add with
     bias and the copy; the fp32 output within the epilogue bound, and the
@@ -280,7 +299,8 @@ def test_epilogue_bf16_copy_every_path(gpu, orc, fmt, xdt, M, N, K):
     Xd = dev_x(torch, X, xdt)
     Y = dev_f32(torch, resid)
     copy = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
-    ql.forward_ep(fmt, Xd, cd, sd, N, Y=Y, bias=dev_f32(torch, bias), residual=Y, ycopy=copy)
+    with ql.forced_path(path):
+        ql.forward_ep(fmt, Xd, cd, sd, N, Y=Y, bias=dev_f32(torch, bias), residual=Y, ycopy=copy)
     torch.cuda.synchronize()
     Yg = host_y(torch, Y)
     check(Yg, Pr, orc.epilogue(Pr, bias, O.ACT_NONE, resid), bias, xdt, False, (M, N, K))
@@ -340,7 +360,8 @@ def test_block_forward_ep_in_kernel_reduction(gpu, orc):
             Yr = orc.epilogue(Pr, bias, act, None if resid is None else resid[rows])
             refs.append((Pr, Yr, bias, ybf16))
         g = ql.make_group_ep(entries)
-        ql.block_forward_ep(None, group=g)
+        with ql.forced_path(ql.PATH_WIDE):
+            ql.block_forward_ep(None, group=g)
         torch.cuda.synchronize()
         first = [e[5].clone() for e in entries] + [copy.clone()]
         for e, (Pr, Yr, bias, yb) in zip(entries, refs):
@@ -355,7 +376,8 @@ def test_block_forward_ep_in_kernel_reduction(gpu, orc):
             else:
                 e[5].fill_(float("nan"))
         copy.fill_(-1)
-        ql.block_forward_ep(None, group=g)
+        with ql.forced_path(ql.PATH_WIDE):
+            ql.block_forward_ep(None, group=g)
         torch.cuda.synchronize()
         again = [e[5] for e in entries] + [copy]
         assert all(torch.equal(a_, b_) for a_, b_ in zip(first, again)), fmt

@@ -10,6 +10,7 @@ sums: element by element |Y - Y_ref| <= (K / 32 + 32 + 16) * 2^-24 *
 import numpy as np
 import pytest
 
+import kgroup_cases as cases
 import synth_inputs as si
 from oracle import oracle as O
 
@@ -35,11 +36,8 @@ def run(gpu, fmt, X, codes, scales, N, **ep):
 
 
 # rows around every staging size and row tile, columns around 32, 64 and 128
-# and not a multiple of 4, one stage and a half-filled last stage (K = 256,
-# 768, 1280), long K
-@pytest.mark.parametrize("M,N,K", [(4, 33, 256), (8, 300, 8192), (9, 65, 768), (24, 1000, 4096), (16, 129, 1024),
-                                   (17, 7, 512), (32, 1000, 1280), (33, 31, 256), (64, 130, 768),
-                                   (65, 258, 2048), (129, 4100, 512), (257, 96, 1024)])
+# and not a multiple of 4, one stage and a half-filled last stage, long K
+@pytest.mark.parametrize("M,N,K", cases.SINGLES)
 @pytest.mark.parametrize("fmt", [O.FMT_Q4, O.FMT_INT8])
 def test_kgroup_shapes(gpu, orc, fmt, M, N, K):
     torch, ql = gpu
@@ -56,8 +54,7 @@ def test_kgroup_shapes(gpu, orc, fmt, M, N, K):
     assert np.all(np.abs(Yg - Yt) <= 2 * B + 1e-30)
 
 
-@pytest.mark.parametrize("M,N,K", [(1, 33, 256), (16, 65, 768), (17, 300, 1280), (64, 1024, 1024),
-                                   (70, 131, 512), (214, 4608, 512)])
+@pytest.mark.parametrize("M,N,K", cases.SINGLES_F32_F16)
 @pytest.mark.parametrize("kind", ["q4 f32", "int8 f32", "f16"])
 def test_kgroup_fp32_and_fp16(gpu, orc, kind, M, N, K):
     """fp32 activations (three exact bf16 planes, six MFMAs per block) and fp16
@@ -80,6 +77,39 @@ def test_kgroup_fp32_and_fp16(gpu, orc, kind, M, N, K):
     Y = ql.forward(fmt, xd, dv(codes), None if f16 else dv(scales.view(np.int16)), N)
     torch.cuda.synchronize()
     assert np.all(np.abs(Y.cpu().numpy().astype(np.float64) - Yr) <= B + 1e-30)
+
+
+@pytest.mark.parametrize("fmt,f32,M,layers,shapes", cases.GROUPS)
+def test_kgroup_every_shape(gpu, orc, fmt, f32, M, layers, shapes):
+    """Groups that cover every shape of every launch (kgroup_cases.py), every
+    output NaN-filled, element by element within the bound above (fp32 X: 96
+    products per block); a second call repeats the first bit for bit."""
+    torch, ql = gpu
+    dv = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    xdt = O.DT_F32 if f32 else O.DT_BF16
+    ents, refs = [], []
+    for i, (N, K) in enumerate(layers):
+        W, X = si.small_case(8700 + i + M + N + K, M, N, K, xdt)
+        x = X if f32 else si.bf16_bits_to_f32(X)
+        if fmt == cases.F16:
+            codes, scales = W.astype(np.float16), None
+            Wd = codes.astype(np.float64)
+        else:
+            codes, scales = orc.quantize(fmt, W)
+            Wd = orc.dequantize(fmt, codes, scales, N, K)
+        Y = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+        ents.append((fmt, dv(X if f32 else X.view(np.int16)), dv(codes),
+                     None if scales is None else dv(scales.view(np.int16)), N, Y))
+        A = np.abs(x).astype(np.float64) @ np.abs(Wd).T
+        refs.append((x.astype(np.float64) @ Wd.T, (K // 32 + 112) * 2.0 ** -24 * A + 1e-30))
+    ql.block_forward(ents)
+    torch.cuda.synchronize()
+    first = [e[5].clone() for e in ents]
+    ql.block_forward(ents)
+    torch.cuda.synchronize()
+    for e, Y1, (Yr, B), nk in zip(ents, first, refs, layers):
+        assert torch.equal(e[5], Y1), nk
+        assert np.all(np.abs(Y1.cpu().numpy().astype(np.float64) - Yr) <= B), nk
 
 
 @pytest.mark.parametrize("M", [7, 30, 107])

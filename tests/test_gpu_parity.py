@@ -59,11 +59,19 @@ def quantize_both(gpu, orc, fmt, W):
     return cr, sr
 
 
-def forward_gpu(gpu, fmt, X, xdt, codes, scales, N):
+# Forced paths (qlinear_force_path).  A test that is about one kernel forces
+# it, so that a change of the library's own choice cannot take the test's
+# shapes elsewhere; what the choice itself must be is checked on the CPU
+# (test_planner_cpu.py, which imports the shapes below).
+AUTO, GEMV, STREAM, SKINNY, TILED, WIDE, MID = range(7)
+
+
+def forward_gpu(gpu, fmt, X, xdt, codes, scales, N, path=AUTO):
     torch, ql = gpu
     cd = torch.from_numpy(codes).cuda()
     sd = torch.from_numpy(scales.view(np.int16)).cuda()
-    Y = ql.forward(fmt, dev_x(torch, X, xdt), cd, sd, N)
+    with ql.forced_path(path):
+        Y = ql.forward(fmt, dev_x(torch, X, xdt), cd, sd, N)
     torch.cuda.synchronize()
     return Y.cpu().numpy()
 
@@ -134,22 +142,27 @@ def test_forward_ragged(gpu, orc, fmt, xdt, N, K):
 
 @pytest.mark.parametrize("fmt", [O.FMT_INT8, O.FMT_Q4])
 def test_forward_large_m_ragged_tiles(gpu, orc, fmt):
-    """The large-M bf16 path (M > 64, K % 256 == 0) at row and column counts
+    """The large-M bf16 path (K % 256 == 0) at row and column counts
     that leave partial 128 x 256 tiles, several K steps (odd and even ring
     positions) and one-step K."""
     for (M, N, K) in ((65, 200, 512), (130, 256, 768), (257, 300, 256), (300, 520, 1280),
                       (129, 17, 1024)):
         W, X = si.small_case(70 + M + N + K + fmt, M, N, K)
         codes, scales = quantize_both(gpu, orc, fmt, W)
-        Yg = forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N)
+        Yg = forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N, WIDE)
         Yr = orc.forward(fmt, X, O.DT_BF16, codes, scales, N)
         e = rel_err(Yg, Yr)
         assert e <= TOL[O.DT_BF16], (M, N, K, e)
 
 
+MID_CASES = [(65, 130, 256), (100, 129, 8192), (128, 2048, 2048), (129, 300, 1024),
+             (200, 1000, 4096), (214, 1027, 1536), (256, 6144, 1536), (97, 8192, 512),
+             (33, 520, 2048), (48, 2049, 8192), (64, 300, 768)]
+
+
 @pytest.mark.parametrize("fmt", [O.FMT_INT8, O.FMT_Q4])
 def test_forward_mid_m(gpu, orc, fmt):
-    """The mid-M exact kernel (32 < M <= 256, K % 256 == 0): partial
+    """The mid-M exact kernel (K % 256 == 0): partial
     128 x 128 tiles in both directions (a single row tile below 65 rows),
     one-chunk and long reductions, K
     parts summed by a second launch (up to 16 parts), the paper's 214-token
@@ -157,10 +170,7 @@ def test_forward_mid_m(gpu, orc, fmt):
     form: within 1e-5 of the oracle; every output written (Y starts as NaN);
     results repeat bit for bit."""
     torch, ql = gpu
-    cases = [(65, 130, 256), (100, 129, 8192), (128, 2048, 2048), (129, 300, 1024),
-             (200, 1000, 4096), (214, 1027, 1536), (256, 6144, 1536), (97, 8192, 512),
-             (33, 520, 2048), (48, 2049, 8192), (64, 300, 768)]
-    for M, N, K in cases:
+    for M, N, K in MID_CASES:
         W, X = si.small_case(90 + M + N + K + fmt, M, N, K)
         codes, scales = quantize_both(gpu, orc, fmt, W)
         cd = torch.from_numpy(codes).cuda()
@@ -169,7 +179,8 @@ def test_forward_mid_m(gpu, orc, fmt):
         outs = []
         for _ in range(2):
             Y = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
-            ql.forward(fmt, xd, cd, sd, N, Y)
+            with ql.forced_path(ql.PATH_MID):
+                ql.forward(fmt, xd, cd, sd, N, Y)
             torch.cuda.synchronize()
             outs.append(Y.cpu().numpy())
         assert np.isfinite(outs[0]).all(), (M, N, K)
@@ -177,6 +188,11 @@ def test_forward_mid_m(gpu, orc, fmt):
         e = rel_err(outs[0], Yr)
         assert e <= 1e-5, (M, N, K, e)
         assert np.array_equal(outs[0], outs[1]), (M, N, K)
+
+
+# name: (M, N, K), forced path
+REPLAY_CASES = {"mid": ((128, 2048, 2048), MID), "wide": ((640, 1024, 4096), WIDE),
+                "ext": ((100, 129, 8192), MID)}
 
 
 def test_mid_split_graph_replay(gpu, orc):
@@ -187,9 +203,8 @@ def test_mid_split_graph_replay(gpu, orc):
     result bit for bit every time."""
     torch, ql = gpu
     fmt = O.FMT_Q4
-    shapes = {"mid": (128, 2048, 2048), "wide": (640, 1024, 4096), "ext": (100, 129, 8192)}
     data = {}
-    for name, (M, N, K) in shapes.items():
+    for name, ((M, N, K), _) in REPLAY_CASES.items():
         W, X = si.small_case(500 + M + N + K, M, N, K)
         codes, scales = orc.quantize(fmt, W)
         data[name] = (dev_x(torch, X, O.DT_BF16), torch.from_numpy(codes).cuda(),
@@ -198,7 +213,8 @@ def test_mid_split_graph_replay(gpu, orc):
 
     def run(name):
         xd, cd, sd, N, Y, _ = data[name]
-        ql.forward(fmt, xd, cd, sd, N, Y)
+        with ql.forced_path(REPLAY_CASES[name][1]):
+            ql.forward(fmt, xd, cd, sd, N, Y)
 
     s = torch.cuda.Stream()
     torch.cuda.synchronize()
@@ -226,8 +242,9 @@ def test_mid_split_graph_replay(gpu, orc):
 
 @pytest.mark.parametrize("fmt", [O.FMT_INT8, O.FMT_Q4])
 def test_forward_streaming_ragged(gpu, orc, fmt):
-    """The weight-streaming path (M <= 32, K % 256 == 0; M <= 4 goes to the
-    GEMV when it fits): row counts around its 8- to 64-row workgroups,
+    """The weight-streaming path (M <= 32, K % 256 == 0), and the same calls as
+    the library chooses (most stay there; M <= 4 goes to the GEMV when it
+    fits): row counts around its 8- to 64-row workgroups,
     K lengths that leave some wavefronts or K parts short or empty and that
     cross the 32-block scale runs, activation stages of 8, 16 and 32 rows,
     and long reductions cut into K parts summed by a second launch (results
@@ -241,12 +258,14 @@ def test_forward_streaming_ragged(gpu, orc, fmt):
     for M, N, K in cases:
         W, X = si.small_case(80 + M + N + K + fmt, M, N, K)
         codes, scales = quantize_both(gpu, orc, fmt, W)
-        Yg = forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N)
         Yr = orc.forward(fmt, X, O.DT_BF16, codes, scales, N)
-        e = rel_err(Yg, Yr)
-        assert e <= TOL[O.DT_BF16], (M, N, K, e)
-        if K >= 4096:
-            assert np.array_equal(Yg, forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N))
+        for path in (AUTO, STREAM):
+            Yg = forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N, path)
+            e = rel_err(Yg, Yr)
+            assert e <= TOL[O.DT_BF16], (M, N, K, path, e)
+            if K >= 4096:
+                assert np.array_equal(Yg, forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N,
+                                                      path))
 
 
 @pytest.mark.parametrize("fmt", [O.FMT_INT8, O.FMT_Q4])
@@ -259,7 +278,7 @@ def test_forward_gemv_shapes(gpu, orc, fmt):
                       (1, 8191, 8192), (4, 300, 8192), (2, 64, 6144), (3, 5, 7936)):
         W, X = si.small_case(40 + M + N + K + fmt, M, N, K)
         codes, scales = quantize_both(gpu, orc, fmt, W)
-        Yg = forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N)
+        Yg = forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N, GEMV)
         Yr = orc.forward(fmt, X, O.DT_BF16, codes, scales, N)
         e = rel_err(Yg, Yr)
         assert e <= TOL[O.DT_BF16], (M, N, K, e)
@@ -274,7 +293,7 @@ def test_forward_long_rows(gpu, orc, K):
     for fmt in (O.FMT_INT8, O.FMT_Q4):
         W, X = si.small_case(40 + K + fmt, M, N, K)
         codes, scales = quantize_both(gpu, orc, fmt, W)
-        Yg = forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N)
+        Yg = forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N, WIDE)
         Yr = orc.forward(fmt, X, O.DT_BF16, codes, scales, N)
         assert rel_err(Yg, Yr) <= TOL[O.DT_BF16], (fmt, K)
 
@@ -282,25 +301,26 @@ def test_forward_long_rows(gpu, orc, K):
 @pytest.mark.parametrize("fmt", [O.FMT_INT8, O.FMT_Q4])
 def test_forward_row_scales_far_apart(gpu, orc, fmt):
     """Activation rows scaled by 2^-100 .. 2^100 (and one all-zero row): each
-    row's own relative error stays within the tolerance, on the small-M path
+    row's own relative error stays within the tolerance, as the library chooses
     and on the large-M path (per-row power-of-two shifts)."""
     rng = np.random.default_rng(91 + fmt)
     N, K = 96, 256
-    for M in (40, 200):
+    for M, path in ((40, AUTO), (200, AUTO), (200, WIDE)):
         W, X0 = si.small_case(92 + M + fmt, M, N, K, O.DT_F32)
         e = rng.integers(-100, 101, M).astype(np.float64)
         Xf = (X0.astype(np.float64) * 2.0 ** e[:, None]).astype(np.float32)
         Xf[M // 2] = 0.0
         X = si.f32_to_bf16_bits(Xf)
         codes, scales = quantize_both(gpu, orc, fmt, W)
-        Yg = forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N).astype(np.float64)
+        Yg = forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N,
+                         path).astype(np.float64)
         Yr = orc.forward(fmt, X, O.DT_BF16, codes, scales, N)
         assert np.all(Yg[M // 2] == 0.0)
         for m in range(M):
             if m == M // 2:
                 continue
             err = np.max(np.abs(Yg[m] - Yr[m])) / np.max(np.abs(Yr[m]))
-            assert err <= TOL[O.DT_BF16], (M, m, err)
+            assert err <= TOL[O.DT_BF16], (M, path, m, err)
 
 
 @pytest.mark.parametrize("fmt", [O.FMT_INT8, O.FMT_Q4])
@@ -308,8 +328,8 @@ def test_forward_block_scales_far_apart(gpu, orc, fmt):
     """Weight rows whose blocks lie many binary decades apart (block
     magnitudes 2^-20 .. 2^16 within one row, rows whose largest block
     exceeds 2^15 so that the large-M path shifts them down, rows of tiny
-    blocks only), on the exact small-M path (M = 40) and the folded large-M
-    path (M = 200).
+    blocks only), on exact kernels (M = 40 and 200, as the library chooses) and
+    the folded large-M path (M = 200).
 
     Bound, element by element: the large-M path enters each weight as
     fp16(c * s') with s' = s * 2^f and f set by the row's largest scale.
@@ -333,16 +353,17 @@ def test_forward_block_scales_far_apart(gpu, orc, fmt):
     codes, scales = quantize_both(gpu, orc, fmt, W)
     Wd = orc.dequantize(fmt, codes, scales, N, K)
     smax = np.max(np.abs(Wd), axis=1) / Q
-    for M in (40, 200):
+    for M, path in ((40, AUTO), (200, AUTO), (200, WIDE)):
         X = si.small_case(3200 + M + fmt, M, 1, K)[1]
         Xv = si.bf16_bits_to_f32(X).astype(np.float64)
-        Yg = forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N).astype(np.float64)
+        Yg = forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N,
+                         path).astype(np.float64)
         Yr = orc.forward(fmt, X, O.DT_BF16, codes, scales, N)
         A = np.abs(Xv) @ np.abs(Wd).T
         lim = (2.0 ** -11 + (K + 8) * 2.0 ** -24) * A + \
             (Q + 2) * Q * 2.0 ** -39 * np.outer(np.abs(Xv).sum(axis=1), smax)
         bad = np.argwhere(np.abs(Yg - Yr) > lim)
-        assert len(bad) == 0, (M, bad[:5], (Yg - Yr)[tuple(bad[0])], lim[tuple(bad[0])])
+        assert len(bad) == 0, (M, path, bad[:5], (Yg - Yr)[tuple(bad[0])], lim[tuple(bad[0])])
         assert rel_err(Yg, Yr) <= TOL[O.DT_BF16]
 
 
@@ -388,34 +409,43 @@ def test_forward_stored_extreme_codes_exact(gpu, orc, fmt):
         assert np.array_equal(Yg.astype(np.int64), Xi.astype(np.int64) @ C.T)
 
 
+IN_KERNEL_M, IN_KERNEL_NK = (768, 700), (2048, 2048)
+
+
 @pytest.mark.parametrize("fmt", [O.FMT_INT8, O.FMT_Q4])
 def test_forward_in_kernel_reduction(gpu, orc, fmt):
-    """Single layers whose split plan adds the K parts inside the large-M
-    kernel (more parts than one wave of workgroups: 700 or 768 tokens x 2048
+    """Single layers whose split plan on the large-M kernel adds the K parts
+    inside it (more parts than one wave of workgroups: 700 or 768 tokens x 2048
     x 2048, 6 x 8 output tiles in 4 parts of 8 steps each; each part stores
     its partial tile and the last part to arrive adds them in part order).
     Every output starts NaN-filled; all rows against the oracle (700: a
     ragged last row tile); a second call repeats the first bit for bit."""
     torch, ql = gpu
-    N, K = 2048, 2048
+    N, K = IN_KERNEL_NK
     W, _ = si.small_case(3600 + fmt, 1, N, K)
     codes, scales = quantize_both(gpu, orc, fmt, W)
     cd = torch.from_numpy(codes).cuda()
     sd = torch.from_numpy(scales.view(np.int16)).cuda()
-    for M in (768, 700):
+    for M in IN_KERNEL_M:
         _, X = si.small_case(3610 + M, M, 1, K)
         Xd = dev_x(torch, X, O.DT_BF16)
         Y = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
-        ql.forward(fmt, Xd, cd, sd, N, Y)
+        with ql.forced_path(ql.PATH_WIDE):
+            ql.forward(fmt, Xd, cd, sd, N, Y)
         torch.cuda.synchronize()
         assert bool(torch.isfinite(Y).all()), M
         Yg = Y.cpu().numpy()
         Yr = orc.forward(fmt, X, O.DT_BF16, codes, scales, N)
         assert rel_err(Yg, Yr) <= TOL[O.DT_BF16], M
         Y.fill_(float("nan"))
-        ql.forward(fmt, Xd, cd, sd, N, Y)
+        with ql.forced_path(ql.PATH_WIDE):
+            ql.forward(fmt, Xd, cd, sd, N, Y)
         torch.cuda.synchronize()
         assert np.array_equal(Y.cpu().numpy(), Yg), M
+
+
+SPLIT_CASES = ((300, 520, 4096), (129, 260, 8448), (2048, 64, 2304))
+SPLIT_GROUP = (384, [(700, 512), (256, 4096), (1000, 512)])  # M, (N, K)
 
 
 @pytest.mark.parametrize("fmt", [O.FMT_INT8, O.FMT_Q4])
@@ -427,18 +457,17 @@ def test_forward_split_reduction(gpu, orc, fmt):
     (K / 64 not a multiple of the part length), ragged tiles; results repeat
     bit for bit.  The in-kernel reduction has tests of its own."""
     torch, ql = gpu
-    for (M, N, K) in ((300, 520, 4096), (129, 260, 8448), (2048, 64, 2304)):
+    for (M, N, K) in SPLIT_CASES:
         W, X = si.small_case(90 + M + N + K + fmt, M, N, K)
         codes, scales = quantize_both(gpu, orc, fmt, W)
-        Yg = forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N)
+        Yg = forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N, WIDE)
         Yr = orc.forward(fmt, X, O.DT_BF16, codes, scales, N)
         assert rel_err(Yg, Yr) <= TOL[O.DT_BF16], (M, N, K)
-        assert np.array_equal(Yg, forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N))
+        assert np.array_equal(Yg, forward_gpu(gpu, fmt, X, O.DT_BF16, codes, scales, N, WIDE))
     # one grouped launch: short and long reductions over two activations
-    M = 384
+    M, shapes = SPLIT_GROUP
     _, xa = si.small_case(95, M, 1, 512)
     _, xb = si.small_case(96, M, 1, 4096)
-    shapes = [(700, 512), (256, 4096), (1000, 512)]
     entries, refs = [], []
     for i, (N, K) in enumerate(shapes):
         W, _ = si.small_case(97 + i, 1, N, K)
@@ -448,7 +477,8 @@ def test_forward_split_reduction(gpu, orc, fmt):
         Y = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
         entries.append((fmt, dev_x(torch, X, O.DT_BF16), cd, sd, N, Y))
         refs.append(orc.forward(fmt, X, O.DT_BF16, cr, sr, N))
-    ql.block_forward(entries)
+    with ql.forced_path(ql.PATH_WIDE):
+        ql.block_forward(entries)
     torch.cuda.synchronize()
     for e, Yr in zip(entries, refs):
         assert rel_err(e[5].cpu().numpy(), Yr) <= TOL[O.DT_BF16]
@@ -479,6 +509,9 @@ def test_forward_on_side_stream(gpu, orc):
     assert e <= TOL[O.DT_BF16]
 
 
+WORKSPACE_CASES = (300, 520, 1024), (640, 1024, 4096)  # on the large-M kernel
+
+
 def test_forward_graph_workspace(gpu, orc):
     """Captured graphs and the per-stream workspace.  A graph captured on a
     stream whose workspace an eager call has sized keeps that buffer when a
@@ -488,7 +521,7 @@ def test_forward_graph_workspace(gpu, orc):
     result bit for bit."""
     torch, ql = gpu
     fmt = O.FMT_Q4
-    small, large = (300, 520, 1024), (640, 1024, 4096)
+    small, large = WORKSPACE_CASES
     data = {}
     for (M, N, K) in (small, large):
         W, X = si.small_case(300 + M + K, M, N, K)
@@ -501,7 +534,8 @@ def test_forward_graph_workspace(gpu, orc):
 
     def run(shape, Y):
         xd, cd, sd, _ = data[shape]
-        ql.forward(fmt, xd, cd, sd, shape[1], Y)
+        with ql.forced_path(ql.PATH_WIDE):
+            ql.forward(fmt, xd, cd, sd, shape[1], Y)
 
     s, s2 = torch.cuda.Stream(), torch.cuda.Stream()
     torch.cuda.synchronize()
@@ -847,12 +881,14 @@ def skinny_block():
 
 
 @pytest.mark.parametrize("fmt", [O.FMT_INT8, O.FMT_Q4])
-@pytest.mark.parametrize("M", [1, 3, 8, 32])
-def test_block_forward_few_rows_grouped(gpu, orc, skinny_block, fmt, M):
+@pytest.mark.parametrize("M,path", [(1, AUTO), (3, AUTO), (8, AUTO), (8, STREAM), (32, AUTO),
+                                    (32, STREAM)])
+def test_block_forward_few_rows_grouped(gpu, orc, skinny_block, fmt, M, path):
     """One block's four linears (QKV 2048->6144, out, FFN-up 2048->8192,
-    FFN-down 8192->2048) at the few-row sizes: the GEMV (M <= 4) and the
-    streaming kernel (M <= 32) each take the four layers in one launch, the
-    streaming kernel's K-split layers share one sum launch.  Every output
+    FFN-down 8192->2048) at the few-row sizes: the GEMV (M <= 4), the
+    streaming kernel (forced) and the K-group kernel (the choice at 8 and 32
+    rows) each take the four layers in one launch, the streaming kernel's
+    K-split layers share one sum launch.  Every output
     NaN-filled beforehand, every row against the oracle; a second call
     repeats the first bit for bit."""
     torch, ql = gpu
@@ -867,15 +903,21 @@ def test_block_forward_few_rows_grouped(gpu, orc, skinny_block, fmt, M):
         Y = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
         entries.append((fmt, dev_x(torch, X, O.DT_BF16), cd, sd, N, Y))
         host.append((X, host_codes(cd), host_scales(sd), N))
-    ql.block_forward(entries)
-    torch.cuda.synchronize()
-    first = [e[5].clone() for e in entries]
-    ql.block_forward(entries)
-    torch.cuda.synchronize()
+    with ql.forced_path(path):
+        ql.block_forward(entries)
+        torch.cuda.synchronize()
+        first = [e[5].clone() for e in entries]
+        ql.block_forward(entries)
+        torch.cuda.synchronize()
     for e, Y1, (X, cr, sr, N) in zip(entries, first, host):
         assert torch.equal(e[5], Y1)
         Yr = orc.forward(fmt, X, O.DT_BF16, cr, sr, N)
         assert rel_err(e[5].cpu().numpy(), Yr) <= 1e-5, (M, N)
+
+
+# (M, N, K) of one call
+MIXED_ROWS = [(1, 300, 2048), (3, 257, 8192), (1, 64, 512), (9, 500, 8192), (30, 1000, 4096),
+              (3, 1000, 512)]
 
 
 def test_block_forward_few_rows_mixed_m(gpu, orc):
@@ -883,8 +925,7 @@ def test_block_forward_few_rows_mixed_m(gpu, orc):
     row counts (two launches), streaming layers of two row counts in one
     launch (activation stage of the larger), some with K parts."""
     torch, ql = gpu
-    specs = [(1, 300, 2048), (4, 257, 8192), (1, 64, 512), (9, 500, 8192), (30, 129, 1024),
-             (4, 1000, 256)]
+    specs = MIXED_ROWS
     for fmt in (O.FMT_INT8, O.FMT_Q4):
         entries, refs = [], []
         for i, (M, N, K) in enumerate(specs):
@@ -903,11 +944,10 @@ def test_block_forward_few_rows_mixed_m(gpu, orc):
 def test_tiled_kernel_k_parts(gpu, orc, fmt):
     """The tiled exact kernel cuts long reductions into K parts when a call
     has too few tiles for the GPU (partials added by the sum launch): fp32
-    activations at the single-linear workload's shape (64 x 1024 x 1024),
-    an odd block count (the last 64-k step is half a step) in the last
-    part, bf16 mid-M shapes forced onto the tiled kernel, and a split layer
-    with its epilogue applied by the sum launch.  Results repeat bit for
-    bit."""
+    activations (64 x 1024 x 1024), an odd block count (the last 64-k step is
+    half a step) in the last part, bf16 mid-M shapes, all forced onto the tiled
+    kernel, and a split layer with its epilogue applied by the sum launch.
+    Results repeat bit for bit."""
     torch, ql = gpu
     cases = [(64, 1024, 1024, O.DT_F32), (40, 512, 2080, O.DT_F32), (7, 300, 4128, O.DT_F32),
              (128, 2048, 8192, O.DT_BF16), (214, 1024, 4096, O.DT_BF16),
@@ -916,12 +956,13 @@ def test_tiled_kernel_k_parts(gpu, orc, fmt):
         for (M, N, K, xdt) in cases:
             W, X = si.small_case(7500 + M + N + K + fmt, M, N, K, xdt)
             codes, scales = quantize_both(gpu, orc, fmt, W)
-            ql.load().qlinear_force_path(ql.PATH_TILED if xdt == O.DT_BF16 else ql.PATH_AUTO)
-            Yg = forward_gpu(gpu, fmt, X, xdt, codes, scales, N)
+            Yg = forward_gpu(gpu, fmt, X, xdt, codes, scales, N, TILED)
             Yr = orc.forward(fmt, X, xdt, codes, scales, N)
             assert rel_err(Yg, Yr) <= (1e-5 if xdt == O.DT_F32 else 2e-6), (M, N, K, rel_err(Yg, Yr))
-            assert np.array_equal(Yg, forward_gpu(gpu, fmt, X, xdt, codes, scales, N))
+            assert np.array_equal(Yg, forward_gpu(gpu, fmt, X, xdt, codes, scales, N,
+                                                  TILED))
         # a split layer with bias, GELU and a residual, applied after the sum
+        ql.load().qlinear_force_path(ql.PATH_TILED)
         M, N, K = 64, 1024, 1024
         W, X = si.small_case(7600 + fmt, M, N, K, O.DT_F32)
         codes, scales = quantize_both(gpu, orc, fmt, W)

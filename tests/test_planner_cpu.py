@@ -26,6 +26,11 @@ import subprocess
 import numpy as np
 import pytest
 
+import kgroup_cases
+import test_gpu_epilogue
+import test_gpu_parity
+import test_zz_no_alloc
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 BUILD = os.path.join(ROOT, "paper_2607_08526_amd", "_build")
@@ -247,6 +252,65 @@ def test_forced_paths_reach_their_kernels(probe):
         got = routes(probe, [(F16, 0, 0, p, one(M)) for p in range(1, 7)])
         assert [g for g in got[:4] + got[5:]] == auto * 5
         assert got[4][0] in ("wide", "wideext")
+
+
+def test_kgroup_cases_run_the_kgroup_kernel(probe):
+    """The calls that test_gpu_kgroup.py makes, and the shapes they take."""
+    groups = [((f, x, 0, AUTO, [(M, N, K) for N, K in ls]), sh)
+              for f, x, M, ls, sh in kgroup_cases.GROUPS]
+    for (c, sh), (kernel, v) in zip(groups, routes(probe, [c for c, _ in groups])):
+        assert kernel == "kg" and [s for _, s in v] == sh, (c, kernel, v)
+    singles = [(f, 0, 0, AUTO, [c]) for f in (Q4, INT8) for c in kgroup_cases.SINGLES]
+    singles += [(f, x, 0, AUTO, [c]) for f, x in ((Q4, 1), (INT8, 1), (F16, 0))
+                for c in kgroup_cases.SINGLES_F32_F16]
+    singles += [(f, 1, 0, AUTO, [(64, 1024, 1024)]) for f in (Q4, INT8)]  # large activations
+    singles += [(Q4, 0, 1, AUTO, [(M, N, K) for N, K in block(512)]) for M in (7, 30, 107)]
+    for c, (kernel, v) in zip(singles, routes(probe, singles)):
+        assert kernel == "kg", (c, kernel)
+
+
+def test_gpu_tests_reach_what_they_are_for(probe):
+    """The kernels, K parts and sum launches of GPU tests that are about them."""
+    par, ep = test_gpu_parity, test_gpu_epilogue
+    for fmt in (Q4, INT8):
+        one = lambda path, M, N, K, epi=0: (fmt, 0, epi, path, [(M, N, K)])
+        M, ls = par.SPLIT_GROUP
+        want = [(one(WIDE, M_, *par.IN_KERNEL_NK), "wide", [4]) for M_ in par.IN_KERNEL_M]
+        want += [(one(WIDE, *c), "wideext", None) for c in par.SPLIT_CASES]
+        want += [((fmt, 0, 0, WIDE, [(M, N, K) for N, K in ls]), "wideext", [16, 2, 2])]
+        want += [(one(p, *c), "mid" if p == MID else "wideext", None)
+                 for c, p in par.REPLAY_CASES.values()]
+        want += [(one(MID, *c), "mid", None) for c in par.MID_CASES]
+        want += [(one(WIDE, *c), "wideext", None) for c in par.WORKSPACE_CASES]
+        want += [((fmt, 0, 1, WIDE, [(384, N, K) for N, K in ep.ROUTED_GROUP]), "wideext",
+                  [16, 16, 2, 2]),
+                 ((fmt, 0, 1, AUTO, [(768, N, K) for N, K in block(1024)]), "wide", [4, 2, 2, 2]),
+                 ((fmt, 0, 0, AUTO, par.MIXED_ROWS), "rows", [0, 0, 0, 1, 1, 0])]
+        for M in (1, 3):
+            want.append(((fmt, 0, 0, AUTO, [(M, N, K) for N, K in block(2048)]), "rows", [0] * 4))
+        for M in (8, 32):
+            want.append(((fmt, 0, 0, AUTO, [(M, N, K) for N, K in block(2048)]), "kg", None))
+        for (c, kernel, v), (k, got) in zip(want, routes(probe, [c for c, _, _ in want])):
+            assert k == kernel, (c, k)
+            assert v is None or [x for _, x in got] == v, (c, got)
+            if k in ("mid", "wideext") and c[4] != [(65, 130, 256)] and v is None:
+                assert all(x > 1 or K < 1024 for K, x in got), (c, got)  # parts, in a workspace
+    names = {ep.GEMV: ("rows", 0), ep.STREAM: ("rows", 1), ep.SKINNY: ("rows", 2),
+             ep.TILED: ("tiled", None), ep.WIDE: ("wide", None), ep.MID: ("mid", None),
+             ep.AUTO: ("kg", None)}
+    calls = [(f, x == 0, 1, p, [(M, N, K)]) for f, x, M, N, K, p in ep.PATHS]
+    for c, (k, v) in zip(calls, routes(probe, calls)):
+        kernel, which = names[c[3]]
+        assert k.startswith(kernel) and (which is None or v[0][1] == which), (c, k, v)
+    calls = [(Q4, 0, 1, p, [(M, N, K) for N, K in ls]) for M, ls, p in ep.EP_GROUPS]
+    assert [k for k, _ in routes(probe, calls)] == ["wideext", "kg", "rows", "kg"]
+    # the static scratch is used: pre-pass copies and partials, then partials
+    (f0, d0, M0, p0), (f1, d1, M1, p1) = test_zz_no_alloc.TWO_CALLS
+    got = routes(probe, [(f0, 0, 1, p0, [(M0, N, K) for N, K in block(d0)]),
+                         (f1, 0, 1, p1, [(M1, N, K) for N, K in block(d1)])])
+    assert [k for k, _ in got] == ["wideext", "rows"] and max(v for _, v in got[0][1]) > 1
+    t = probe([f"stream {f1} {M1} " + " ".join(f"{N} {K}" for N, K in block(d1))])[0]
+    assert max(map(int, t[5::3])) > 1, t
 
 
 def test_one_stage_layers_at_few_rows(probe):

@@ -71,15 +71,16 @@ def entries_for(gpu, xs, layers, fmt, M):
     return out
 
 
-def run_both(gpu, orc, fmt, d, M, seed, check_rows):
+def run_both(gpu, orc, fmt, d, M, seed, check_rows, path):
     torch, ql = gpu
     xs, layers = block(gpu, orc, fmt, d, M, seed)
     ref = entries_for(gpu, xs, layers, fmt, M)
-    ql.block_forward_ep(ref)
-    torch.cuda.synchronize()
     got = entries_for(gpu, xs, layers, fmt, M)
-    ql.block_forward_ep_noalloc(got)
-    torch.cuda.synchronize()
+    with ql.forced_path(path):
+        ql.block_forward_ep(ref)
+        torch.cuda.synchronize()
+        ql.block_forward_ep_noalloc(got)
+        torch.cuda.synchronize()
     rows = check_rows
     for (name, N, K, codes, scales, (bias, act, resid, ydt)), e_ref, e_got in zip(layers, ref, got):
         Yref, Ygot = e_ref[5], e_got[5]
@@ -97,13 +98,21 @@ def run_both(gpu, orc, fmt, d, M, seed, check_rows):
         assert np.all(np.abs(Yg - Yr) <= bound), name
 
 
+# format, d, M, forced path (5 the large-M kernel, 2 the streaming kernel)
+TWO_CALLS = [(O.FMT_Q4, 1024, 300, 5), (O.FMT_INT8, 1024, 8, 2)]
+
+
 def test_no_alloc_matches_pool_entry_two_calls(gpu, orc):
-    """First call: a block at d = 1024 and 300 tokens (the large-M path,
-    pre-pass copies and split partials in the scratch).  Second call, smaller:
-    the same block shape at 8 tokens (the streaming kernel with K parts summed
-    by a second launch, partials in the scratch)."""
-    run_both(gpu, orc, O.FMT_Q4, 1024, 300, 11, np.array([0, 1, 77, 128, 200, 255, 299]))
-    run_both(gpu, orc, O.FMT_INT8, 1024, 8, 12, np.arange(8))
+    """First call: a block at d = 1024 and 300 tokens on the large-M kernel
+    (pre-pass copies and split partials in the scratch).  Second call, smaller: the
+    same block shape at 8 tokens on the streaming kernel (K parts summed by a
+    second launch, partials in the scratch).  Then both as the library
+    chooses."""
+    rows = {300: np.array([0, 1, 77, 128, 200, 255, 299]), 8: np.arange(8)}
+    for seed, (fmt, d, M, path) in enumerate(TWO_CALLS, 11):
+        run_both(gpu, orc, fmt, d, M, seed, rows[M], path)
+    for seed, (fmt, d, M, _) in enumerate(TWO_CALLS, 11):
+        run_both(gpu, orc, fmt, d, M, seed, rows[M], 0)
 
 
 def test_no_alloc_refuses_oversized_workspace(gpu, orc):
