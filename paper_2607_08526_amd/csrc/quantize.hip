@@ -51,15 +51,17 @@ __device__ inline uint32_t scale_bits(float amax)
 }
 
 // The integer nearest to w / s, ties to even, clamped to [-Q, Q], for s > 0 an
-// fp16 value, |w| <= (Q + 1) s and inv within 2 ulp of 1 / s; exact.
-//   n = rint(w * inv) is within one of it (the product is off by less than
-// 2^-21 of a quotient below 2^8).  The remainder w - n s is exact in fp32:
-// for n = 0 it is w; otherwise |w| > s / 4, so both w and n s (18 significant
-// bits) are multiples of u = min(ulp(w), ulp(s)) >= 2^-25 of the power of two
-// at or below s, and the remainder, below s, is a multiple of u small enough
-// for 24 bits wherever it decides (|r| <= s / 2 + 2^-13 s).  It is compared
-// with s / 2, exact as well: above, n moves towards w; at the tie, n moves if
-// it is odd.
+// fp16 value, |w| < 2^8 s and inv within 2 ulp of 1 / s; exact.  (|w| is at
+// most Q (1 + 2^-11) s for a normal scale, and 1.5 Q s for a subnormal one,
+// which may round down by a third; the clamp takes the excess.)
+//   n = rint(w * inv) is within one of it: the product is off by less than
+// 2^-21 of itself, 2^-13.  The remainder r = w - n s, at most s / 2 + 2^-13 s in
+// size wherever it decides, is then compared with s / 2: above, n moves towards
+// w; at the tie, n moves if it is odd.  r is exact in fp32.  With 2^E <= s <
+// 2^(E+1): for n = 0 it is w; otherwise |w| > s / 2 (1 - 2^-21), so w and n s
+// are multiples of 2^(E-24) and r, below 2^E, has 24 bits, unless s = 2^E and
+// |w| is just below s / 2: there n = +-1 and r rounds to s / 2 or more, and n
+// moves to 0 either way, as it has to.
 __device__ inline int nearest_code(float w, float s, float inv, float half_s, int Q)
 {
     const float n = __builtin_rintf(w * inv);
@@ -72,11 +74,11 @@ __device__ inline int nearest_code(float w, float s, float inv, float half_s, in
     return c < -Q ? -Q : c;
 }
 
-// The same for a bf16 x and Q = 127.  x has 8 significant bits, so a correctly
-// rounded fp32 quotient decides every rounding as the exact one would (a
-// non-half-integer quotient lies at least 2^-9 of its size from every
-// half-integer, and exact half-integers are representable); one Newton step
-// on x * inv with its exact remainder gives that quotient at every
+// The same for a bf16 x and Q = 127.  x has 8 significant bits and s 11, so that
+// a quotient above 1/4 that is no half-integer is at least 2^-12 from every one
+// (170 / 1.9208984375 = 88.50025...), while an fp32 quotient below 2^8 within an
+// ulp is within 2^-16 of it; exact half-integers are representable.  One Newton
+// step on x * inv with its exact remainder gives the quotient at every
 // half-integer, and within an ulp elsewhere.
 __device__ inline int nearest_code_bf16(float x, float s, float inv)
 {

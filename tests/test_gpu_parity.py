@@ -96,6 +96,27 @@ def test_quantize_bitexact_adversarial(gpu, orc, fmt):
     quantize_both(gpu, orc, fmt, W)
 
 
+@pytest.mark.parametrize("fmt", [O.FMT_INT8, O.FMT_Q4])
+def test_quantize_bitexact_subnormal_scales(gpu, orc, fmt):
+    """Scales of 0 to 4 times 2^-24, block maxima around every rounding of
+    absmax / Q (up to 1.5 Q s, beyond the range of the codes) and weights around
+    every half-integer of w / s."""
+    Q = QMAX[fmt]
+    rng = np.random.default_rng(3800 + fmt)
+    ulp = lambda x, n: np.float32(x) + np.float32(n) * np.spacing(np.float32(x))
+    rows = []
+    for half in range(1, 9):  # absmax / Q in units of 2^-25
+        for n in (-2, -1, 0, 1, 2):
+            top = ulp(half * 2.0 ** -25 * Q, n)
+            s = max(1, round(half / 2)) * 2.0 ** -24
+            c = rng.integers(-2 * Q - 2, 2 * Q + 3, 32) * 0.5 * s
+            b = np.array([ulp(v, k) if v else v for v, k in zip(c, rng.integers(-2, 3, 32))])
+            b = np.clip(b, -top, top).astype(np.float32)
+            b[0], b[31] = top, -top
+            rows.append(b)
+    quantize_both(gpu, orc, fmt, np.stack(rows).reshape(-1, 64))
+
+
 @pytest.mark.parametrize("name", ["single_int8", "single_q4"])
 def test_quantize_bitexact_single_configs(gpu, orc, name):
     cfg = getattr(si, name)()

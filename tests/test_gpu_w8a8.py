@@ -79,6 +79,36 @@ def test_quantize_act_bitexact(gpu, orc, xdt):
         assert np.array_equal(qg, qr), (M, K, np.argwhere(qg != qr)[:4])
 
 
+@pytest.mark.parametrize("xdt", [O.DT_BF16, O.DT_F32])
+def test_quantize_act_near_ties(gpu, orc, xdt):
+    """bf16 values whose quotient is closest to a half-integer (170 / 1.9209 =
+    88.50025: 2^-12 away) in rows whose maximum sets that scale, found by
+    search over the 8-bit values and 11-bit scales; and subnormal scales, whose
+    rows reach 1.5 * 127 times them."""
+    S, X = np.arange(1024, 2048) / 1024.0, np.arange(128, 256) / 128.0
+    rows = [np.array([170.0, 244.0])]
+    for e in range(-1, 7):
+        q = X[:, None] * 2.0 ** e / S[None, :]
+        near = np.abs((q - 0.5) - np.round(q - 0.5))
+        near[(near == 0) | (q > 126.5)] = 1.0
+        for i in np.argsort(near, axis=None)[:40]:
+            x, s = X[i // 1024] * 2.0 ** e, S[i % 1024]
+            top = si.bf16_bits_to_f32(si.f32_to_bf16_bits(np.float32([127 * s]))).astype(float)[0]
+            if float(np.float16(top / 127)) == s:  # a bf16 maximum that gives this scale
+                rows.append(np.array([x, top]))
+    assert len(rows) > 30
+    for half in range(1, 9):
+        top = half * 2.0 ** -25 * 127
+        rows.append(np.array([top, 0.5 * top]))
+    Xf = np.zeros((len(rows), 64), np.float32)
+    for m, r in enumerate(rows):
+        Xf[m, 3:63:4], Xf[m, 5:63:4], Xf[m, 0] = r[0], -r[0], r[1]
+    X = Xf if xdt == O.DT_F32 else si.f32_to_bf16_bits(Xf)
+    qg, sg = quant_act_gpu(gpu, X, xdt)
+    qr, sr = orc.quantize_act(X, xdt)
+    assert np.array_equal(sg, sr) and np.array_equal(qg, qr)
+
+
 def test_quantize_act_bad_rows(gpu, orc):
     """A row with a NaN or Inf, or whose scale would overflow fp16, gets the
     NaN scale and zero codes; the other rows are untouched."""
