@@ -28,8 +28,9 @@
  * an operand is not 16-byte aligned), are contracted with the exact codes
  * and fp32 block partials (error a few fp32 roundings); so are bf16
  * activations at larger M wherever an exact kernel is the faster one (most
- * layers and blocks up to a few hundred rows).  The others take the fp16
- * path: X is copied
+ * layers and blocks up to a few hundred rows).  A block's partial sum has to
+ * fit fp32: activations up to 7e34 in size with any codes (1e36 with q4 and
+ * fp32 X).  The others take the fp16 path, which has no such limit: X is copied
  * exactly to fp16 with a power-of-two shift per row, each weight enters the
  * matrix cores as fp16(c * fp16(s * 2^f)) with one shift f per weight row
  * and K part (the library may cut a long reduction into parts; Q * max_b s

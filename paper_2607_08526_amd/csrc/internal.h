@@ -148,8 +148,8 @@ int mid_wgs_per_cu();  // resident workgroups per CU
 hipError_t launch_qgemm_mid(int fmt, const GroupArgs &args, hipStream_t stream);
 
 // K-group kernel (qgemm_kg.hip: exact, no partials in memory): bf16 or fp32
-// activations and int8 / q4 weights, with the mid-M kernel's limits on K and
-// alignment; or fp16 weights, with X and xexp those of launch_xprep.
+// activations and int8 / q4 weights, with the mid-M kernel's alignment and
+// K < 2^22; or fp16 weights, with X and xexp those of launch_xprep.
 // LinDesc::psteps holds the layer's shape (a KgShape), and tiles_m, tiles_n
 // count its tiles (kg_tile_shape; {0, 0}: the launch has no such shape).
 enum KgShape { KG_R1W1, KG_R1W2, KG_R1W4, KG_R2W2, KG_R2W4, KG_R1C16, KG_SHAPES };

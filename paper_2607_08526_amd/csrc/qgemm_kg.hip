@@ -1,6 +1,7 @@
-// Quantized linear forward for few to a few hundred activation rows (bf16
-// X, int8 or q4 weights), in its exact per-block form, one launch and no
-// partial sums in memory:
+// Linear forward for few to a few hundred activation rows, in its exact
+// per-block form, one launch and no partial sums in memory (bf16 or fp32 X with
+// int8 or q4 weights; fp16 weights against the pre-pass's fp16 copy of a bf16
+// X):
 //
 //   Y[m][n] = sum_b s[n][b] * sum_{k in b} X[m][k] * c[n][k]
 //
@@ -21,7 +22,7 @@
 // because one wavefront issues a VALU instruction every ~5 cycles at best
 // while a SIMD takes one every 2 to 4 from several.
 //
-// Memory.  Activations, codes and scales of a stage (256 or 512 k) go to LDS
+// Memory.  Activations, codes and scales of a stage (256 to 1024 k) go to LDS
 // by direct-to-LDS loads of 16 bytes per lane, at least 128 contiguous bytes
 // per row, through a ring of NST stages; the loads of a stage go out spread
 // over the step before.  Up to 32 rows only the first XR = 8, 16 or 32 are
@@ -36,8 +37,9 @@
 // other kernel takes the q4 codes as they are, so does this one: 16 times them
 // would overflow a block's partial sum at 1/16 of the activations.
 //
-// Requirements (checked by the host): K % 256 == 0, K < 2^23, 16-byte
-// aligned X, codes and scales.
+// Requirements (checked by the host): K % 256 == 0, K < 2^22 (32-bit offsets
+// within a tile's fp32 activations or fp16 weights), 16-byte aligned X, codes
+// and scales.
 #include <algorithm>
 #include <type_traits>
 
@@ -76,8 +78,9 @@ struct KgGeo {
     static constexpr int XU = XBYTES / 1024, CU = CBYTES / 1024, SU = (SBYTES + 1023) / 1024;
     static constexpr int UNITS = XU + CU + SU, LOADS = (UNITS + WAVES - 1) / WAVES;
     static constexpr int RED = KG * TM * TN * 4;       // the groups' sums at the end
-    // two stages ahead (deeper rings were no faster, and a second workgroup
-    // fits a CU beside a small one)
+    // two stages ahead where they fit (deeper rings were no faster).  A launch
+    // holds the LDS of its largest shape, so that one workgroup is resident per
+    // CU (two only of q4's at 9 to 16 rows)
     static constexpr int SLOT = XBYTES + CBYTES + SU * 1024;
     static constexpr int NST = std::min(3, 160 * 1024 / SLOT), RING = NST * SLOT;
     static_assert(NST >= 2, "a stage ahead");
@@ -193,8 +196,8 @@ __device__ inline void kg_tile(const LinDesc &d, int tile, uint8_t *ring)
 
     // this wavefront's loads: per unit a base, a per-lane offset within the
     // stage's first columns, and the bytes a stage advances.  Rows past M and
-    // N repeat the last one; chunks past K (K % 512 == 256 and a 512-k stage)
-    // the last chunk, and are not used.
+    // N repeat the last one; chunks past K (a part-filled last stage) the last
+    // chunk, and are not used.
     const uint8_t *ub[G::LOADS];
     uint32_t urow[G::LOADS];
     int ucol[G::LOADS], ustep[G::LOADS], ulim[G::LOADS];

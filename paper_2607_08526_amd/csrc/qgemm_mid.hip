@@ -1,6 +1,6 @@
 // Quantized linear forward for a few hundred activation rows (bf16 X, int8
-// or q4 weights; the dispatch sends 64 < M <= mid_max_m()
-// here where the K-group kernel is not estimated faster):
+// or q4 weights; the dispatch sends short groups of 65 to 256 rows here where
+// the K-group kernel is not estimated faster):
 //
 //   Y[m][n] = sum_b s[n][b] * sum_{k in b} X[m][k] * c[n][k]
 //

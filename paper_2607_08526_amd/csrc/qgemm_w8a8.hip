@@ -13,7 +13,7 @@
 // (exact), converted and folded into an fp32 accumulator with one FMA per
 // output (scale of the lane's column); s_x[m] and the layer epilogue are
 // applied at the store.  The per-block rescale is what bounds this path:
-// 16 outputs per lane per MFMA cost two VALU instructions each (128 issue
+// 16 outputs per lane per MFMA cost two VALU instructions each (64 issue
 // cycles against the MFMA's 32), so a kernel can at best keep every SIMD's
 // VALU issuing: M N K / 32 * 2 lane operations.
 //
@@ -195,9 +195,10 @@ __global__ __launch_bounds__(THREADS, 2) void qgemm_w8a8_kernel(const W8Args a)
 // still gives every SIMD four wavefronts without partial sums in memory.
 //
 // Four wavefronts per SIMD because one wavefront issues a VALU instruction
-// every ~5 cycles at best, while the SIMD takes an fp32 add or FMA from
-// another wavefront every 2 (v_fma_mix_f32 and the int-to-float conversion
-// take 4: hence the explicit fp32 scales and the seeded accumulators below).
+// every ~5 cycles at best (2.0 to 2.2 ns measured), while the SIMD takes an fp32
+// add or FMA from several every 2 (1.02 to 1.06 ns; v_fma_mix_f32 and the
+// int-to-float conversion take 4, 1.83 ns: hence the explicit fp32 scales and
+// the seeded accumulators below).
 //
 // Activations, codes and scales go to LDS by direct-to-LDS loads through a
 // ring of NST stages of SB steps per group: at least 128 contiguous bytes of

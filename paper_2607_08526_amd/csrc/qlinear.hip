@@ -901,17 +901,18 @@ int launch_mid(const ql_linear_ep *const *ord, int n, WsSource &wsrc, hipStream_
 // plus its 256-k stages at the measured rate; one workgroup is resident per
 // CU.  For every shape of every layer, taken as the bound on the longest
 // workgroup, each other layer takes the shape of least total work within it;
-// the launch then lasts the longest
-// workgroup, or, with more workgroups than CUs, the work per CU plus half
-// the longest one (the tail).  Within 10% of the measured time on most of
-// 160 single layers and blocks (d = 512 to 2048, 5 to 640 rows).
+// the launch then lasts the longest workgroup, or, with more workgroups than
+// CUs, the work per CU plus half the longest one (the tail).  Within 25% of the
+// measured time on four in five of 6000 random layers and groups (1 to 2048
+// rows, K up to 65536); at the median 12% low above 64 bf16 rows, 9% low with
+// fp32 X and 15% high with fp16 weights, which kg_choose's lines take in.
 struct KgPlan {
     int shape[QL_MAX_GROUP];
     double us;
 };
 
 // Below 4 bf16 rows the GEMV is ahead (a d = 2048 block at 4 rows: int8 22.5 us,
-// q4 streamed 17.1, against about 16 and 14 here); beyond the upper bound the
+// q4 streamed 17.5, against 16.2 and 14.5 here); beyond the upper bound the
 // large-M kernel has a tile per CU for any layer of some width
 constexpr int64_t KG_MIN_M = 4, KG_MAX_M = 2048;
 
@@ -983,28 +984,31 @@ KgPlan kg_plan(int fmt, const ql_linear_ep *const *ls, int n)
 }
 
 // Whether a group (one format and activation type, kg_fits each, ordered as
-// launched) goes to the K-group kernel, and its shapes.  Measured on single
-// layers and blocks at 1 to 1000 rows, each against the kernel that ran
-// before:
+// launched) goes to the K-group kernel, and its shapes.  Measured on random
+// single layers and groups, each against the kernel that would run otherwise
+// (graphs of 12 calls over rotated weight copies).  "Slower" below: by more than
+// 4% than that kernel.
 //   bf16 X, up to 32 rows: where its estimate is under 0.8 of the streaming
 //     kernel's (blocks 1.1-1.7 times faster; single layers, which cannot fill
-//     the GPU with whole reductions, mostly stay: 2048 x 8192 at 8 rows 9.0 us
+//     the GPU with whole reductions, mostly stay: 2048 x 8192 at 8 rows 9.7 us
 //     streamed against 11.6).  For q4 at up to 16 rows its estimate is 0.5 us
-//     low: 1025 x 1280 at 9 rows stays, 5.5 us against 6.0;
+//     low: 1025 x 1280 at 9 rows stays, 5.5 us against 6.0.  3 of 800 slower;
 //   int8, bf16 X, four rows, where the streaming kernel is not the
 //     alternative: where 1.1 of its estimate (1.25 with K <= 2048, where it is
 //     low) and a margin are under the GEMV's (gemv4_int8_us; a d = 512 block
-//     6.6 us there against 7.5, d = 1024 12.5 against 9.6);
-//   bf16 X, 33 to 64 rows: always (1.3-2.4 times faster than the mid-M kernel);
+//     6.6 us there against 7.5, d = 1024 12.5 against 9.6; none of 300 slower);
+//   bf16 X, 33 to 64 rows: always (2.5 times faster than the mid-M kernel at K
+//     up to 8192, 1.6 up to 16384; 11 of 760 slower above, by up to 1.2 times);
 //   bf16 X above: where its estimate is under 8 us + 0.8 of the large-M plan's
-//     steps (up to 3 times faster: 768 x 768 at 500 rows 19.4 -> 5.9 us; no
-//     case of 260 where the rule picks the slower one);
+//     steps (up to 3 times faster: 768 x 768 at 500 rows 19.7 -> 6.2 us; 3 of
+//     1536 slower, 2619 x 768 at 1552 rows 32.4 us against 30.0);
 //   fp16 weights: under 12 us + the plan's steps (that kernel has one
-//     workgroup per CU there: 4608 x 1536 at 214 rows 27.2 -> 14.9 us, 2048 x
-//     8192 at 400 rows stays, 41 against 50);
+//     workgroup per CU there: 4608 x 1536 at 214 rows 27.4 -> 15.2 us, 2048 x
+//     8192 at 400 rows stays, 41 against 50; 5 of 806 slower, by up to 1.11);
 //   fp32 X, up to 32 rows: where its estimate and 1 us are under the tiled
 //     kernel's (4608 x 1536 at 16 rows 14.5 -> 8.9 us; 91 x 4352 at one row
-//     stays, 10.9 against 15.2, as does 2048 x 8192 at 8, 20.8 against 23.0);
+//     stays, 10.9 against 15.2, as does 2048 x 8192 at 8, 20.8 against 23.0;
+//     none of 432 slower);
 //   fp32 X above: where its estimate is under 14 us + 1.2 us per 64-k step of
 //     the tiled kernel's two workgroups per CU, and under 1.05 of the tiled
 //     kernel's own (1024 x 1024 at 64 rows 15.9 -> 6.8 us; 5855 x 256 at 416
