@@ -35,6 +35,7 @@
 // of 16 lanes, result lane 4q + p receives element p of the 8 bytes that
 // source lanes q, 4 + q, 8 + q and 12 + q address, so 16 lanes that
 // address 4 keys x 4 runs of 4 channels receive 4 keys of one channel each.
+#include "dma.h"
 #include "internal.h"
 
 namespace qlk {
@@ -69,28 +70,6 @@ __device__ inline uint32_t pack_bf16(float lo, float hi)
 {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
-
-// wave-uniform 64-bit base in an SGPR pair (readfirstlane returns int: widen
-// through uint32_t)
-__device__ inline uint64_t sbase(const void *p)
-{
-    const uint64_t v = (uint64_t)(uintptr_t)p;
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-    return (uint64_t)lo | ((uint64_t)hi << 32);
-}
-
-// Direct-to-LDS 16-byte load from (wave-uniform base + per-lane offset):
-// lane t's data lands at lds + t * 16.
-__device__ inline void dma16(const void *base, uint32_t off, uint32_t lds)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :
-                 : "v"(off), "s"(sbase(base)), "s"(__builtin_amdgcn_readfirstlane(lds))
-                 : "memory");
-}
-
-__device__ inline uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)p; }
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
@@ -183,7 +162,7 @@ void attention_kernel(const AttnArgs a)
         const uint8_t *const t = tbase + kt * tstep;
 #pragma unroll
         for (int j = 0; j < TLOADS; ++j)
-            dma16(t, o[j], lds_addr(buf) + (j * GT + wave * 64) * 16);
+            dma_load16(t, o[j], dma_lds(buf) + (j * GT + wave * 64) * 16);
     };
     auto fetch_k = [&](int kt, uint8_t *buf) { fetch(kt, kbase, ktile, a.ldk, true, kof, buf); };
     auto fetch_v = [&](int kt, uint8_t *buf) { fetch(kt, vbase, vtile, a.ldv, false, vof, buf); };

@@ -71,6 +71,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "dma.h"
 #include "epilogue.h"
 #include "internal.h"
 
@@ -120,13 +121,6 @@ struct MidGeo {
     static_assert(WGS * LDS <= 160 * 1024, "resident workgroups per CU");
 };
 
-__device__ inline constexpr int vmcnt_imm(int v)
-{
-    // gfx9 s_waitcnt encoding: vmcnt[3:0] + vmcnt[5:4] at bits 15:14;
-    // expcnt (bits 6:4) and lgkmcnt (bits 11:8) left at "no wait"
-    return (v & 15) | (((v >> 4) & 3) << 14) | (7 << 4) | (15 << 8);
-}
-
 // physical 16-byte chunk = logical ^ swizzle(row)
 __device__ inline int xswz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
 template <int FMT>
@@ -134,28 +128,6 @@ __device__ inline int cswz(int row)
 {
     return FMT == QL_FMT_INT8 ? ((row >> 1) ^ (row >> 3)) & 3 : ((row >> 2) ^ (row >> 3)) & 1;
 }
-
-// wave-uniform 64-bit base in an SGPR pair (readfirstlane returns int: widen
-// through uint32_t)
-__device__ inline uint64_t sbase(const void *p)
-{
-    const uint64_t v = (uint64_t)(uintptr_t)p;
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-    return (uint64_t)lo | ((uint64_t)hi << 32);
-}
-
-// Direct-to-LDS 16-byte load from (wave-uniform base + per-lane offset):
-// lane t's data lands at lds + t * 16.
-__device__ inline void dma16(const void *base, uint32_t off, uint32_t lds)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :
-                 : "v"(off), "s"(sbase(base)), "s"(__builtin_amdgcn_readfirstlane(lds))
-                 : "memory");
-}
-
-__device__ inline uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)p; }
 
 __device__ inline f32x16 mfma(u32x4 a, u32x4 b, f32x16 c)
 {
@@ -228,18 +200,18 @@ template <int FMT, bool SC>
 __device__ inline void issue(const MidCtx<FMT> &c, uint8_t *stage, int s)
 {
     using G = MidGeo<FMT>;
-    const uint32_t base = lds_addr(stage);
+    const uint32_t base = dma_lds(stage);
     const uint8_t *xb = c.xb + s * 128;
     const uint8_t *cb = c.cb + s * G::CROW;
 #pragma unroll
     for (int r = 0; r < G::XLOADS; ++r)
-        dma16(xb, c.xoff[r], base + (r * THREADS + c.wave * 64) * 16);
+        dma_load16(xb, c.xoff[r], base + (r * THREADS + c.wave * 64) * 16);
 #pragma unroll
     for (int r = 0; r < G::CLOADS; ++r)
-        dma16(cb, c.coff[r], base + G::XBYTES + (r * THREADS + c.wave * 64) * 16);
+        dma_load16(cb, c.coff[r], base + G::XBYTES + (r * THREADS + c.wave * 64) * 16);
     if constexpr (SC)
-        dma16(c.sb + (s / SGROUP) * 16, c.soff,
-              lds_addr(c.sring + ((s / SGROUP) % SRING) * G::SSLOT) + c.wave * 64 * 16);
+        dma_load16(c.sb + (s / SGROUP) * 16, c.soff,
+                   dma_lds(c.sring + ((s / SGROUP) % SRING) * G::SSLOT) + c.wave * 64 * 16);
 }
 
 // Activation fragments of block bl, chunks h = 0, 1, row blocks i = 0, 1.
@@ -421,12 +393,12 @@ __device__ inline void wait_stage(int y)
     using G = MidGeo<FMT>;
     if constexpr (Y > 0) {
         if (y == Y) {
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(Y * G::LOADS + (U + Y) / SGROUP));
+            __builtin_amdgcn_s_waitcnt(dma_vmcnt(Y * G::LOADS + (U + Y) / SGROUP));
             return;
         }
         wait_stage<FMT, U, Y - 1>(y);
     } else {
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        __builtin_amdgcn_s_waitcnt(dma_vmcnt(0));
     }
 }
 

@@ -45,6 +45,7 @@
 #include <algorithm>
 #include <cmath>
 
+#include "dma.h"
 #include "epilogue.h"
 #include "internal.h"
 
@@ -54,34 +55,6 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-__device__ inline constexpr int vmcnt_imm(int v)
-{
-    // gfx9 s_waitcnt encoding: vmcnt[3:0] + vmcnt[5:4] at bits 15:14;
-    // expcnt (bits 6:4) and lgkmcnt (bits 11:8) left at "no wait"
-    return (v & 15) | (((v >> 4) & 3) << 14) | (7 << 4) | (15 << 8);
-}
-
-// wave-uniform 64-bit base in an SGPR pair (readfirstlane returns int:
-// widen through uint32_t)
-__device__ inline uint64_t sbase(const void *p)
-{
-    const uint64_t v = (uint64_t)(uintptr_t)p;
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-    return (uint64_t)lo | ((uint64_t)hi << 32);
-}
-
-// Direct-to-LDS 16-byte load: the active lane t's data lands at lds + t * 16.
-__device__ inline void dma16(const void *base, uint32_t off, uint32_t lds)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :
-                 : "v"(off), "s"(sbase(base)), "s"(__builtin_amdgcn_readfirstlane(lds))
-                 : "memory");
-}
-
-__device__ inline uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)p; }
 
 __device__ inline f32x4 mfma(u32x4 a, u32x4 b, f32x4 c)
 {
@@ -213,10 +186,10 @@ __device__ __forceinline__ void stream_body(const LinDesc &d, const int wg)
 #pragma unroll
         for (int r = 0; r < G::NCI; ++r)
             if (cact[r])
-                dma16(cbase + c * G::CB, coff[r], lds_addr(st) + r * 1024);
+                dma_load16(cbase + c * G::CB, coff[r], dma_lds(st) + r * 1024);
 #pragma unroll
         for (int r = 0; r < G::NXI; ++r)
-            dma16(xbase + c * G::XROW, xoff[r], lds_addr(st + G::CODE) + r * 1024);
+            dma_load16(xbase + c * G::XROW, xoff[r], dma_lds(st + G::CODE) + r * 1024);
         if (c % 8 == 0) {
             // scales of blocks bw0 + 4c .. + 31 (pieces past the row end
             // repeat its last piece; their values are never read)
@@ -227,8 +200,8 @@ __device__ __forceinline__ void stream_body(const LinDesc &d, const int wg)
                 const int dn = min(n0 + min(sj, RW - 1), N - 1) - n0;
                 const int b = min(bw0 + 32 * g + 8 * ((sp ^ ((sj >> 2) & 3))), nb - 8);
                 if (sj < RW)
-                    dma16(sbase8, (uint32_t)(dn * nb * 2 + b * 2),
-                          lds_addr(sring + (g & 1) * G::SLOT) + h * 1024);
+                    dma_load16(sbase8, (uint32_t)(dn * nb * 2 + b * 2),
+                               dma_lds(sring + (g & 1) * G::SLOT) + h * 1024);
             }
         }
     };
@@ -236,12 +209,12 @@ __device__ __forceinline__ void stream_body(const LinDesc &d, const int wg)
     // stage waits: all but the loads of the `younger` chunks issued after c
     auto wait_younger = [&](int younger) {
         switch (younger) {
-        case 0: __builtin_amdgcn_s_waitcnt(vmcnt_imm(0)); break;
-        case 1: __builtin_amdgcn_s_waitcnt(vmcnt_imm(1 * G::N)); break;
-        case 2: __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * G::N)); break;
-        case 3: __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * G::N)); break;
-        case 4: __builtin_amdgcn_s_waitcnt(vmcnt_imm(4 * G::N)); break;
-        default: __builtin_amdgcn_s_waitcnt(vmcnt_imm(5 * G::N)); break;
+        case 0: __builtin_amdgcn_s_waitcnt(dma_vmcnt(0)); break;
+        case 1: __builtin_amdgcn_s_waitcnt(dma_vmcnt(1 * G::N)); break;
+        case 2: __builtin_amdgcn_s_waitcnt(dma_vmcnt(2 * G::N)); break;
+        case 3: __builtin_amdgcn_s_waitcnt(dma_vmcnt(3 * G::N)); break;
+        case 4: __builtin_amdgcn_s_waitcnt(dma_vmcnt(4 * G::N)); break;
+        default: __builtin_amdgcn_s_waitcnt(dma_vmcnt(5 * G::N)); break;
         }
     };
 

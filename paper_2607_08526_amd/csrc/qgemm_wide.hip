@@ -73,6 +73,7 @@
 // end of the kernel).
 #include <algorithm>
 
+#include "dma.h"
 #include "epilogue.h"
 #include "internal.h"
 
@@ -137,13 +138,6 @@ struct Geo {
     static_assert(wgs_per_cu<FMT>() * LDS <= 160 * 1024, "resident workgroups per CU");
 };
 
-__device__ inline constexpr int vmcnt_imm(int v)
-{
-    // gfx9 s_waitcnt encoding: vmcnt[3:0] + vmcnt[5:4] at bits 15:14;
-    // expcnt (bits 6:4) and lgkmcnt (bits 11:8) left at "no wait"
-    return (v & 15) | (((v >> 4) & 3) << 14) | (7 << 4) | (15 << 8);
-}
-
 // 16-byte chunk swizzles (physical chunk = logical ^ swz(row)); each keeps
 // the reads described above free of bank conflicts for 32 or 64 banks
 __device__ inline int xswz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
@@ -153,33 +147,6 @@ __device__ inline int cswz(int row)
     if constexpr (FMT == QL_FMT_F16)
         return xswz(row);  // 8 chunks per row, as the activations
     return FMT == QL_FMT_INT8 ? ((row >> 1) ^ (row >> 3)) & 3 : ((row >> 2) ^ (row >> 3)) & 1;
-}
-
-// Direct-to-LDS loads from (wave-uniform base + per-lane 32-bit offset):
-// lane t's data lands at LDS address lds + t * size.
-// The base is wave-uniform by construction; readfirstlane makes that
-// visible to the compiler so it always lands in an SGPR pair.
-__device__ inline uint64_t sbase(const void *p)
-{
-    const uint64_t v = (uint64_t)(uintptr_t)p;
-    // readfirstlane returns int: widen through uint32_t (no sign extension)
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-    return (uint64_t)lo | ((uint64_t)hi << 32);
-}
-
-__device__ inline void dma16(const void *base, uint32_t off, uint32_t lds)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :
-                 : "v"(off), "s"(sbase(base)), "s"(__builtin_amdgcn_readfirstlane(lds))
-                 : "memory");
-}
-
-__device__ inline uint32_t lds_addr(const void *p)
-{
-    // a generic pointer into LDS carries the LDS offset in its low 32 bits
-    return (uint32_t)(uintptr_t)p;
 }
 
 __device__ inline f32x16 mfma32(u32x4 a, u32x4 b, f32x16 c)
@@ -241,21 +208,21 @@ template <int FMT, bool SCALES>
 __device__ inline void issue_stage(const Ctx<FMT> &c, uint8_t *stage, int s)
 {
     using G = Geo<FMT>;
-    const uint32_t base = lds_addr(stage);
+    const uint32_t base = dma_lds(stage);
     const uint8_t *xb = c.xbase + s * 128;  // 64 fp16 per row per step
     const uint8_t *cb = c.cbase + s * G::CROW;
 #pragma unroll
     for (int r = 0; r < G::XLOADS; ++r)
-        dma16(xb, c.xoff[r], base + (r * THREADS + c.wave * 64) * 16);
+        dma_load16(xb, c.xoff[r], base + (r * THREADS + c.wave * 64) * 16);
 #pragma unroll
     for (int r = 0; r < G::CLOADS; ++r)
-        dma16(cb, c.coff[r], base + G::XBYTES + (r * THREADS + c.wave * 64) * 16);
+        dma_load16(cb, c.coff[r], base + G::XBYTES + (r * THREADS + c.wave * 64) * 16);
     if constexpr (SCALES) {
         const int g = s / G::SGROUP;
 #pragma unroll
         for (int h = 0; h < G::SPT; ++h)
-            dma16(c.sbase + g * 16, c.soff[h],
-                  lds_addr(c.sring + (g & 1) * G::SSLOT) + (h * THREADS + c.wave * 64) * 16);
+            dma_load16(c.sbase + g * 16, c.soff[h],
+                       dma_lds(c.sring + (g & 1) * G::SSLOT) + (h * THREADS + c.wave * 64) * 16);
     }
 }
 
@@ -474,9 +441,9 @@ __device__ inline void step(const Ctx<FMT> &c, uint8_t *ring, int s, int &slot, 
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if constexpr (YOUNGER)
             __builtin_amdgcn_s_waitcnt(
-                vmcnt_imm(G::LOADS + ((U + 2) % G::SGROUP == 0 ? G::SPT : 0)));
+                dma_vmcnt(G::LOADS + ((U + 2) % G::SGROUP == 0 ? G::SPT : 0)));
         else
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            __builtin_amdgcn_s_waitcnt(dma_vmcnt(0));
         __builtin_amdgcn_s_barrier();
         if constexpr (ISSUE)
             issue_stage<FMT, (U + NST) % G::SGROUP == 0>(c, ring + slot * G::STAGE, s + NST);
@@ -576,8 +543,8 @@ __global__ __launch_bounds__(THREADS, wgs_per_cu<FMT>()) void qgemm_wide_kernel(
     static_assert(FMT == QL_FMT_F16 || BN * 4 == 64 * 16, "one 16-byte load per lane of a wavefront");
     if constexpr (FMT != QL_FMT_F16)
         if (c.wave == 0)
-            dma16(d.wshift + (int64_t)part * d.wsld + n0, (uint32_t)(tid & 63) * 16,
-                  lds_addr(c.sring + G::SSLOT));
+            dma_load16(d.wshift + (int64_t)part * d.wsld + n0, (uint32_t)(tid & 63) * 16,
+                       dma_lds(c.sring + G::SSLOT));
     // ns >= 4 > NST: every ring slot gets its first stage
     issue_stage<FMT, true>(c, ring, 0);
 #pragma unroll
@@ -600,7 +567,7 @@ __global__ __launch_bounds__(THREADS, wgs_per_cu<FMT>()) void qgemm_wide_kernel(
     // flight (ns >= 4 > NST - 1: K parts are whole scale groups); the
     // shifts, issued before stage 0, have landed with it.
     static_assert(NST == 2 || NST == 3, "wait counts cover at most one younger stage");
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 1) * G::LOADS));
+    __builtin_amdgcn_s_waitcnt(dma_vmcnt((NST - 1) * G::LOADS));
     __builtin_amdgcn_s_barrier();
 #pragma unroll
     for (int j = 0; j < NSUB; ++j)  // (fp16 weights enter as they are)
