@@ -891,10 +891,10 @@ def block_int8(torch, ql, si):
             "weight_GBps": round(wbytes / t / 1e9, 1), "copies": R}
 
 
-# non-packed fp32 VALU lane operations per second: 256 CUs x 4 SIMDs x 16
-# lanes x 2.4 GHz (the published 157.3 TFLOP/s counts packed FMAs, which this
-# build does not emit)
-VALU_LANE_OPS = 256 * 4 * 16 * 2.4e9
+# fp32 add or FMA lane operations per second: 256 CUs x 4 SIMDs x 32 lanes x
+# 2.4 GHz (half the published 157.3 TFLOP/s; a wavefront's instruction every 2
+# cycles per SIMD, as measured with four wavefronts)
+VALU_LANE_OPS = 256 * 4 * 32 * 2.4e9
 INT8_MFMA_PEAK_TOPS = 5000.0
 
 
@@ -938,7 +938,7 @@ def block_w8a8(torch, ql, si):
     t_g = graph_time(torch, lambda: [gemms(w) for w in wcopies])[0] / R
     M = xa.shape[0]
     mnk = sum(M * N * K for _, N, K in lin)
-    valu_floor_us = mnk / 16 / VALU_LANE_OPS * 1e6  # cvt + FMA per output per 32-k block
+    valu_floor_us = mnk / 16 / VALU_LANE_OPS * 1e6  # subtract + FMA per output per 32-k block
     tops = 2.0 * mnk / (t_all * 1e-3) / 1e12
     return {"note": "per-token int8 activations x int8 block-32 weights: activation "
                     "quantization (both X) + 4 int8-MFMA products, same inputs as block_int8",
