@@ -166,3 +166,32 @@ def test_kgroup_fp32_large_activations(gpu, orc, fmt):
         Y = Y.cpu().numpy().astype(np.float64)
         assert np.isfinite(Y).all()
         assert np.all(np.abs(Y - Yr) <= B)
+
+
+@pytest.mark.parametrize("fmt", [O.FMT_Q4, O.FMT_INT8])
+@pytest.mark.parametrize("M", [1, 4, 16, 48, 100, 300])
+def test_activations_at_the_stated_limit(gpu, fmt, M):
+    """bf16 activations of 7e34 with the largest codes, all of one sign: the
+    size up to which every exact kernel's block sums fit fp32
+    (include/qlinear.h), offset forms included.  Y is K x c s, from the library's
+    own choice and from every exact kernel that takes the call, within the bound
+    above, twice for the offset forms' larger codes (up to 255 for 127)."""
+    torch, ql = gpu
+    N, K, Q, s = 96, 512, 7 if fmt == O.FMT_Q4 else 127, 2.0 ** -10
+    X = torch.full((M, K), 7e34, device="cuda").to(torch.bfloat16)
+    scales = torch.full((N, K // 32), s, dtype=torch.float16, device="cuda").view(torch.int16)
+    paths = [ql.PATH_AUTO, ql.PATH_TILED, ql.PATH_MID]
+    paths += [ql.PATH_GEMV] if M <= 4 else []
+    paths += [ql.PATH_STREAM, ql.PATH_SKINNY] if M <= 32 else []
+    want = float(X[0, 0]) * K * Q * s
+    for sign in (1, -1):
+        if fmt == O.FMT_Q4:
+            codes = torch.full((N, K // 2), 17 * (sign * Q & 15), dtype=torch.uint8, device="cuda")
+        else:
+            codes = torch.full((N, K), sign * Q, dtype=torch.int8, device="cuda").view(torch.uint8)
+        for path in paths:
+            with ql.forced_path(path):
+                Y = ql.forward(fmt, X, codes, scales, N)
+            torch.cuda.synchronize()
+            err = np.abs(Y.cpu().numpy().astype(np.float64) - sign * want)
+            assert np.all(err <= 2 * (K // 32 + 48) * 2.0 ** -24 * want), (path, sign)
