@@ -218,11 +218,14 @@ def check_end_to_end(orc, model, h0, h_final, B, T, alpha, steer_block):
     return err
 
 
-@pytest.mark.parametrize("B,T", [(2, 96), (2, 12)])
-def test_dit_chain_graph_with_steering(gpu, orc, B, T):
+CHAINS = [(2, 96, 5), (2, 96, 0), (2, 12, 0)]  # B, T, forced path (5 the large-M kernel)
+
+
+@pytest.mark.parametrize("B,T,path", CHAINS)
+def test_dit_chain_graph_with_steering(gpu, orc, B, T, path):
     """Two chained blocks at d = 256 (4 heads): 2 x 96 tokens (every linear
-    on the large-M fp16 path) and 2 x 12 tokens (the few-row kernels).  The
-    chain is captured once; replays at strength 0, 0.25 and 0 again each
+    on the large-M fp16 path, and on the K-group kernel) and 2 x 12 tokens (the
+    few-row kernels).  The chain is captured once; replays at strength 0, 0.25 and 0 again each
     equal an eager run at the same strength bit for bit, and pass both
     checks.  Steering changes only what follows the steered block, and
     strength 0 gives back the unsteered result bit for bit."""
@@ -230,7 +233,12 @@ def test_dit_chain_graph_with_steering(gpu, orc, B, T):
     d, steer_block = 256, 0
     model = Model(gpu, orc, d, 2, 4200 + T)
     h0 = np.random.default_rng(4300 + T).standard_normal((B * T, d)).astype(np.float32)
-    st, run, strength = gpu_chain(gpu, model, h0, B, T, steer_block)
+    st, run_free, strength = gpu_chain(gpu, model, h0, B, T, steer_block)
+
+    def run():
+        with ql.forced_path(path):
+            run_free()
+
     s = torch.cuda.Stream()
     s.wait_stream(torch.cuda.current_stream())
     eager = {}

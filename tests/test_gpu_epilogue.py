@@ -143,8 +143,8 @@ def test_epilogue_f16_weights(gpu, orc):
                 check(Yg, Pr, Yr, bias, O.DT_BF16, ydt == "bf16", (M, N, K, ydt, path))
 
 
-@pytest.mark.parametrize("M", [3, 16, 40, 200])
-def test_epilogue_exact_and_bf16_rounding(gpu, orc, M):
+@pytest.mark.parametrize("M,path", [(3, AUTO), (16, AUTO), (40, AUTO), (200, AUTO), (200, WIDE)])
+def test_epilogue_exact_and_bf16_rounding(gpu, orc, M, path):
     """W = c * 2^-12 with integer activations, an integer bias and residual:
     P + bias + residual is exact in fp32, so fp32 outputs must equal it and
     bf16 outputs must be its round-to-nearest-even bf16 value (torch's CPU
@@ -163,9 +163,10 @@ def test_epilogue_exact_and_bf16_rounding(gpu, orc, M):
     exact = ((Xi.astype(np.int64) @ C.T) * 2.0 ** -12 + bias.astype(np.float64)[None, :]
              + resid.astype(np.float64))
     assert np.array_equal(exact.astype(np.float32).astype(np.float64), exact)
-    Yf = run_ep(gpu, O.FMT_INT8, X, O.DT_BF16, cd, sd, N, bias, O.ACT_NONE, resid, "f32")
+    with ql.forced_path(path):
+        Yf = run_ep(gpu, O.FMT_INT8, X, O.DT_BF16, cd, sd, N, bias, O.ACT_NONE, resid, "f32")
+        Yb = run_ep(gpu, O.FMT_INT8, X, O.DT_BF16, cd, sd, N, bias, O.ACT_NONE, resid, "bf16")
     assert np.array_equal(Yf, exact)
-    Yb = run_ep(gpu, O.FMT_INT8, X, O.DT_BF16, cd, sd, N, bias, O.ACT_NONE, resid, "bf16")
     want = torch.from_numpy(exact.astype(np.float32)).to(torch.bfloat16).float().numpy()
     assert np.array_equal(Yb, want.astype(np.float64))
 

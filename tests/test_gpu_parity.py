@@ -392,18 +392,19 @@ def test_forward_block_scales_far_apart(gpu, orc, fmt):
 @pytest.mark.parametrize("xdt", [O.DT_BF16, O.DT_F32])
 def test_forward_power_of_two_exact(gpu, orc, fmt, xdt):
     """W = c * 2^-12, integer X: the exact result is representable, so the
-    GPU must reproduce it exactly."""
+    GPU must reproduce it exactly, the large-M path (M = 200) included."""
     Q = QMAX[fmt]
     rng = np.random.default_rng(17 + fmt + xdt)
     N, K = 80, 512
-    for M in (5, 40, 200):
+    for M, path in ((5, AUTO), (40, AUTO), (200, AUTO)) + \
+            (((200, WIDE),) if xdt == O.DT_BF16 else ()):
         C = rng.integers(-Q, Q + 1, (N, K))
         C.reshape(N, K // 32, 32)[:, :, 3] = rng.choice([-Q, Q], (N, K // 32))
         W = (C * 2.0 ** -12).astype(np.float32)
         codes, scales = quantize_both(gpu, orc, fmt, W)
         Xi = rng.integers(-8, 9, (M, K)).astype(np.float32)
         X = Xi if xdt == O.DT_F32 else si.f32_to_bf16_bits(Xi)
-        Yg = forward_gpu(gpu, fmt, X, xdt, codes, scales, N)
+        Yg = forward_gpu(gpu, fmt, X, xdt, codes, scales, N, path)
         want = (Xi.astype(np.int64) @ C.T).astype(np.float64) * 2.0 ** -12
         assert np.array_equal(Yg.astype(np.float64), want)
         assert np.array_equal(Yg.astype(np.float64), orc.forward(fmt, X, xdt, codes, scales, N))
@@ -509,9 +510,10 @@ def test_forward_deterministic(gpu, orc):
     torch, ql = gpu
     W, X = si.small_case(5, 300, 520, 1024, O.DT_BF16)
     codes, scales = orc.quantize(O.FMT_Q4, W)
-    a = forward_gpu(gpu, O.FMT_Q4, X, O.DT_BF16, codes, scales, 520)
-    b = forward_gpu(gpu, O.FMT_Q4, X, O.DT_BF16, codes, scales, 520)
-    assert np.array_equal(a, b)
+    for path in (AUTO, WIDE, MID):
+        a = forward_gpu(gpu, O.FMT_Q4, X, O.DT_BF16, codes, scales, 520, path)
+        b = forward_gpu(gpu, O.FMT_Q4, X, O.DT_BF16, codes, scales, 520, path)
+        assert np.array_equal(a, b), path
 
 
 def test_forward_on_side_stream(gpu, orc):

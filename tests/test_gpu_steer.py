@@ -14,6 +14,7 @@ import pytest
 
 import synth_inputs as si
 from oracle import oracle as O
+from test_gpu_epilogue import AUTO, PATHS, WIDE
 
 pytestmark = pytest.mark.gpu
 
@@ -77,21 +78,9 @@ def test_steer_op(gpu, orc, N):
         assert np.isnan(hg[1, 1]) and hg[2, 2] == np.inf
 
 
-# (fmt, xdt, M, N, K): each kernel that stores final outputs
-PATHS = [
-    (O.FMT_Q4, O.DT_BF16, 3, 4097, 2048),     # GEMV
-    (O.FMT_INT8, O.DT_BF16, 16, 4100, 512),   # weight streaming, one K part
-    (O.FMT_Q4, O.DT_BF16, 8, 2048, 8192),     # weight streaming + split sum
-    (O.FMT_INT8, O.DT_BF16, 20, 70, 320),     # small-M MFMA
-    (O.FMT_Q4, O.DT_F32, 40, 200, 320),       # MFMA kernel, fp32 activations
-    (O.FMT_Q4, O.DT_BF16, 300, 520, 1280),    # fp16 path
-    (O.FMT_INT8, O.DT_BF16, 300, 520, 4096),  # fp16 path, parts summed by split sum
-    (O.FMT_Q4, O.DT_BF16, 129, 17, 1024),     # fp16 path, element-by-element store
-]
-
-
-@pytest.mark.parametrize("fmt,xdt,M,N,K", PATHS)
-def test_steer_in_epilogue(gpu, orc, fmt, xdt, M, N, K):
+# every kernel that stores final outputs, by forced path
+@pytest.mark.parametrize("fmt,xdt,M,N,K,path", PATHS)
+def test_steer_in_epilogue(gpu, orc, fmt, xdt, M, N, K, path):
     torch, ql = gpu
     W, X = si.small_case(8100 + M + N + K, M, N, K, xdt)
     cd, sd = ql.quantize(fmt, dev_f32(torch, W))
@@ -110,11 +99,13 @@ def test_steer_in_epilogue(gpu, orc, fmt, xdt, M, N, K):
                              (False, False, O.ACT_NONE, torch.float32),
                              (True, False, O.ACT_GELU, torch.bfloat16)):
         kw = dict(bias=bd if b_ else None, residual=rd if r_ else None, act=act, ydtype=ydt)
-        plain = ql.forward_ep(fmt, Xd, cd, sd, N, **kw)
+        with ql.forced_path(path):
+            plain = ql.forward_ep(fmt, Xd, cd, sd, N, **kw)
         base = orc.epilogue(P, bias if b_ else None, act, resid if r_ else None)
         for alpha in (0.0, 0.25):
             strength.fill_(alpha)
-            Y = ql.forward_ep(fmt, Xd, cd, sd, N, steer=(dd, hnorm, strength), **kw)
+            with ql.forced_path(path):
+                Y = ql.forward_ep(fmt, Xd, cd, sd, N, steer=(dd, hnorm, strength), **kw)
             torch.cuda.synchronize()
             if alpha == 0.0:
                 assert torch.equal(Y.view(torch.int16) if ydt == torch.bfloat16 else Y.view(
@@ -128,7 +119,7 @@ def test_steer_in_epilogue(gpu, orc, fmt, xdt, M, N, K):
                 + steer_bound(d, hnorm, alpha, Yr)
             if ydt == torch.bfloat16:
                 lim = lim + 2.0 ** -8 * np.abs(Yr)
-            assert np.all(np.abs(Yg - Yr) <= lim), (M, N, K, b_, act)
+            assert np.all(np.abs(Yg - Yr) <= lim), (M, N, K, path, b_, act)
 
 
 def test_steer_w8a8(gpu, orc):
@@ -153,12 +144,14 @@ def test_steer_w8a8(gpu, orc):
     assert np.all(np.abs(Y.cpu().numpy() - Yr) <= lim)
 
 
-def test_steer_graph_strength_refresh(gpu, orc):
+@pytest.mark.parametrize("path", [AUTO, WIDE])
+def test_steer_graph_strength_refresh(gpu, orc, path):
     """One block's grouped call with steering on the FFN-down output, and the
     steering operation on a residual stream, captured once in a HIP graph;
     every replay re-reads the strength: replays at alpha = 0.5, 0, 1, 0
     equal eager calls at those strengths bit for bit, and alpha = 0 equals
-    the unsteered call."""
+    the unsteered call.  On the library's own choice (the K-group kernel) and
+    on the large-M path, with its workspace."""
     torch, ql = gpu
     M, d_model = 256, 512
     rng = np.random.default_rng(8300)
@@ -186,7 +179,8 @@ def test_steer_graph_strength_refresh(gpu, orc):
     h = h0.clone()
 
     def step():
-        ql.block_forward_ep(None, group=grp)
+        with ql.forced_path(path):
+            ql.block_forward_ep(None, group=grp)
         h.copy_(h0)
         ql.steer(h, dvec, 3.0, strength)
 
@@ -200,7 +194,8 @@ def test_steer_graph_strength_refresh(gpu, orc):
         torch.cuda.synchronize()
         eager[alpha] = snapshot()
     Yp, gp = make(False)
-    ql.block_forward_ep(None, group=gp)
+    with ql.forced_path(path):
+        ql.block_forward_ep(None, group=gp)
     torch.cuda.synchronize()
     for a, b in zip(eager[0.0][:4], [Y.cpu().numpy() for Y in Yp]):
         assert np.array_equal(a.view(np.uint32), b.view(np.uint32))

@@ -27,6 +27,7 @@ import numpy as np
 import pytest
 
 import kgroup_cases
+import test_gpu_dit_chain
 import test_gpu_epilogue
 import test_gpu_parity
 import test_zz_no_alloc
@@ -295,6 +296,12 @@ def test_gpu_tests_reach_what_they_are_for(probe):
             assert v is None or [x for _, x in got] == v, (c, got)
             if k in ("mid", "wideext") and c[4] != [(65, 130, 256)] and v is None:
                 assert all(x > 1 or K < 1024 for K, x in got), (c, got)  # parts, in a workspace
+    # the chained step's linears, one call each, and the steered block
+    for (B, T, p), kernel in zip(test_gpu_dit_chain.CHAINS, ("wide", "kg", "rows")):
+        got = routes(probe, [(Q4, 0, 1, p, [(B * T, N, K)]) for N, K in block(256)])
+        assert all(k.startswith(kernel) for k, _ in got), (B, T, p, got)
+    got = routes(probe, [(Q4, 0, 1, p, [(256, N, K) for N, K in block(512)]) for p in (AUTO, WIDE)])
+    assert [k for k, _ in got] == ["kg", "wideext"], got
     names = {ep.GEMV: ("rows", 0), ep.STREAM: ("rows", 1), ep.SKINNY: ("rows", 2),
              ep.TILED: ("tiled", None), ep.WIDE: ("wide", None), ep.MID: ("mid", None),
              ep.AUTO: ("kg", None)}
